@@ -28,28 +28,19 @@ void cast_d2f(const cd* a, cf* b, long long n, hipStream_t st);
 void cast_f2d(const cf* a, cd* b, long long n, hipStream_t st);
 void square_slowness(const double* kap, double* m64, float* m32, long long n, int is_m, hipStream_t st);
 void nd_zero(cd* p, long long n, hipStream_t s);
-void nd_iota(int* perm, const NDFrontDev* fr, int nfronts, hipStream_t s);
-void nd_assemble(const NDFrontDev* fr, const int* ids, int nids, int max_asm, const NDAsm* asmv, const cd* coef,
-                 cd* Fp, hipStream_t s);
-void nd_extend(const NDFrontDev* fr, const int* ids, int nids, long long max_nb2, const int* children,
-               const long long* child_map_off, const int* maps, cd* Fp, int slot, hipStream_t s);
-// Fp: the fronts; Pb: a panel buffer of max_nF (rounded to 32) x kb entries per front;
-// cand: two candidate sets of nids x ceil(max_nF / 32)
-void nd_panel_multi(const NDFrontDev* fr, int nids, int max_nF, cd* Fp, cd* Pb, int* perm, int* swp,
-                    PivCand* cand, int k0, int kb, int max_nS, int* err, hipStream_t s);
-void nd_save_t(const NDFrontDev* fr, const int* ids, int nids, const long long* toff, long long max_n, cd* Fp,
-               cd* T, int k0, int kb, int u0, int un, hipStream_t s);
-void nd_gemm(const NDFrontDev* fr, const int* ids, int nids, const long long* toff, int max_rows, int max_cols,
-             cd* Fp, const cd* T, int k0, int kb, int u0, int un, hipStream_t s);
+void nd_fill_int(int* p, long long n, int x, hipStream_t s);
+void nd_assemble(const NDInv& v, int nids, int max_asm, const NDAsm* asmv, const cd* coef, hipStream_t s);
+void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, long long max_nb2, const int* children,
+               const long long* child_map_off, const int* maps, int slot, hipStream_t s);
+// A^-1 of the height's fronts (in exchanged order), in blocks of block_cols columns; returns
+// the block width used, which nd_products takes
+int nd_invert(const NDInv& v, int nids, int max_nS, int max_wn, int block_cols, hipStream_t s);
 template <typename C>
-void nd_finalize(const NDFrontDev* fr, const int* ids, int nids, long long max_n, const cd* Fp, const int* perm,
+void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, int sym, const long long* toff, cd* T,
                  C* Lp, C* Wp, hipStream_t s);
 template <typename C>
 void nd_fwd(const NDLaunchDev& L, const NDFrontDev* fr, const int* idx, const int* cptr, const int* cidx,
             const C* Lp, C* upd, const C* r, C* x, C* gvec, int cap, int conj, C* P, const NDRhs& rh, hipStream_t s);
-int panel_reg_kb(int nF);
-void nd_panel_reg(const NDFrontDev* fr, const int* ids, int nids, int max_nF, cd* Fp, int* perm, int* swp, int k0,
-                  int kb, int* err, hipStream_t s);
 template <typename C>
 void nd_bwd(const NDLaunchDev& L, const NDFrontDev* fr, const int* idx, const int* cidx, const C* Wp, C* upd, C* x,
             C* gvec, int cap, int conj, C* P, const NDRhs& rh, hipStream_t s);
@@ -100,14 +91,15 @@ struct Carver {
 struct NDDev {        // device-side ND tables (pointers into the workspace)
   NDFrontDev* fronts = nullptr;
   NDFrontDev* hfr = nullptr;   // fronts in height order
-  int *idx = nullptr, *maps = nullptr, *cptr = nullptr, *cidx = nullptr, *perm = nullptr, *hlist = nullptr,
-      *err = nullptr, *swp = nullptr;
+  int *idx = nullptr, *maps = nullptr, *cptr = nullptr, *cidx = nullptr, *perm = nullptr, *iperm = nullptr,
+      *err = nullptr;
   int* children = nullptr;
   long long* child_map_off = nullptr;
   NDAsm* asmv = nullptr;
-  long long* toff = nullptr;
-  cd *F = nullptr, *T = nullptr, *pb = nullptr;   // pb: multi-work-group panel buffer
-  PivCand* cand = nullptr;
+  long long *toff = nullptr, *goff = nullptr;   // per slot: offsets in T and G
+  cd *F = nullptr;      // front matrices
+  cd *T = nullptr;      // one height's W in FP64
+  cd *G = nullptr;      // second copy of one height's separator blocks
   void *L = nullptr, *W = nullptr;
   std::vector<NDLaunchDev> launch[2];   // forward, backward
   int gvec_cap = 0;
@@ -135,9 +127,10 @@ struct Pending {
 };
 
 struct HeightInfo {
-  int start, count, max_asm, max_nS, max_nF, max_child;
-  long long max_nb2, max_T, max_fin;
-  long long f_bytes;      // the fronts' dense matrices, FP64 complex
+  int start, count, max_asm, max_nS, max_nB, max_child;
+  int max_wn;             // rows of the widest inversion window
+  long long max_nb2;
+  long long s_bytes;      // the fronts' separator blocks, FP64 complex
 };
 
 }  // namespace
@@ -166,7 +159,8 @@ struct helm_ctx {
   NDPlan plan;
   NDDev nd;
   std::vector<HeightInfo> hinfo;
-  std::vector<long long> hlist_toff;
+  std::vector<long long> hlist_toff, hlist_goff;
+  long long T_elems = 0, G_elems = 0;   // the largest height's entries
   std::vector<int> hlist;
   // Krylov
   cd *V = nullptr, *part = nullptr;
@@ -192,7 +186,7 @@ struct helm_ctx {
   std::vector<Pending> pending;
   std::vector<hipEvent_t> evpool;
   size_t lds_limit = 65536;     // LDS bytes for substitution vectors
-  size_t lds_panel = 0;         // LDS bytes for a resident factorisation panel (device maximum - 2 KB)
+  int nd_win = 1024;            // rows of an inversion window of the factorisation (HELM_ND_WIN)
   bool tuned = false;           // schedule parameters came from the autotuner cache
   int nd_leaf = 0, nd_root = 0;  // nested-dissection leaf size and root merge limit in use
   // the compact fourth-order stack: restriction (tr) and interpolating-restriction (ip, P =
@@ -315,7 +309,6 @@ void init_geometry(helm_ctx* c) {
 // planes of the FP32 level-2 coefficients: 3D keeps the symmetric half (centre onwards;
 // the level kernels' Op2<3, float> reads them so)
 static inline int sym2_planes(int dim) { return dim == 3 ? 14 : 9; }
-const int ND_KB = ND_KBOUT;      // scratch of the exchange updates is sized for the widest column block
 // nested-dissection parameters (tunable through the environment for the autotuner):
 // leaf box size, rows per work-group of big fronts, nodes per subtree task
 int env_int(const char* name, int dflt) {
@@ -486,31 +479,38 @@ void build_plan(helm_ctx* c) {
   // the many small subtrees run two work-groups per CU (measured 3 % faster at 256^3)
   const int tree_waves = env_int("HELM_ND_TREE_WAVES", c->grid.dim == 3 ? 8 : 16);
   nd_plan(c->g3, leaf, 16, merge, (int)c->ndsz, lds, cuts, splitk, c->plan, tree_waves, mh, c->r3);
+  // inversion windows of the factorisation: 16 to 1024 rows, a multiple of 16
+  c->nd_win = std::max(16, std::min(1024, env_int("HELM_ND_WIN", 1024) / 16 * 16));
   NDPlan& P = c->plan;
   c->hlist.clear();
   c->hlist_toff.clear();
+  c->hlist_goff.clear();
   c->hinfo.clear();
+  c->T_elems = c->G_elems = 0;
   for (int h = 0; h <= P.max_height; ++h) {
     HeightInfo hi{};
     hi.start = (int)c->hlist.size();
     hi.count = (int)P.by_height[h].size();
-    long long toff = 0;
+    long long toff = 0, goff = 0;
     for (int t : P.by_height[h]) {
       const NDFrontDev& f = P.fronts[t];
       c->hlist.push_back(t);
       c->hlist_toff.push_back(toff);
-      toff += (long long)ND_KB * f.nF;
+      c->hlist_goff.push_back(goff);
+      toff += (long long)f.nS * f.nB;
+      goff += (long long)f.nS * f.nS;
       hi.max_asm = std::max(hi.max_asm, f.asm_cnt);
       hi.max_nS = std::max(hi.max_nS, f.nS);
-      hi.max_nF = std::max(hi.max_nF, f.nF);
+      hi.max_nB = std::max(hi.max_nB, f.nB);
+      hi.max_wn = std::max(hi.max_wn, std::min(f.nS, win_size(f.nS, c->nd_win)));
       int nbc = 0;
       hi.max_child = std::max(hi.max_child, f.nchild);
       for (int q = 0; q < f.nchild; ++q) nbc = std::max(nbc, P.fronts[P.children[f.child_off + q]].nB);
       hi.max_nb2 = std::max(hi.max_nb2, (long long)nbc * nbc);
-      hi.max_T = std::max(hi.max_T, (long long)ND_KB * f.nF);
-      hi.max_fin = std::max(hi.max_fin, (long long)f.nF * f.nS + (long long)f.nS * f.nB);
-      hi.f_bytes += (long long)sizeof(cd) * f.nF * f.nF;
     }
+    hi.s_bytes = (long long)sizeof(cd) * goff;
+    c->T_elems = std::max(c->T_elems, toff);
+    c->G_elems = std::max(c->G_elems, goff);
     c->hinfo.push_back(hi);
   }
 }
@@ -564,33 +564,16 @@ size_t carve(helm_ctx* c, void* ws) {
   d.cidx = cv.take<int>(std::max<size_t>(1, P.cidx.size()));
   d.children = cv.take<int>(std::max<size_t>(1, P.children.size()));
   d.child_map_off = cv.take<long long>(std::max<size_t>(1, P.child_map_off.size()));
-  {
-    size_t mx = 1;
-    size_t nc = 1;     // pivot candidates of the multi-work-group panels: fronts x row blocks of 32
-    size_t pbr = 1;    // panel-buffer rows: fronts x rows rounded to 32, over the multi-panel heights
-    // every height takes the multi-work-group panel when HELM_ND_LDS_PANEL is 0, else those
-    // whose fronts are too large for the register panel (as nd_factor decides)
-    const bool all_multi = getenv("HELM_ND_LDS_PANEL") && env_int("HELM_ND_LDS_PANEL", 0) <= 0;
-    for (auto& h : P.by_height) {
-      mx = std::max(mx, h.size());
-      int mf = 0;
-      for (int t : h) mf = std::max(mf, P.fronts[t].nF);
-      const size_t rows = h.size() * (size_t)((mf + 31) / 32) * 32;
-      nc = std::max(nc, rows / 32);
-      if (all_multi || panel_reg_kb(mf) == 0) pbr = std::max(pbr, rows);
-    }
-    d.swp = cv.take<int>((size_t)ND_KBMAX * mx);
-    d.cand = cv.take<PivCand>(2 * nc);
-    d.pb = cv.take<cd>(pbr * ND_KBMAX);
-  }
   d.asmv = cv.take<NDAsm>(P.asmv.size());
   d.perm = cv.take<int>(P.perm_total);
-  d.hlist = cv.take<int>(c->hlist.size());
+  d.iperm = cv.take<int>(P.perm_total);
   d.hfr = cv.take<NDFrontDev>(c->hlist.size());   // the fronts in height order (factorisation)
   d.toff = cv.take<long long>(c->hlist_toff.size());
+  d.goff = cv.take<long long>(c->hlist_goff.size());
   d.err = cv.take<int>(1);
   d.F = cv.take<cd>(P.F_total);
-  d.T = cv.take<cd>(std::max<long long>(1, P.T_scratch));
+  d.T = cv.take<cd>(std::max<long long>(1, c->T_elems));
+  d.G = cv.take<cd>(std::max<long long>(1, c->G_elems));
   d.L = cv.take<char>(c->ndsz * P.L_alloc);
   d.W = cv.take<char>(c->ndsz * std::max<long long>(1, P.W_alloc));
   long long part_max = 1;      // split-K partial products (entries)
@@ -674,54 +657,26 @@ void nd_factor(helm_ctx* c, hipStream_t s) {
   NDDev& d = c->nd;
   NDPlan& P = c->plan;
   nd_zero(d.F, P.F_total, s);
-  nd_iota(d.perm, d.fronts, (int)P.fronts.size(), s);
-  CK(hipMemsetAsync(d.err, 0, sizeof(int), s));
+  nd_fill_int(d.iperm, P.perm_total, -1, s);
+  nd_fill_int(d.err, 1, 0, s);
   for (size_t h = 0; h < c->hinfo.size(); ++h) {
     const HeightInfo& hi = c->hinfo[h];
-    const int* ids = d.hlist + hi.start;
-    const NDFrontDev* hf = d.hfr + hi.start;     // the height's fronts, slot order
+    const NDInv v{d.hfr + hi.start, d.goff + hi.start, d.F, d.G, d.perm, d.iperm, d.err, c->nd_win};
     const long long* toff = d.toff + hi.start;
-    nd_assemble(d.fronts, ids, hi.count, hi.max_asm, d.asmv, c->coef3_64, d.F, s);
+    nd_assemble(v, hi.count, hi.max_asm, d.asmv, c->coef3_64, s);
     for (int slot = 0; slot < hi.max_child; ++slot)
-      nd_extend(d.fronts, ids, hi.count, hi.max_nb2, d.children, d.child_map_off, d.maps, d.F, slot, s);
-    // the register-resident panel (one work-group per front) when the fronts are small
-    // enough; otherwise the panel is spread over many work-groups
-    const int kreg = panel_reg_kb(hi.max_nF);
-    const bool reg_panel = kreg > 0 && c->lds_panel > 0;
-    // multi-work-group panels: HELM_ND_KB_MULTI columns (16, 32 or 64).  Every pivot step
-    // reads and writes its panel over all rows of the front, so with the trailing passes
-    // taken per block the narrower 32-column panel is the faster one.
-    // Panels are grouped into blocks of HELM_ND_KB_OUTER columns: the panels of a block
-    // update each other, and the rest of the front takes one trailing update per block, so
-    // the GEMM streams the front once per block instead of once per panel.  For the 8- to
-    // 32-column register panels that pass is bound by the fronts' traffic, and blocking
-    // pays once the height's fronts hold at least HELM_ND_REG_BLOCK_MB megabytes and have
-    // at least two blocks' worth of rows; below that every pass costs about one launch (and
-    // a block covers most of a small front), so the block's two extra launches do not pay.
-    const int kmulti = std::max(8, std::min(ND_KBMAX, env_int("HELM_ND_KB_MULTI", 32)));
-    const int kb = reg_panel ? kreg : kmulti;
-    const int reg_mb = env_int("HELM_ND_REG_BLOCK_MB", 32);
-    const bool blocked = !reg_panel || (hi.f_bytes >= (long long)reg_mb * 1000000 &&
-                                        (reg_mb == 0 || hi.max_nF >= 2 * ND_KBOUT));
-    const int kout = blocked ? std::max(1, std::min(ND_KBOUT, env_int("HELM_ND_KB_OUTER", ND_KBOUT)) / kb) * kb : kb;
-    for (int k0 = 0; k0 < hi.max_nS; k0 += kout) {
-      for (int k1 = k0; k1 < std::min(k0 + kout, hi.max_nS); k1 += kb) {
-        if (reg_panel)
-          nd_panel_reg(hf, nullptr, hi.count, hi.max_nF, d.F, d.perm, d.swp, k1, kb, d.err, s);
-        else
-          nd_panel_multi(hf, hi.count, hi.max_nF, d.F, d.pb, d.perm, d.swp, d.cand, k1, kb, hi.max_nS, d.err, s);
-        if (kout > kb) {        // the block's other panels, earlier ones included
-          nd_save_t(hf, nullptr, hi.count, toff, (long long)kb * kout, d.F, d.T, k1, kb, k0, kout, s);
-          nd_gemm(hf, nullptr, hi.count, toff, hi.max_nF, kout, d.F, d.T, k1, kb, k0, kout, s);
-        }
-      }
-      nd_save_t(hf, nullptr, hi.count, toff, hi.max_T, d.F, d.T, k0, kout, 0, -1, s);
-      nd_gemm(hf, nullptr, hi.count, toff, hi.max_nF, hi.max_nF, d.F, d.T, k0, kout, 0, -1, s);
-    }
+      nd_extend(v, d.fronts, hi.count, hi.max_nb2, d.children, d.child_map_off, d.maps, slot, s);
+    // panels grouped into blocks of HELM_ND_KB_OUTER columns: the panels of a block update
+    // each other and the rest of the window takes one product per block, so the separator
+    // blocks are streamed once per block instead of once per panel.  That pays once they
+    // hold HELM_ND_REG_BLOCK_MB megabytes; below, a pass costs about one launch.
+    const bool blocked = hi.s_bytes >= (long long)env_int("HELM_ND_REG_BLOCK_MB", 32) * 1000000;
+    const int kout = nd_invert(v, hi.count, hi.max_nS, hi.max_wn, blocked ? env_int("HELM_ND_KB_OUTER", 128) : 1, s);
+    // the 5/7-point stack's operators are complex symmetric
     if (!c->nd64)
-      nd_finalize<cf>(hf, nullptr, hi.count, hi.max_fin, d.F, d.perm, (cf*)d.L, (cf*)d.W, s);
+      nd_products<cf>(v, hi.count, hi.max_nS, hi.max_nB, kout, !c->compact, toff, d.T, (cf*)d.L, (cf*)d.W, s);
     else
-      nd_finalize<cd>(hf, nullptr, hi.count, hi.max_fin, d.F, d.perm, (cd*)d.L, (cd*)d.W, s);
+      nd_products<cd>(v, hi.count, hi.max_nS, hi.max_nB, kout, !c->compact, toff, d.T, (cd*)d.L, (cd*)d.W, s);
   }
 }
 
@@ -1424,16 +1379,6 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
     carve(c.get(), ws);
     CK(hipHostMalloc((void**)&c->hstate, 4096, hipHostMallocMapped | hipHostMallocCoherent));
     CK(hipHostGetDevicePointer((void**)&c->hstate_dev, c->hstate, 0));
-    {
-      int dev = 0, lds = 0;
-      CK(hipGetDevice(&dev));
-      CK(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-      c->lds_panel = lds > 4096 ? (size_t)lds - 2048 : 0;
-      // HELM_ND_LDS_PANEL caps the LDS-resident panel (bytes; 0: every panel takes the
-      // multi-work-group path)
-      if (getenv("HELM_ND_LDS_PANEL")) c->lds_panel = std::min<size_t>(c->lds_panel, (size_t)env_int("HELM_ND_LDS_PANEL", 0));
-      if (env_int("HELM_VERBOSE", 0)) fprintf(stderr, "helm: LDS per block %d bytes\n", lds);
-    }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     CK(hipEventCreate(&e0));
     CK(hipEventCreate(&e1));
@@ -1449,7 +1394,6 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
     up(d.children, P.children, s);
     up(d.child_map_off, P.child_map_off, s);
     up(d.asmv, P.asmv, s);
-    up(d.hlist, c->hlist, s);
     {
       std::vector<NDFrontDev> hf;
       hf.reserve(c->hlist.size());
@@ -1457,6 +1401,7 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
       up(d.hfr, hf, s);
     }
     up(d.toff, c->hlist_toff, s);
+    up(d.goff, c->hlist_goff, s);
     for (int fb = 0; fb < 2; ++fb) {
       std::vector<NDLaunch>& Ls = fb == 0 ? P.fwd : P.bwd;
       for (size_t l = 0; l < Ls.size(); ++l) {

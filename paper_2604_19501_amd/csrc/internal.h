@@ -196,13 +196,24 @@ struct NDFrontDev {
   int pad;
 };
 
-#define ND_KBMAX 64     // widest factorisation panel (columns)
-#define ND_KBOUT 128    // widest column block of the trailing exchange update
-
-struct PivCand {        // a row block's pivot candidate: largest |F[i][k]| and its row
-  double v;
-  int i, pad;
+// the factorisation's device arrays for the fronts of one height (slot order): the front
+// matrices, the second copy of their separator blocks (offset goff per slot, nS x nS), the
+// pivot rows pm (perm_off + column) and their inverse ip (-1: not yet a pivot row), and the
+// rows of an inversion window (a multiple of 16, at most 1024)
+struct NDInv {
+  const NDFrontDev* hf;
+  const long long* goff;
+  cd *F, *G;
+  int *pm, *ip, *err;
+  int win;
 };
+
+// windows of a separator of nS rows: nwin of wsz rows (a multiple of 16; the last shorter)
+__host__ __device__ inline int win_count(int nS, int win) { return (nS + win - 1) / win; }
+__host__ __device__ inline int win_size(int nS, int win) {
+  const int n = win_count(nS, win);
+  return ((nS + n - 1) / n + 15) / 16 * 16;
+}
 
 struct NDAsm {          // F[row][col] += coef[cidx]
   int row, col;
@@ -316,7 +327,6 @@ struct NDPlan {
   int max_height = 0;
   long long F_total = 0, L_total = 0, W_total = 0, upd_total = 0, perm_total = 0;
   long long L_alloc = 0, W_alloc = 0;   // entries of the padded L and W storage
-  long long T_scratch = 0;              // doubles2 of panel row buffer (max over heights)
   int max_nS = 0, max_nB = 0, max_nF = 0;
   std::vector<NDLaunch> fwd, bwd;
   std::vector<int> cuts;                // heights closing the tree-block launches

@@ -1,0 +1,637 @@
+// Factorisation of the real-shifted coarsest operator A3 (eq. 3.6) on the GPU (set-up, FP64).
+//
+// Fronts are processed by height in the nested-dissection tree (nd_plan.cpp).  A front
+// matrix F (nF x nF, row major, S nodes first) is assembled from the original coefficients
+// and the children's Schur complements (extend-add).  With A = F_SS, B = F_SB, C = F_BS,
+// D = F_BB the front then gives
+//     L = [A^-1; C A^-1],   W = -A^-1 B   (stored in the substitution's precision)
+//     D + C W                             (its Schur complement, for the parent).
+// A is inverted by Gauss-Jordan exchange steps with partial pivoting among the S rows; the
+// rest are dense products with the whole inverse, on the FP64 matrix cores:
+//     W = -A^-1 B  (depth nS),  C A^-1  (depth nS),  D += C W  (depth nS).
+// Taking them once per front, after the inversion, keeps B, C and D (most of the front) out
+// of the pivoting: a panel covers the nS rows of A instead of all nF, the products run at
+// full depth instead of in slices of 8 to 128, and no row swap touches B.  The 5/7-point
+// stack's operators are complex symmetric, so C A^-1 = -W^T needs no product and D + C W is
+// formed for its lower tiles only: nS^3 + nS^2 nB + nS nB^2 / 2 complex multiply-adds
+// instead of nS (nS + nB)^2.  Set-up times against exchanging the S pivots over all nF rows
+// and columns: 228 -> 121 ms (256^3), 6.8 -> 4.8 ms (1024^2), 62.7 -> 41.7 ms (192x192x72
+// compact), 17.5 -> 11.3 ms (1024^2 compact), 1.19 -> 0.74 ms (128^2).
+//
+// Exchange steps without row swaps.  Exchanging pivot (p, k) in y = Q x makes row p stand
+// for x_k and column k for y_p:
+//     Q[i][j] -= Q[i][k] Q[p][j] / Q[p][k],   Q[i][k] = Q[i][k] / Q[p][k],
+//     Q[p][j] = -Q[p][j] / Q[p][k],           Q[p][k] = 1 / Q[p][k].
+// Rows stay where they are; pm[k] is the pivot row of column k, ip its inverse.  Once every
+// column is exchanged, A^-1[k][pm[l]] = Q[pm[k]][l] (k_inv_final).
+//
+// A run of pivots K is taken in three nested sizes: panels of KB columns in registers
+// (k_inv_panel), blocks of several panels, and windows of at most HELM_ND_WIN rows.  After
+// a run, every column J outside it takes one product
+//     Q[:, J] = Q0[:, J] (pivot rows: 0) - Q'[:, K] Q0[pm[K], J]           (k_inv_gemm),
+// read from one copy of A and written to the other (the front itself and a scratch copy,
+// parity 0 and 1), so that a launch reads no entry that it writes.  The pivots of a window's
+// columns come from the window's rows, as those of a front come from its own separator; the
+// rows of A outside the window take their part of the run's columns from the finished
+// window, Q'[i, K] = Q0[i, K] Q'[pm[K], K] (k_inv_outer).
+#include <algorithm>
+#include <stdexcept>
+
+#include "internal.h"
+
+namespace helm {
+
+__global__ void k_zero_d2(cd* __restrict__ p, long long n) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
+    p[i] = mk(0.0, 0.0);
+}
+
+__global__ void __launch_bounds__(256) k_nd_assemble(const NDFrontDev* __restrict__ hf,
+                                                     const NDAsm* __restrict__ asmv, const cd* __restrict__ coef,
+                                                     cd* __restrict__ Fp) {
+  const NDFrontDev f = hf[blockIdx.y];
+  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < f.asm_cnt;
+       e += (long long)gridDim.x * blockDim.x) {
+    NDAsm a = asmv[f.asm_off + e];
+    cd* F = Fp + f.F_off;
+    F[(long long)a.row * f.nF + a.col] += coef[a.cidx];
+  }
+}
+
+__global__ void __launch_bounds__(256) k_nd_extend(const NDFrontDev* __restrict__ hf,
+                                                   const NDFrontDev* __restrict__ fr,
+                                                   const int* __restrict__ children,
+                                                   const long long* __restrict__ child_map_off,
+                                                   const int* __restrict__ maps, cd* __restrict__ Fp, int slot) {
+  const NDFrontDev f = hf[blockIdx.y];
+  if (slot >= f.nchild) return;
+  const NDFrontDev fc = fr[children[f.child_off + slot]];
+  long long n2 = (long long)fc.nB * fc.nB;
+  const int* mp = maps + child_map_off[f.child_off + slot];
+  cd* F = Fp + f.F_off;
+  const cd* Fc = Fp + fc.F_off;
+  for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < n2; p += (long long)gridDim.x * blockDim.x) {
+    int k1 = (int)(p / fc.nB), k2 = (int)(p % fc.nB);
+    F[(long long)mp[k1] * f.nF + mp[k2]] += Fc[(long long)(fc.nS + k1) * fc.nF + fc.nS + k2];
+  }
+}
+
+// ----------------------------------------------------------------- inversion of A ----
+// one front's inversion: the two copies of A, its pivot maps and the window in work
+struct InvFront {
+  int nS, nwin, w0, wn;      // window rows and columns [w0, w0 + wn); wn <= 0: nothing to do
+  cd *q0, *q1;
+  int ld0, ld1;
+  int *pm, *ip;
+  __device__ __forceinline__ cd* q(int par) const { return par ? q1 : q0; }
+  __device__ __forceinline__ long long ld(int par) const { return par ? ld1 : ld0; }
+};
+__device__ __forceinline__ InvFront inv_front(const NDInv& v, int y, int w) {
+  const NDFrontDev f = v.hf[y];
+  InvFront a;
+  a.nS = f.nS;
+  a.nwin = win_count(f.nS, v.win);
+  const int wsz = win_size(f.nS, v.win);
+  a.w0 = w * wsz;
+  a.wn = w < a.nwin ? min(wsz, f.nS - a.w0) : 0;
+  a.q0 = v.F + f.F_off;
+  a.q1 = v.G + v.goff[y];
+  a.ld0 = f.nF;
+  a.ld1 = f.nS;
+  a.pm = v.pm + f.perm_off;
+  a.ip = v.ip + f.perm_off;
+  return a;
+}
+__device__ __forceinline__ int steps_of(int n, int step) { return (n + step - 1) / step; }
+
+template <int CTRL, int RMASK>
+__device__ __forceinline__ unsigned dpp_umax(unsigned v) {
+  return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, RMASK, 0xf, false));
+}
+// largest of the 64 lanes' values (pair and quad swaps, row mirrors, row broadcasts)
+__device__ __forceinline__ unsigned wave_umax(unsigned v) {
+  v = dpp_umax<0xB1, 0xf>(v);
+  v = dpp_umax<0x4E, 0xf>(v);
+  v = dpp_umax<0x141, 0xf>(v);
+  v = dpp_umax<0x140, 0xf>(v);
+  v = dpp_umax<0x142, 0xa>(v);
+  v = dpp_umax<0x143, 0xc>(v);
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// A row's key for the pivot search: the leading bits of |Q[i][k]|^2 (a positive double's bits
+// order as its value) with the row in the last 10, lower rows first among equals.  The chosen
+// pivot is within 2^-10 of the largest in |.|^2.  Zero, NaN and exchanged rows come last.
+__device__ __forceinline__ unsigned pivot_key(cd a, bool open, int row) {
+  const double v = abs2(a);
+  const unsigned hb = v >= 0.0 ? (unsigned)__double2hiint(v) & ~1023u : 0u;
+  return open ? hb | (unsigned)(1023 - row) : 0u;
+}
+
+// Panel [w0 + k0, + KB) of the window's rows, one work-group of NT threads per front: thread
+// t owns rows t + r NT, r < R, with their KB panel entries in registers.  Bound by the chain
+// of its pivots: each is the new column's keys, a wave maximum by DPP, the waves' candidate
+// rows into LDS, one barrier, a division and the rank-1 update.  Every wave publishes its
+// own best row with its key before the barrier, so one barrier per pivot serves both the
+// search and the pivot row (two LDS sets alternate), and without row swaps no other row is
+// exchanged.  The column loop stays rolled (unrolled it overflows the instruction cache), so
+// a thread's entries are kept rotated: before pivot kk slot j holds column (kk + j) mod KB.
+// Rows pass through LDS 8 columns (a cache line) at a time on their way in and out: taken
+// directly, every 16-byte access of a wave would touch 64 lines.
+template <int KB, int R, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
+k_inv_panel(NDInv v, int w, int k0, int par) {
+  constexpr int NW = NT / 64, CB = 8, LS = CB + 1;
+  __shared__ cd s_row[2][NW][KB];
+  __shared__ unsigned s_key[2][NW];
+  __shared__ cd s_t[NT * LS];
+  const InvFront f = inv_front(v, blockIdx.x, w);
+  if (k0 >= f.wn) return;
+  const int kbb = min(KB, f.wn - k0), t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const cd* __restrict__ src = f.q(par) + (long long)f.w0 * f.ld(par) + f.w0 + k0;
+  cd* __restrict__ dst = f.q(par ^ 1) + (long long)f.w0 * f.ld(par ^ 1) + f.w0 + k0;
+  const long long ls = f.ld(par), ldd = f.ld(par ^ 1);
+  cd a[R][KB];
+  bool open[R];
+  // entry (row e / 8, column e % 8) of a pass of NT rows and 8 columns, e = t + NT u
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < KB; c += CB)
+#pragma unroll
+      for (int u = 0; u < CB; ++u) {
+        const int e = t + NT * u;
+        a[r][c + u] = src[min(r * NT + e / CB, f.wn - 1) * ls + min(c + e % CB, kbb - 1)];
+      }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = r * NT + t;
+    open[r] = i < f.wn && f.ip[f.w0 + min(i, f.wn - 1)] < 0;
+#pragma unroll
+    for (int c = 0; c < KB; c += CB) {
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < CB; ++u) {
+        const int e = t + NT * u;
+        s_t[e / CB * LS + e % CB] = a[r][c + u];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < CB; ++u) a[r][c + u] = s_t[t * LS + u];
+    }
+  }
+  unsigned key = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) key = max(key, pivot_key(a[r][0], open[r], r * NT + t));
+  for (int kk = 0; kk < kbb; ++kk) {
+    const int b = kk & 1;
+    const unsigned wk = wave_umax(key);
+    const int wrow = 1023 - (int)(wk & 1023u);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r * NT + t == wrow) {
+#pragma unroll
+        for (int j = 0; j < KB; ++j) s_row[b][wv][j] = a[r][j];
+      }
+    if (lane == 0) s_key[b][wv] = wk;
+    __syncthreads();
+    unsigned bk = s_key[b][0];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) bk = max(bk, s_key[b][q]);
+    bk = (unsigned)__builtin_amdgcn_readfirstlane((int)bk);
+    const int p = 1023 - (int)(bk & 1023u);            // the pivot row, counted from w0
+    const cd* __restrict__ row = s_row[b][(p & (NT - 1)) >> 6];
+    cd piv = row[0];
+    const bool ok = abs2(piv) > 0.0;
+    if (!ok) piv = mk(1.0, 0.0);
+    const cd inv = cdiv(mk(1.0, 0.0), piv);
+    if (t == 0) {
+      f.pm[f.w0 + k0 + kk] = f.w0 + p;
+      f.ip[f.w0 + p] = f.w0 + k0 + kk;
+      if (!ok) atomicOr(v.err, 1);
+    }
+    key = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      cd ck = a[r][0] * inv;
+      if (r * NT + t == p) {                           // the pivot row: -row / pivot, 1 / pivot
+        ck = inv;
+        open[r] = false;
+#pragma unroll
+        for (int j = 1; j < KB; ++j) a[r][j] = mk(0.0, 0.0);
+      }
+#pragma unroll
+      for (int j = 0; j + 1 < KB; ++j) a[r][j] = a[r][j + 1] - ck * row[j + 1];
+      a[r][KB - 1] = ck;
+      key = max(key, pivot_key(a[r][0], open[r], r * NT + t));
+    }
+  }
+  // slot j now holds column (kbb + j) mod KB
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int c = 0; c < KB; c += CB) {
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < CB; ++u) s_t[t * LS + u] = a[r][c + u];
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < CB; ++u) {
+        const int e = t + NT * u, i = r * NT + e / CB, col = (kbb + c + e % CB) % KB;
+        if (i < f.wn && col < kbb) dst[i * ldd + col] = s_t[e / CB * LS + e % CB];
+      }
+    }
+}
+
+// ------------------------------------------------------ complex FP64 products (MFMA) ----
+// C tile of 64 x 64, K deep: a work-group of 4 wavefronts, each a 32 x 32 quarter as 2 x 2
+// blocks of the 16 x 16 x 4 FP64 MFMA, real and imaginary parts accumulated separately:
+//   Cr += Ar Br - Ai Bi,  Ci += Ar Bi + Ai Br  (four real MFMAs per k group).
+// MFMA lane layout: A[m][k] from lane m + 16 k, B[k][n] from lane n + 16 k, and lane l
+// holds D[l / 16 + 4 i][l % 16], i < 4.  Panels of A and B pass through LDS, 16 k at a time;
+// the next 16 are loaded into registers while the matrix cores work on these.
+#define GT 64
+#define GK 16
+typedef double mfma_d4 __attribute__((ext_vector_type(4)));
+struct GemmLds {
+  cd a[GK][GT + 1], b[GK][GT + 1];
+};
+struct GemmAcc {
+  mfma_d4 r[2][2], i[2][2];
+};
+// la(row, k) and lb(k, col): entries of the tile's operands; both are called for every
+// row and column of the tile and every k < K rounded up to 16, and return 0 outside
+template <class LA, class LB>
+__device__ __forceinline__ void gemm_tile(GemmLds& s, int K, GemmAcc& acc, LA la, LB lb) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int wr = (wv >> 1) * 32, wc = (wv & 1) * 32, lm = lane & 15, lk = lane >> 4;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      acc.r[a][b] = mfma_d4{0.0, 0.0, 0.0, 0.0};
+      acc.i[a][b] = mfma_d4{0.0, 0.0, 0.0, 0.0};
+    }
+  constexpr int NLD = GK * GT / 256;
+  cd ra[NLD], rb[NLD];
+  auto load = [&](int kk0) {
+#pragma unroll
+    for (int it = 0; it < NLD; ++it) {
+      const int p = (int)threadIdx.x + 256 * it;
+      ra[it] = la(p / GK, kk0 + p % GK);             // consecutive threads along a row of A
+      rb[it] = lb(kk0 + p / GT, p % GT);             // consecutive threads along a row of B
+    }
+  };
+  load(0);
+  for (int kk0 = 0; kk0 < K; kk0 += GK) {
+#pragma unroll
+    for (int it = 0; it < NLD; ++it) {
+      const int p = (int)threadIdx.x + 256 * it;
+      s.a[p % GK][p / GK] = ra[it];
+      s.b[p / GT][p % GT] = rb[it];
+    }
+    __syncthreads();
+    if (kk0 + GK < K) load(kk0 + GK);
+#pragma unroll
+    for (int k4 = 0; k4 < GK; k4 += 4) {
+      cd av[2], bv[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        av[q] = s.a[k4 + lk][wr + 16 * q + lm];
+        bv[q] = s.b[k4 + lk][wc + 16 * q + lm];
+      }
+      // the four products of a block go to two accumulators: issue them in rounds over the
+      // eight accumulators, so that no MFMA waits for the one just before it
+#pragma unroll
+      for (int qa = 0; qa < 2; ++qa)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          acc.r[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[qa].x, bv[qb].x, acc.r[qa][qb], 0, 0, 0);
+          acc.i[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[qa].x, bv[qb].y, acc.i[qa][qb], 0, 0, 0);
+        }
+#pragma unroll
+      for (int qa = 0; qa < 2; ++qa)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+          acc.r[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[qa].y, bv[qb].y, acc.r[qa][qb], 0, 0, 0);
+          acc.i[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[qa].y, bv[qb].x, acc.i[qa][qb], 0, 0, 0);
+        }
+    }
+    __syncthreads();
+  }
+}
+// st(row, col, value) for the tile's 64 x 64 entries
+template <class ST>
+__device__ __forceinline__ void gemm_store(const GemmAcc& acc, ST st) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int wr = (wv >> 1) * 32, wc = (wv & 1) * 32, lm = lane & 15, lk = lane >> 4;
+#pragma unroll
+  for (int qa = 0; qa < 2; ++qa)
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        st(wr + 16 * qa + lk + 4 * i, wc + 16 * qb + lm, mk(acc.r[qa][qb][i], acc.i[qa][qb][i]));
+}
+#define GEMM_KERNEL __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+
+// Columns outside a run K = [w0 + k0, + kw) of pivots (clipped to the window).  cmode 0: the
+// other columns of the block [w0 + b0, + bw) (after a panel), 1: of the window (after a
+// block), over the window's rows; 2: of A (after a window), over all rows.  The run's own
+// entries Q'[:, K] are in copy pa, Q0 in copy par, and the result goes to copy par ^ 1.
+// pa < 0: a block's entries, whose copy depends on its number of panels of kb columns; where
+// that is copy par, they are copied over.
+GEMM_KERNEL k_inv_gemm(NDInv v, int w, int k0, int kw, int cmode, int b0, int bw, int par, int pa, int kb) {
+  const InvFront f = inv_front(v, blockIdx.y, w);
+  if (k0 >= f.wn || (cmode == 2 && f.nwin == 1)) return;
+  const int kn = min(kw, f.wn - k0);
+  const int r0 = cmode == 2 ? 0 : f.w0, M = cmode == 2 ? f.nS : f.wn;
+  const int c0 = cmode == 0 ? f.w0 + b0 : cmode == 1 ? f.w0 : 0;
+  const int nc = cmode == 0 ? min(bw, f.wn - b0) : cmode == 1 ? f.wn : f.nS;
+  if (nc == kn && pa >= 0) return;
+  const int tilesN = steps_of(nc, GT), tilesM = steps_of(M, GT);
+  if ((int)blockIdx.x >= tilesM * tilesN) return;
+  const int tm = blockIdx.x / tilesN * GT, tn = blockIdx.x % tilesN * GT;
+  if (pa < 0) pa = par ^ (steps_of(kn, kb) & 1);
+  const int K0 = f.w0 + k0, po = par ^ 1;
+  const cd* __restrict__ A = f.q(pa) + (long long)r0 * f.ld(pa) + K0;
+  const cd* __restrict__ Q0 = f.q(par);
+  cd* __restrict__ O = f.q(po);
+  const long long la = f.ld(pa), l0 = f.ld(par), lo = f.ld(po);
+  const int* __restrict__ pm = f.pm + K0;
+  const bool inside = c0 + tn >= K0 && c0 + min(tn + GT, nc) <= K0 + kn;   // only columns of K
+  if (inside && pa == po) return;
+  __shared__ GemmLds s;
+  GemmAcc acc;
+  if (!inside)
+    gemm_tile(
+        s, kn, acc,
+        [&](int r, int k) { return tm + r < M && k < kn ? A[(tm + r) * la + k] : mk(0.0, 0.0); },
+        [&](int k, int c) {
+          return tn + c < nc && k < kn ? Q0[pm[k] * l0 + c0 + tn + c] : mk(0.0, 0.0);
+        });
+  gemm_store(acc, [&](int r, int c, cd x) {
+    const int i = r0 + tm + r, j = c0 + tn + c;
+    if (tm + r >= M || tn + c >= nc) return;
+    if (j >= K0 && j < K0 + kn) {
+      if (pa != po) O[i * lo + j] = A[(tm + r) * la + (j - K0)];
+      return;
+    }
+    const int q = f.ip[i];
+    const cd o = q >= K0 && q < K0 + kn ? mk(0.0, 0.0) : Q0[i * l0 + j];
+    O[i * lo + j] = o - x;
+  });
+}
+
+// a finished window's columns in the rows outside it: Q'[i, K] = Q0[i, K] Q'[pm[K], K]; the
+// window's own rows are copied where its result is not in copy par ^ 1 already
+GEMM_KERNEL k_inv_outer(NDInv v, int w, int par, int kout) {
+  const InvFront f = inv_front(v, blockIdx.y, w);
+  if (f.nwin == 1 || f.wn <= 0) return;
+  const int M = f.nS, N = f.wn;
+  const int tilesN = steps_of(N, GT), tilesM = steps_of(M, GT);
+  if ((int)blockIdx.x >= tilesM * tilesN) return;
+  const int tm = blockIdx.x / tilesN * GT, tn = blockIdx.x % tilesN * GT;
+  const int po = par ^ 1, pr = par ^ (steps_of(f.wn, kout) & 1);
+  const cd* __restrict__ A = f.q(par) + f.w0;
+  const cd* __restrict__ B = f.q(pr) + f.w0;
+  cd* __restrict__ O = f.q(po) + f.w0;
+  const long long la = f.ld(par), lb = f.ld(pr), lo = f.ld(po);
+  const int* __restrict__ pm = f.pm + f.w0;
+  const bool inside = tm >= f.w0 && min(tm + GT, M) <= f.w0 + f.wn;
+  if (inside && pr == po) return;
+  __shared__ GemmLds s;
+  GemmAcc acc;
+  if (!inside)
+    gemm_tile(
+        s, N, acc, [&](int r, int k) { return tm + r < M && k < N ? A[(tm + r) * la + k] : mk(0.0, 0.0); },
+        [&](int k, int c) { return tn + c < N && k < N ? B[pm[k] * lb + tn + c] : mk(0.0, 0.0); });
+  gemm_store(acc, [&](int r, int c, cd x) {
+    const int i = tm + r, j = tn + c;
+    if (i >= M || j >= N) return;
+    if (i >= f.w0 && i < f.w0 + f.wn) {
+      if (pr != po) O[i * lo + j] = B[i * lb + j];
+    } else {
+      O[i * lo + j] = x;
+    }
+  });
+}
+
+// the copy that holds a front's exchanged A once every window is done
+__device__ __forceinline__ int final_par(const InvFront& f, int kout) {
+  return (f.nwin > 1 ? f.nwin : steps_of(f.nS, kout)) & 1;
+}
+
+// A^-1 in natural order, N[k][m] = Q[pm[k]][ip[m]], into the copy that Q does not occupy, and
+// into the upper block of L (column major, in the substitution's precision; a 32 x 32 tile
+// passes through LDS so that both are written in runs)
+template <typename C>
+__global__ void __launch_bounds__(256) k_inv_final(NDInv v, int kout, C* __restrict__ Lp) {
+  const NDFrontDev fr = v.hf[blockIdx.y];
+  const InvFront f = inv_front(v, blockIdx.y, 0);
+  const int nt = steps_of(f.nS, 32);
+  if ((int)blockIdx.x >= nt * nt) return;
+  const int k0 = blockIdx.x / nt * 32, m0 = blockIdx.x % nt * 32;
+  const int pf = final_par(f, kout), tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const cd* __restrict__ Q = f.q(pf);
+  cd* __restrict__ N = f.q(pf ^ 1);
+  const long long lq = f.ld(pf), ln = f.ld(pf ^ 1);
+  __shared__ C t[32][33];
+  const int q = f.ip[min(m0 + tx, f.nS - 1)];
+  cd x[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) x[u] = Q[f.pm[min(k0 + ty + 8 * u, f.nS - 1)] * lq + q];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int k = k0 + ty + 8 * u;
+    if (k < f.nS && m0 + tx < f.nS) N[k * ln + m0 + tx] = x[u];
+    t[ty + 8 * u][tx] = conv<C>::from(x[u]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int m = m0 + ty + 8 * u, k = k0 + tx;
+    if (k < f.nS && m < f.nS) Lp[fr.L_off + (long long)m * fr.ldL + k] = t[tx][ty + 8 * u];
+  }
+}
+
+// W = -A^-1 B: in FP64 for the Schur product (T, nS x nB row major), in the substitution's
+// precision into W and, for a complex symmetric operator, as C A^-1 = (A^-1 B)^T into the
+// lower block of L
+template <typename C, int SYM>
+GEMM_KERNEL k_nd_w(NDInv v, const long long* __restrict__ toff, int kout, cd* __restrict__ T, C* __restrict__ Lp,
+                   C* __restrict__ Wp) {
+  const NDFrontDev fr = v.hf[blockIdx.y];
+  const int nS = fr.nS, nB = fr.nB;
+  const int tilesN = steps_of(nB, GT), tilesM = steps_of(nS, GT);
+  if ((int)blockIdx.x >= tilesM * tilesN) return;
+  const int tm = blockIdx.x / tilesN * GT, tn = blockIdx.x % tilesN * GT;
+  const InvFront f = inv_front(v, blockIdx.y, 0);
+  const int pn = final_par(f, kout) ^ 1;
+  const cd* __restrict__ N = f.q(pn);
+  const cd* __restrict__ B = v.F + fr.F_off + nS;
+  const long long ln = f.ld(pn), lf = fr.nF;
+  cd* __restrict__ Tt = T + toff[blockIdx.y];
+  __shared__ GemmLds s;
+  GemmAcc acc;
+  gemm_tile(
+      s, nS, acc, [&](int r, int k) { return tm + r < nS && k < nS ? N[(tm + r) * ln + k] : mk(0.0, 0.0); },
+      [&](int k, int c) { return tn + c < nB && k < nS ? B[k * lf + tn + c] : mk(0.0, 0.0); });
+  gemm_store(acc, [&](int r, int c, cd x) {
+    const int k = tm + r, j = tn + c;
+    if (k >= nS || j >= nB) return;
+    Tt[(long long)k * nB + j] = -x;
+    Wp[fr.W_off + (long long)j * fr.ldW + k] = conv<C>::from(-x);
+    if (SYM) Lp[fr.L_off + (long long)k * fr.ldL + nS + j] = conv<C>::from(x);
+  });
+}
+
+// C A^-1 into the lower block of L (operators that are not symmetric)
+template <typename C>
+GEMM_KERNEL k_nd_x(NDInv v, int kout, C* __restrict__ Lp) {
+  const NDFrontDev fr = v.hf[blockIdx.y];
+  const int nS = fr.nS, nB = fr.nB;
+  const int tilesN = steps_of(nS, GT), tilesM = steps_of(nB, GT);
+  if ((int)blockIdx.x >= tilesM * tilesN) return;
+  const int tm = blockIdx.x / tilesN * GT, tn = blockIdx.x % tilesN * GT;
+  const InvFront f = inv_front(v, blockIdx.y, 0);
+  const int pn = final_par(f, kout) ^ 1;
+  const cd* __restrict__ N = f.q(pn);
+  const cd* __restrict__ Cb = v.F + fr.F_off + (long long)nS * fr.nF;
+  const long long ln = f.ld(pn), lf = fr.nF;
+  __shared__ GemmLds s;
+  GemmAcc acc;
+  gemm_tile(
+      s, nS, acc, [&](int r, int k) { return tm + r < nB && k < nS ? Cb[(tm + r) * lf + k] : mk(0.0, 0.0); },
+      [&](int k, int c) { return tn + c < nS && k < nS ? N[k * ln + tn + c] : mk(0.0, 0.0); });
+  gemm_store(acc, [&](int r, int c, cd x) {
+    if (tm + r < nB && tn + c < nS)
+      Lp[fr.L_off + (long long)(tn + c) * fr.ldL + nS + tm + r] = conv<C>::from(x);
+  });
+}
+
+// D += C W, the front's Schur complement; for a complex symmetric operator the tiles on and
+// below the diagonal, the others being their mirror images
+template <int SYM>
+GEMM_KERNEL k_nd_schur(NDInv v, const long long* __restrict__ toff, const cd* __restrict__ T) {
+  const NDFrontDev fr = v.hf[blockIdx.y];
+  const int nS = fr.nS, nB = fr.nB, nt = steps_of(nB, GT);
+  int bm, bn;
+  if (SYM) {
+    // tile x of the lower triangle, row by row
+    bm = (int)((sqrt(8.0 * blockIdx.x + 1.0) - 1.0) * 0.5);
+    while ((bm + 1) * (bm + 2) / 2 <= (int)blockIdx.x) ++bm;
+    while (bm * (bm + 1) / 2 > (int)blockIdx.x) --bm;
+    bn = (int)blockIdx.x - bm * (bm + 1) / 2;
+  } else {
+    bm = blockIdx.x / max(nt, 1);
+    bn = blockIdx.x % max(nt, 1);
+  }
+  if (bm >= nt) return;
+  const int tm = bm * GT, tn = bn * GT;
+  cd* __restrict__ F = v.F + fr.F_off + (long long)nS * fr.nF;
+  const cd* __restrict__ Tt = T + toff[blockIdx.y];
+  const long long lf = fr.nF;
+  __shared__ GemmLds s;
+  GemmAcc acc;
+  gemm_tile(
+      s, nS, acc, [&](int r, int k) { return tm + r < nB && k < nS ? F[(tm + r) * lf + k] : mk(0.0, 0.0); },
+      [&](int k, int c) { return tn + c < nB && k < nS ? Tt[(long long)k * nB + tn + c] : mk(0.0, 0.0); });
+  gemm_store(acc, [&](int r, int c, cd x) {
+    const int i = tm + r, j = tn + c;
+    if (i >= nB || j >= nB) return;
+    const cd d = F[i * lf + nS + j] + x;
+    F[i * lf + nS + j] = d;
+    if (SYM && bm != bn) F[j * lf + nS + i] = d;
+  });
+}
+
+__global__ void k_fill_int(int* __restrict__ p, long long n, int x) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
+    p[i] = x;
+}
+
+// ------------------------------------------------------------- launchers ----
+static unsigned blocks256(long long n, unsigned cap) {
+  return (unsigned)std::min<long long>(cap, std::max<long long>(1, (n + 255) / 256));
+}
+void nd_zero(cd* p, long long n, hipStream_t s) {
+  hipLaunchKernelGGL(k_zero_d2, dim3(2048), dim3(256), 0, s, p, n);
+}
+void nd_fill_int(int* p, long long n, int x, hipStream_t s) {
+  hipLaunchKernelGGL(k_fill_int, dim3(blocks256(n, 1024)), dim3(256), 0, s, p, n, x);
+}
+void nd_assemble(const NDInv& v, int nids, int max_asm, const NDAsm* asmv, const cd* coef, hipStream_t s) {
+  hipLaunchKernelGGL(k_nd_assemble, dim3(blocks256(max_asm, 1024), nids), dim3(256), 0, s, v.hf, asmv, coef, v.F);
+}
+void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, long long max_nb2, const int* children,
+               const long long* child_map_off, const int* maps, int slot, hipStream_t s) {
+  hipLaunchKernelGGL(k_nd_extend, dim3(blocks256(max_nb2, 2048), nids), dim3(256), 0, s, v.hf, fr, children,
+                     child_map_off, maps, v.F, slot);
+}
+
+// columns of a panel over a window of up to rows rows: 32 while a thread owns one row, then
+// 16 (R x KB entries of 4 registers each stay within a wave's 512)
+static int panel_cols(int rows) { return rows <= 256 ? 32 : 16; }
+static void inv_panel(const NDInv& v, int nids, int rows, int w, int k0, int par, hipStream_t s) {
+  if (rows <= 64)
+    hipLaunchKernelGGL((k_inv_panel<32, 1, 64>), dim3(nids), dim3(64), 0, s, v, w, k0, par);
+  else if (rows <= 128)
+    hipLaunchKernelGGL((k_inv_panel<32, 1, 128>), dim3(nids), dim3(128), 0, s, v, w, k0, par);
+  else if (rows <= 256)
+    hipLaunchKernelGGL((k_inv_panel<32, 1, 256>), dim3(nids), dim3(256), 0, s, v, w, k0, par);
+  else if (rows <= 512)
+    hipLaunchKernelGGL((k_inv_panel<16, 2, 256>), dim3(nids), dim3(256), 0, s, v, w, k0, par);
+  else if (rows <= 1024)
+    hipLaunchKernelGGL((k_inv_panel<16, 2, 512>), dim3(nids), dim3(512), 0, s, v, w, k0, par);
+  else
+    throw std::runtime_error("nd_invert: window of more than 1024 rows");
+}
+static unsigned tiles(int m, int n) { return (unsigned)(((m + GT - 1) / GT) * ((n + GT - 1) / GT)); }
+
+int nd_invert(const NDInv& v, int nids, int max_nS, int max_wn, int block_cols, hipStream_t s) {
+  const int kb = panel_cols(max_wn);
+  const int kout = std::max(1, block_cols / kb) * kb;
+  const int nwin = win_count(max_nS, v.win);
+  for (int w = 0; w < nwin; ++w) {
+    for (int b0 = 0, blk = 0; b0 < max_wn; b0 += kout, ++blk) {
+      const int cur = (w ^ blk) & 1;            // the copy that holds A before this block
+      const int nb = std::min(kout, max_wn - b0);
+      for (int k0 = b0, q = 0; k0 < b0 + nb; k0 += kb, ++q) {
+        inv_panel(v, nids, max_wn, w, k0, cur ^ (q & 1), s);
+        if (nb > kb)                             // the block's other panels, earlier ones included
+          hipLaunchKernelGGL(k_inv_gemm, dim3(tiles(max_wn, nb), nids), dim3(256), 0, s, v, w, k0, kb, 0, b0, kout,
+                             cur ^ (q & 1), cur ^ (q & 1) ^ 1, kb);
+      }
+      if (max_wn > kb)
+        hipLaunchKernelGGL(k_inv_gemm, dim3(tiles(max_wn, max_wn), nids), dim3(256), 0, s, v, w, b0, kout, 1, 0, 0,
+                           cur, -1, kb);
+    }
+    if (nwin > 1) {
+      hipLaunchKernelGGL(k_inv_outer, dim3(tiles(max_nS, max_wn), nids), dim3(256), 0, s, v, w, w & 1, kout);
+      hipLaunchKernelGGL(k_inv_gemm, dim3(tiles(max_nS, max_nS), nids), dim3(256), 0, s, v, w, 0, max_wn, 2, 0, 0,
+                         w & 1, (w & 1) ^ 1, kb);
+    }
+  }
+  return kout;
+}
+
+template <typename C>
+void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, int sym, const long long* toff, cd* T,
+                 C* Lp, C* Wp, hipStream_t s) {
+  const int nt = (max_nS + 31) / 32, nb = (max_nB + GT - 1) / GT;
+  hipLaunchKernelGGL((k_inv_final<C>), dim3(nt * nt, nids), dim3(256), 0, s, v, kout, Lp);
+  if (max_nB == 0) return;
+  if (sym) {
+    hipLaunchKernelGGL((k_nd_w<C, 1>), dim3(tiles(max_nS, max_nB), nids), dim3(256), 0, s, v, toff, kout, T, Lp, Wp);
+    hipLaunchKernelGGL((k_nd_schur<1>), dim3(nb * (nb + 1) / 2, nids), dim3(256), 0, s, v, toff, (const cd*)T);
+  } else {
+    hipLaunchKernelGGL((k_nd_w<C, 0>), dim3(tiles(max_nS, max_nB), nids), dim3(256), 0, s, v, toff, kout, T, Lp, Wp);
+    hipLaunchKernelGGL((k_nd_x<C>), dim3(tiles(max_nB, max_nS), nids), dim3(256), 0, s, v, kout, Lp);
+    hipLaunchKernelGGL((k_nd_schur<0>), dim3(nb * nb, nids), dim3(256), 0, s, v, toff, (const cd*)T);
+  }
+}
+template void nd_products<cf>(const NDInv&, int, int, int, int, int, const long long*, cd*, cf*, cf*, hipStream_t);
+template void nd_products<cd>(const NDInv&, int, int, int, int, int, const long long*, cd*, cd*, cd*, hipStream_t);
+
+}  // namespace helm
