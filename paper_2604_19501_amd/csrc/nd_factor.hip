@@ -119,6 +119,18 @@ __device__ __forceinline__ unsigned wave_umax(unsigned v) {
   return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// a - b c in four fused multiply-adds
+__device__ __forceinline__ cd csubmul(cd a, cd b, cd c) {
+  return mk(fma(b.y, c.y, fma(-b.x, c.x, a.x)), fma(-b.y, c.x, fma(-b.x, c.y, a.y)));
+}
+
+// lane l's v, in scalar registers
+__device__ __forceinline__ double lane_d(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ cd lane_cd(cd v, int l) { return mk(lane_d(v.x, l), lane_d(v.y, l)); }
+
 // A row's key for the pivot search: the leading bits of |Q[i][k]|^2 (a positive double's bits
 // order as its value) with the row in the last 10, lower rows first among equals.  The chosen
 // pivot is within 2^-10 of the largest in |.|^2.  Zero, NaN and exchanged rows come last.
@@ -138,12 +150,19 @@ __device__ __forceinline__ unsigned pivot_key(cd a, bool open, int row) {
 // a thread's entries are kept rotated: before pivot kk slot j holds column (kk + j) mod KB.
 // Rows pass through LDS 8 columns (a cache line) at a time on their way in and out: taken
 // directly, every 16-byte access of a wave would touch 64 lines.
+// A thread divides for its own candidate while the wave searches, and the pivot row reaches
+// the update as scalars (one LDS read per lane and lane reads): with a division after the
+// barrier and LDS broadcasts a panel of 16 columns took 28.8 us over 512 rows and 38.7 us
+// over 1024, now 25 and 33.  Per pivot (512 rows, cycle counter): about 1000 cycles to
+// search and publish, 440 across the barrier, 1150 for the update.
 template <int KB, int R, int NT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
 k_inv_panel(NDInv v, int w, int k0, int par) {
   constexpr int NW = NT / 64, CB = 8, LS = CB + 1;
   __shared__ cd s_row[2][NW][KB];
   __shared__ unsigned s_key[2][NW];
+  __shared__ int s_ok[2][NW], s_piv[KB];
+  int bad = 0;
   __shared__ cd s_t[NT * LS];
   const InvFront f = inv_front(v, blockIdx.x, w);
   if (k0 >= f.wn) return;
@@ -180,18 +199,33 @@ k_inv_panel(NDInv v, int w, int k0, int par) {
       for (int u = 0; u < CB; ++u) a[r][c + u] = s_t[t * LS + u];
     }
   }
-  unsigned key = 0;
+  unsigned kr[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) key = max(key, pivot_key(a[r][0], open[r], r * NT + t));
+  for (int r = 0; r < R; ++r) kr[r] = pivot_key(a[r][0], open[r], r * NT + t);
   for (int kk = 0; kk < kbb; ++kk) {
     const int b = kk & 1;
+    // this thread's candidate and its reciprocal: the division overlaps the wave's search
+    cd c0 = a[0][0];
+    unsigned key = kr[0];
+#pragma unroll
+    for (int r = 1; r < R; ++r) {
+      const bool up = kr[r] > key;
+      c0.x = up ? a[r][0].x : c0.x;
+      c0.y = up ? a[r][0].y : c0.y;
+      key = up ? kr[r] : key;
+    }
+    const double d = abs2(c0);
+    const double di = 1.0 / d;
     const unsigned wk = wave_umax(key);
     const int wrow = 1023 - (int)(wk & 1023u);
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (r * NT + t == wrow) {
 #pragma unroll
-        for (int j = 0; j < KB; ++j) s_row[b][wv][j] = a[r][j];
+        for (int j = 1; j < KB; ++j) s_row[b][wv][j] = a[r][j];
+        // slot 0: the reciprocal of the pivot (a zero or NaN pivot is recorded and taken as 1)
+        s_row[b][wv][0] = d > 0.0 ? mk(c0.x * di, -c0.y * di) : mk(1.0, 0.0);
+        s_ok[b][wv] = d > 0.0;
       }
     if (lane == 0) s_key[b][wv] = wk;
     __syncthreads();
@@ -200,31 +234,42 @@ k_inv_panel(NDInv v, int w, int k0, int par) {
     for (int q = 1; q < NW; ++q) bk = max(bk, s_key[b][q]);
     bk = (unsigned)__builtin_amdgcn_readfirstlane((int)bk);
     const int p = 1023 - (int)(bk & 1023u);            // the pivot row, counted from w0
-    const cd* __restrict__ row = s_row[b][(p & (NT - 1)) >> 6];
-    cd piv = row[0];
-    const bool ok = abs2(piv) > 0.0;
-    if (!ok) piv = mk(1.0, 0.0);
-    const cd inv = cdiv(mk(1.0, 0.0), piv);
+    const int pw = (p & (NT - 1)) >> 6;
+    // lane l takes entry l mod KB of the pivot row; the entries then pass as scalars
+    const cd rl = s_row[b][pw][t & (KB - 1)];
+    const cd inv = lane_cd(rl, 0);
     if (t == 0) {
-      f.pm[f.w0 + k0 + kk] = f.w0 + p;
-      f.ip[f.w0 + p] = f.w0 + k0 + kk;
-      if (!ok) atomicOr(v.err, 1);
+      s_piv[kk] = p;
+      if (!s_ok[b][pw]) bad = 1;
     }
-    key = 0;
+    cd ck[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      cd ck = a[r][0] * inv;
+      ck[r] = a[r][0] * inv;
       if (r * NT + t == p) {                           // the pivot row: -row / pivot, 1 / pivot
-        ck = inv;
+        ck[r] = inv;
         open[r] = false;
 #pragma unroll
         for (int j = 1; j < KB; ++j) a[r][j] = mk(0.0, 0.0);
       }
-#pragma unroll
-      for (int j = 0; j + 1 < KB; ++j) a[r][j] = a[r][j + 1] - ck * row[j + 1];
-      a[r][KB - 1] = ck;
-      key = max(key, pivot_key(a[r][0], open[r], r * NT + t));
     }
+#pragma unroll
+    for (int j = 0; j + 1 < KB; ++j) {
+      const cd rj = lane_cd(rl, j + 1);
+#pragma unroll
+      for (int r = 0; r < R; ++r) a[r][j] = csubmul(a[r][j + 1], ck[r], rj);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      a[r][KB - 1] = ck[r];
+      kr[r] = pivot_key(a[r][0], open[r], r * NT + t);
+    }
+  }
+  if (t == 0 && bad) atomicOr(v.err, 1);
+  __syncthreads();
+  if (t < kbb) {
+    f.pm[f.w0 + k0 + t] = f.w0 + s_piv[t];
+    f.ip[f.w0 + s_piv[t]] = f.w0 + k0 + t;
   }
   // slot j now holds column (kbb + j) mod KB
 #pragma unroll
@@ -244,31 +289,33 @@ k_inv_panel(NDInv v, int w, int k0, int par) {
 }
 
 // ------------------------------------------------------ complex FP64 products (MFMA) ----
-// C tile of 64 x 64, K deep: a work-group of 4 wavefronts, each a 32 x 32 quarter as 2 x 2
-// blocks of the 16 x 16 x 4 FP64 MFMA, real and imaginary parts accumulated separately:
+// C tile of GT x GT (64 or 32), K deep: a work-group of 4 wavefronts, each a quarter of 2 x 2
+// or 1 x 1 blocks of the 16 x 16 x 4 FP64 MFMA, real and imaginary parts accumulated separately:
 //   Cr += Ar Br - Ai Bi,  Ci += Ar Bi + Ai Br  (four real MFMAs per k group).
 // MFMA lane layout: A[m][k] from lane m + 16 k, B[k][n] from lane n + 16 k, and lane l
 // holds D[l / 16 + 4 i][l % 16], i < 4.  Panels of A and B pass through LDS, 16 k at a time;
 // the next 16 are loaded into registers while the matrix cores work on these.
-#define GT 64
 #define GK 16
 typedef double mfma_d4 __attribute__((ext_vector_type(4)));
+template <int GT>
 struct GemmLds {
   cd a[GK][GT + 1], b[GK][GT + 1];
 };
+template <int GT>
 struct GemmAcc {
-  mfma_d4 r[2][2], i[2][2];
+  mfma_d4 r[GT / 32][GT / 32], i[GT / 32][GT / 32];
 };
 // la(row, k) and lb(k, col): entries of the tile's operands; both are called for every
 // row and column of the tile and every k < K rounded up to 16, and return 0 outside
-template <class LA, class LB>
-__device__ __forceinline__ void gemm_tile(GemmLds& s, int K, GemmAcc& acc, LA la, LB lb) {
+template <int GT, class LA, class LB>
+__device__ __forceinline__ void gemm_tile(GemmLds<GT>& s, int K, GemmAcc<GT>& acc, LA la, LB lb) {
+  constexpr int NQ = GT / 32;            // 16 x 16 blocks of a wavefront per axis
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wr = (wv >> 1) * 32, wc = (wv & 1) * 32, lm = lane & 15, lk = lane >> 4;
+  const int wr = (wv >> 1) * (GT / 2), wc = (wv & 1) * (GT / 2), lm = lane & 15, lk = lane >> 4;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NQ; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < NQ; ++b) {
       acc.r[a][b] = mfma_d4{0.0, 0.0, 0.0, 0.0};
       acc.i[a][b] = mfma_d4{0.0, 0.0, 0.0, 0.0};
     }
@@ -294,25 +341,25 @@ __device__ __forceinline__ void gemm_tile(GemmLds& s, int K, GemmAcc& acc, LA la
     if (kk0 + GK < K) load(kk0 + GK);
 #pragma unroll
     for (int k4 = 0; k4 < GK; k4 += 4) {
-      cd av[2], bv[2];
+      cd av[NQ], bv[NQ];
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
+      for (int q = 0; q < NQ; ++q) {
         av[q] = s.a[k4 + lk][wr + 16 * q + lm];
         bv[q] = s.b[k4 + lk][wc + 16 * q + lm];
       }
       // the four products of a block go to two accumulators: issue them in rounds over the
-      // eight accumulators, so that no MFMA waits for the one just before it
+      // accumulators, so that no MFMA waits for the one just before it
 #pragma unroll
-      for (int qa = 0; qa < 2; ++qa)
+      for (int qa = 0; qa < NQ; ++qa)
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < NQ; ++qb) {
           acc.r[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[qa].x, bv[qb].x, acc.r[qa][qb], 0, 0, 0);
           acc.i[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[qa].x, bv[qb].y, acc.i[qa][qb], 0, 0, 0);
         }
 #pragma unroll
-      for (int qa = 0; qa < 2; ++qa)
+      for (int qa = 0; qa < NQ; ++qa)
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
+        for (int qb = 0; qb < NQ; ++qb) {
           acc.r[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[qa].y, bv[qb].y, acc.r[qa][qb], 0, 0, 0);
           acc.i[qa][qb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[qa].y, bv[qb].x, acc.i[qa][qb], 0, 0, 0);
         }
@@ -320,19 +367,27 @@ __device__ __forceinline__ void gemm_tile(GemmLds& s, int K, GemmAcc& acc, LA la
     __syncthreads();
   }
 }
-// st(row, col, value) for the tile's 64 x 64 entries
-template <class ST>
-__device__ __forceinline__ void gemm_store(const GemmAcc& acc, ST st) {
+// st(row, col, value, old) for the tile's entries, old = ld(row, col); the loads of a 16-column
+// strip are issued together (ld clamps its indices, so they stand under no branch)
+template <int GT, class LD, class ST>
+__device__ __forceinline__ void gemm_store(const GemmAcc<GT>& acc, LD ld, ST st) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wr = (wv >> 1) * 32, wc = (wv & 1) * 32, lm = lane & 15, lk = lane >> 4;
+  const int wr = (wv >> 1) * (GT / 2), wc = (wv & 1) * (GT / 2), lm = lane & 15, lk = lane >> 4;
 #pragma unroll
-  for (int qa = 0; qa < 2; ++qa)
+  for (int qb = 0; qb < GT / 32; ++qb) {
+    cd o[GT / 32][4];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
+    for (int qa = 0; qa < GT / 32; ++qa)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[qa][i] = ld(wr + 16 * qa + lk + 4 * i, wc + 16 * qb + lm);
+#pragma unroll
+    for (int qa = 0; qa < GT / 32; ++qa)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        st(wr + 16 * qa + lk + 4 * i, wc + 16 * qb + lm, mk(acc.r[qa][qb][i], acc.i[qa][qb][i]));
+        st(wr + 16 * qa + lk + 4 * i, wc + 16 * qb + lm, mk(acc.r[qa][qb][i], acc.i[qa][qb][i]), o[qa][i]);
+  }
 }
+__device__ __forceinline__ cd no_old(int, int) { return mk(0.0, 0.0); }
 #define GEMM_KERNEL __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
 
 // Columns outside a run K = [w0 + k0, + kw) of pivots (clipped to the window).  cmode 0: the
@@ -341,6 +396,7 @@ __device__ __forceinline__ void gemm_store(const GemmAcc& acc, ST st) {
 // entries Q'[:, K] are in copy pa, Q0 in copy par, and the result goes to copy par ^ 1.
 // pa < 0: a block's entries, whose copy depends on its number of panels of kb columns; where
 // that is copy par, they are copied over.
+template <int GT>
 GEMM_KERNEL k_inv_gemm(NDInv v, int w, int k0, int kw, int cmode, int b0, int bw, int par, int pa, int kb) {
   const InvFront f = inv_front(v, blockIdx.y, w);
   if (k0 >= f.wn || (cmode == 2 && f.nwin == 1)) return;
@@ -361,30 +417,40 @@ GEMM_KERNEL k_inv_gemm(NDInv v, int w, int k0, int kw, int cmode, int b0, int bw
   const int* __restrict__ pm = f.pm + K0;
   const bool inside = c0 + tn >= K0 && c0 + min(tn + GT, nc) <= K0 + kn;   // only columns of K
   if (inside && pa == po) return;
-  __shared__ GemmLds s;
-  GemmAcc acc;
+  __shared__ GemmLds<GT> s;
+  GemmAcc<GT> acc;
   if (!inside)
-    gemm_tile(
+    gemm_tile<GT>(
         s, kn, acc,
         [&](int r, int k) { return tm + r < M && k < kn ? A[(tm + r) * la + k] : mk(0.0, 0.0); },
         [&](int k, int c) {
           return tn + c < nc && k < kn ? Q0[pm[k] * l0 + c0 + tn + c] : mk(0.0, 0.0);
         });
-  gemm_store(acc, [&](int r, int c, cd x) {
-    const int i = r0 + tm + r, j = c0 + tn + c;
-    if (tm + r >= M || tn + c >= nc) return;
-    if (j >= K0 && j < K0 + kn) {
-      if (pa != po) O[i * lo + j] = A[(tm + r) * la + (j - K0)];
-      return;
-    }
-    const int q = f.ip[i];
-    const cd o = q >= K0 && q < K0 + kn ? mk(0.0, 0.0) : Q0[i * l0 + j];
-    O[i * lo + j] = o - x;
-  });
+  gemm_store<GT>(
+      acc,
+      [&](int r, int c) {
+        // old entry; 0 in the run's pivot rows.  Columns of K: the entry to copy
+        const int i = r0 + min(tm + r, M - 1), j = c0 + min(tn + c, nc - 1);
+        const bool own = j >= K0 && j < K0 + kn;
+        const cd* __restrict__ src = own ? A + (i - r0) * la + (j - K0) : Q0 + i * l0 + j;
+        const int q = f.ip[i];
+        const cd o = *src;
+        return !own && q >= K0 && q < K0 + kn ? mk(0.0, 0.0) : o;
+      },
+      [&](int r, int c, cd x, cd o) {
+        const int i = r0 + tm + r, j = c0 + tn + c;
+        if (tm + r >= M || tn + c >= nc) return;
+        if (j >= K0 && j < K0 + kn) {
+          if (pa != po) O[i * lo + j] = o;
+        } else {
+          O[i * lo + j] = o - x;
+        }
+      });
 }
 
 // a finished window's columns in the rows outside it: Q'[i, K] = Q0[i, K] Q'[pm[K], K]; the
 // window's own rows are copied where its result is not in copy par ^ 1 already
+template <int GT>
 GEMM_KERNEL k_inv_outer(NDInv v, int w, int par, int kout) {
   const InvFront f = inv_front(v, blockIdx.y, w);
   if (f.nwin == 1 || f.wn <= 0) return;
@@ -400,13 +466,13 @@ GEMM_KERNEL k_inv_outer(NDInv v, int w, int par, int kout) {
   const int* __restrict__ pm = f.pm + f.w0;
   const bool inside = tm >= f.w0 && min(tm + GT, M) <= f.w0 + f.wn;
   if (inside && pr == po) return;
-  __shared__ GemmLds s;
-  GemmAcc acc;
+  __shared__ GemmLds<GT> s;
+  GemmAcc<GT> acc;
   if (!inside)
-    gemm_tile(
+    gemm_tile<GT>(
         s, N, acc, [&](int r, int k) { return tm + r < M && k < N ? A[(tm + r) * la + k] : mk(0.0, 0.0); },
         [&](int k, int c) { return tn + c < N && k < N ? B[pm[k] * lb + tn + c] : mk(0.0, 0.0); });
-  gemm_store(acc, [&](int r, int c, cd x) {
+  gemm_store<GT>(acc, no_old, [&](int r, int c, cd x, cd) {
     const int i = tm + r, j = tn + c;
     if (i >= M || j >= N) return;
     if (i >= f.w0 && i < f.w0 + f.wn) {
@@ -458,7 +524,7 @@ __global__ void __launch_bounds__(256) k_inv_final(NDInv v, int kout, C* __restr
 // W = -A^-1 B: in FP64 for the Schur product (T, nS x nB row major), in the substitution's
 // precision into W and, for a complex symmetric operator, as C A^-1 = (A^-1 B)^T into the
 // lower block of L
-template <typename C, int SYM>
+template <int GT, typename C, int SYM>
 GEMM_KERNEL k_nd_w(NDInv v, const long long* __restrict__ toff, int kout, cd* __restrict__ T, C* __restrict__ Lp,
                    C* __restrict__ Wp) {
   const NDFrontDev fr = v.hf[blockIdx.y];
@@ -472,12 +538,12 @@ GEMM_KERNEL k_nd_w(NDInv v, const long long* __restrict__ toff, int kout, cd* __
   const cd* __restrict__ B = v.F + fr.F_off + nS;
   const long long ln = f.ld(pn), lf = fr.nF;
   cd* __restrict__ Tt = T + toff[blockIdx.y];
-  __shared__ GemmLds s;
-  GemmAcc acc;
-  gemm_tile(
+  __shared__ GemmLds<GT> s;
+  GemmAcc<GT> acc;
+  gemm_tile<GT>(
       s, nS, acc, [&](int r, int k) { return tm + r < nS && k < nS ? N[(tm + r) * ln + k] : mk(0.0, 0.0); },
       [&](int k, int c) { return tn + c < nB && k < nS ? B[k * lf + tn + c] : mk(0.0, 0.0); });
-  gemm_store(acc, [&](int r, int c, cd x) {
+  gemm_store<GT>(acc, no_old, [&](int r, int c, cd x, cd) {
     const int k = tm + r, j = tn + c;
     if (k >= nS || j >= nB) return;
     Tt[(long long)k * nB + j] = -x;
@@ -487,7 +553,7 @@ GEMM_KERNEL k_nd_w(NDInv v, const long long* __restrict__ toff, int kout, cd* __
 }
 
 // C A^-1 into the lower block of L (operators that are not symmetric)
-template <typename C>
+template <int GT, typename C>
 GEMM_KERNEL k_nd_x(NDInv v, int kout, C* __restrict__ Lp) {
   const NDFrontDev fr = v.hf[blockIdx.y];
   const int nS = fr.nS, nB = fr.nB;
@@ -499,12 +565,12 @@ GEMM_KERNEL k_nd_x(NDInv v, int kout, C* __restrict__ Lp) {
   const cd* __restrict__ N = f.q(pn);
   const cd* __restrict__ Cb = v.F + fr.F_off + (long long)nS * fr.nF;
   const long long ln = f.ld(pn), lf = fr.nF;
-  __shared__ GemmLds s;
-  GemmAcc acc;
-  gemm_tile(
+  __shared__ GemmLds<GT> s;
+  GemmAcc<GT> acc;
+  gemm_tile<GT>(
       s, nS, acc, [&](int r, int k) { return tm + r < nB && k < nS ? Cb[(tm + r) * lf + k] : mk(0.0, 0.0); },
       [&](int k, int c) { return tn + c < nS && k < nS ? N[k * ln + tn + c] : mk(0.0, 0.0); });
-  gemm_store(acc, [&](int r, int c, cd x) {
+  gemm_store<GT>(acc, no_old, [&](int r, int c, cd x, cd) {
     if (tm + r < nB && tn + c < nS)
       Lp[fr.L_off + (long long)(tn + c) * fr.ldL + nS + tm + r] = conv<C>::from(x);
   });
@@ -512,7 +578,7 @@ GEMM_KERNEL k_nd_x(NDInv v, int kout, C* __restrict__ Lp) {
 
 // D += C W, the front's Schur complement; for a complex symmetric operator the tiles on and
 // below the diagonal, the others being their mirror images
-template <int SYM>
+template <int GT, int SYM>
 GEMM_KERNEL k_nd_schur(NDInv v, const long long* __restrict__ toff, const cd* __restrict__ T) {
   const NDFrontDev fr = v.hf[blockIdx.y];
   const int nS = fr.nS, nB = fr.nB, nt = steps_of(nB, GT);
@@ -532,15 +598,16 @@ GEMM_KERNEL k_nd_schur(NDInv v, const long long* __restrict__ toff, const cd* __
   cd* __restrict__ F = v.F + fr.F_off + (long long)nS * fr.nF;
   const cd* __restrict__ Tt = T + toff[blockIdx.y];
   const long long lf = fr.nF;
-  __shared__ GemmLds s;
-  GemmAcc acc;
-  gemm_tile(
+  __shared__ GemmLds<GT> s;
+  GemmAcc<GT> acc;
+  gemm_tile<GT>(
       s, nS, acc, [&](int r, int k) { return tm + r < nB && k < nS ? F[(tm + r) * lf + k] : mk(0.0, 0.0); },
       [&](int k, int c) { return tn + c < nB && k < nS ? Tt[(long long)k * nB + tn + c] : mk(0.0, 0.0); });
-  gemm_store(acc, [&](int r, int c, cd x) {
+  gemm_store<GT>(acc, [&](int r, int c) { return F[min(tm + r, nB - 1) * lf + nS + min(tn + c, nB - 1)]; },
+                 [&](int r, int c, cd x, cd o) {
     const int i = tm + r, j = tn + c;
     if (i >= nB || j >= nB) return;
-    const cd d = F[i * lf + nS + j] + x;
+    const cd d = o + x;
     F[i * lf + nS + j] = d;
     if (SYM && bm != bn) F[j * lf + nS + i] = d;
   });
@@ -587,7 +654,18 @@ static void inv_panel(const NDInv& v, int nids, int rows, int w, int k0, int par
   else
     throw std::runtime_error("nd_invert: window of more than 1024 rows");
 }
-static unsigned tiles(int m, int n) { return (unsigned)(((m + GT - 1) / GT) * ((n + GT - 1) / GT)); }
+// A product's tiles are 64 x 64, or 32 x 32 where 64 x 64 ones would not give every CU one:
+// there the launch lasts as long as one tile (a 16-deep update of 577 columns: 16.3 us with
+// 64 x 64 tiles and their old entries loaded one by one, 7.2 us).
+static unsigned tiles(int m, int n, int gt) { return (unsigned)(((m + gt - 1) / gt) * ((n + gt - 1) / gt)); }
+static bool small_tiles(int m, int n, int nids) { return (long long)tiles(m, n, 64) * nids < 256; }
+#define LAUNCH_GEMM(m, n, nids, s, k64, k32, ...)                                                     \
+  do {                                                                                                \
+    if (small_tiles(m, n, nids))                                                                      \
+      hipLaunchKernelGGL((k32), dim3(tiles(m, n, 32), nids), dim3(256), 0, s, __VA_ARGS__);           \
+    else                                                                                              \
+      hipLaunchKernelGGL((k64), dim3(tiles(m, n, 64), nids), dim3(256), 0, s, __VA_ARGS__);           \
+  } while (0)
 
 int nd_invert(const NDInv& v, int nids, int max_nS, int max_wn, int block_cols, hipStream_t s) {
   const int kb = panel_cols(max_wn);
@@ -598,19 +676,19 @@ int nd_invert(const NDInv& v, int nids, int max_nS, int max_wn, int block_cols, 
       const int cur = (w ^ blk) & 1;            // the copy that holds A before this block
       const int nb = std::min(kout, max_wn - b0);
       for (int k0 = b0, q = 0; k0 < b0 + nb; k0 += kb, ++q) {
-        inv_panel(v, nids, max_wn, w, k0, cur ^ (q & 1), s);
+        const int par = cur ^ (q & 1);
+        inv_panel(v, nids, max_wn, w, k0, par, s);
         if (nb > kb)                             // the block's other panels, earlier ones included
-          hipLaunchKernelGGL(k_inv_gemm, dim3(tiles(max_wn, nb), nids), dim3(256), 0, s, v, w, k0, kb, 0, b0, kout,
-                             cur ^ (q & 1), cur ^ (q & 1) ^ 1, kb);
+          LAUNCH_GEMM(max_wn, nb, nids, s, k_inv_gemm<64>, k_inv_gemm<32>, v, w, k0, kb, 0, b0, kout, par, par ^ 1,
+                      kb);
       }
       if (max_wn > kb)
-        hipLaunchKernelGGL(k_inv_gemm, dim3(tiles(max_wn, max_wn), nids), dim3(256), 0, s, v, w, b0, kout, 1, 0, 0,
-                           cur, -1, kb);
+        LAUNCH_GEMM(max_wn, max_wn, nids, s, k_inv_gemm<64>, k_inv_gemm<32>, v, w, b0, kout, 1, 0, 0, cur, -1, kb);
     }
     if (nwin > 1) {
-      hipLaunchKernelGGL(k_inv_outer, dim3(tiles(max_nS, max_wn), nids), dim3(256), 0, s, v, w, w & 1, kout);
-      hipLaunchKernelGGL(k_inv_gemm, dim3(tiles(max_nS, max_nS), nids), dim3(256), 0, s, v, w, 0, max_wn, 2, 0, 0,
-                         w & 1, (w & 1) ^ 1, kb);
+      const int par = w & 1;
+      LAUNCH_GEMM(max_nS, max_wn, nids, s, k_inv_outer<64>, k_inv_outer<32>, v, w, par, kout);
+      LAUNCH_GEMM(max_nS, max_nS, nids, s, k_inv_gemm<64>, k_inv_gemm<32>, v, w, 0, max_wn, 2, 0, 0, par, par ^ 1, kb);
     }
   }
   return kout;
@@ -619,16 +697,22 @@ int nd_invert(const NDInv& v, int nids, int max_nS, int max_wn, int block_cols, 
 template <typename C>
 void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, int sym, const long long* toff, cd* T,
                  C* Lp, C* Wp, hipStream_t s) {
-  const int nt = (max_nS + 31) / 32, nb = (max_nB + GT - 1) / GT;
+  const int nt = (max_nS + 31) / 32;
+  const cd* Tc = T;
   hipLaunchKernelGGL((k_inv_final<C>), dim3(nt * nt, nids), dim3(256), 0, s, v, kout, Lp);
   if (max_nB == 0) return;
   if (sym) {
-    hipLaunchKernelGGL((k_nd_w<C, 1>), dim3(tiles(max_nS, max_nB), nids), dim3(256), 0, s, v, toff, kout, T, Lp, Wp);
-    hipLaunchKernelGGL((k_nd_schur<1>), dim3(nb * (nb + 1) / 2, nids), dim3(256), 0, s, v, toff, (const cd*)T);
+    LAUNCH_GEMM(max_nS, max_nB, nids, s, (k_nd_w<64, C, 1>), (k_nd_w<32, C, 1>), v, toff, kout, T, Lp, Wp);
+    const bool small = small_tiles(max_nB, max_nB / 2, nids);
+    const int nb = (max_nB + (small ? 31 : 63)) / (small ? 32 : 64);
+    if (small)
+      hipLaunchKernelGGL((k_nd_schur<32, 1>), dim3(nb * (nb + 1) / 2, nids), dim3(256), 0, s, v, toff, Tc);
+    else
+      hipLaunchKernelGGL((k_nd_schur<64, 1>), dim3(nb * (nb + 1) / 2, nids), dim3(256), 0, s, v, toff, Tc);
   } else {
-    hipLaunchKernelGGL((k_nd_w<C, 0>), dim3(tiles(max_nS, max_nB), nids), dim3(256), 0, s, v, toff, kout, T, Lp, Wp);
-    hipLaunchKernelGGL((k_nd_x<C>), dim3(tiles(max_nB, max_nS), nids), dim3(256), 0, s, v, kout, Lp);
-    hipLaunchKernelGGL((k_nd_schur<0>), dim3(nb * nb, nids), dim3(256), 0, s, v, toff, (const cd*)T);
+    LAUNCH_GEMM(max_nS, max_nB, nids, s, (k_nd_w<64, C, 0>), (k_nd_w<32, C, 0>), v, toff, kout, T, Lp, Wp);
+    LAUNCH_GEMM(max_nB, max_nS, nids, s, (k_nd_x<64, C>), (k_nd_x<32, C>), v, kout, Lp);
+    LAUNCH_GEMM(max_nB, max_nB, nids, s, (k_nd_schur<64, 0>), (k_nd_schur<32, 0>), v, toff, Tc);
   }
 }
 template void nd_products<cf>(const NDInv&, int, int, int, int, int, const long long*, cd*, cf*, cf*, hipStream_t);
