@@ -280,8 +280,8 @@ int helm_get_timing(helm_ctx* ctx, double* t, int n);
  * [8] forward and [9] backward substitution kernel launches per coarsest solve, [10] workspace
  * bytes, [11] largest front size nF, [12] bytes per complex of the cycle (8 or 16),
  * [13] leaf box size and [14] root merge limit of the nested dissection, [15] 1 if the
- * schedule came from the autotuner cache (HELM_TUNE_CACHE), [16] number of tree-block
- * launches per direction, [17..20] the heights closing them (-1 beyond), [21] bit mask of
+ * schedule came from the autotuner cache (HELM_TUNE_CACHE), [16] 0 and [17..20] -1 (the
+ * substitution has one kind of launch per height), [21] bit mask of
  * the dissection-tree heights whose fronts were merged into their parents, [22] and [23]
  * coefficient planes of the stored level-2 and level-3 operators ((2r+1)^dim for stencil
  * radius r: 9 / 27 for the 5/7-point stack), [24] bytes per complex of the coarsest solve's

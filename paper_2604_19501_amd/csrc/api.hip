@@ -39,11 +39,11 @@ template <typename C>
 void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, int sym, const long long* toff, cd* T,
                  C* Lp, C* Wp, hipStream_t s);
 template <typename C>
-void nd_fwd(const NDLaunchDev& L, const NDFrontDev* fr, const int* idx, const int* cptr, const int* cidx,
-            const C* Lp, C* upd, const C* r, C* x, C* gvec, int cap, int conj, C* P, const NDRhs& rh, hipStream_t s);
+void nd_fwd(const NDLaunchDev& L, const NDFrontDev* fr, const int* idx, const int* cidx, const C* Lp, C* upd,
+            const C* r, C* x, int conj, C* P, const NDRhs& rh, hipStream_t s);
 template <typename C>
 void nd_bwd(const NDLaunchDev& L, const NDFrontDev* fr, const int* idx, const int* cidx, const C* Wp, C* upd, C* x,
-            C* gvec, int cap, int conj, C* P, const NDRhs& rh, hipStream_t s);
+            int conj, C* P, const NDRhs& rh, hipStream_t s);
 void grad_accumulate(const FineOp& op, double omega, const cd* u, const cd* lam, double* g, int first,
                      hipStream_t s);
 
@@ -91,7 +91,7 @@ struct Carver {
 struct NDDev {        // device-side ND tables (pointers into the workspace)
   NDFrontDev* fronts = nullptr;
   NDFrontDev* hfr = nullptr;   // fronts in height order
-  int *idx = nullptr, *maps = nullptr, *cptr = nullptr, *cidx = nullptr, *perm = nullptr, *iperm = nullptr,
+  int *idx = nullptr, *maps = nullptr, *cidx = nullptr, *perm = nullptr, *iperm = nullptr,
       *err = nullptr;
   int* children = nullptr;
   long long* child_map_off = nullptr;
@@ -102,19 +102,17 @@ struct NDDev {        // device-side ND tables (pointers into the workspace)
   cd *G = nullptr;      // second copy of one height's separator blocks
   void *L = nullptr, *W = nullptr;
   std::vector<NDLaunchDev> launch[2];   // forward, backward
-  int gvec_cap = 0;
-  long long part_n = 1, gvec_n = 0;   // entries per right-hand side of part, gvec
+  long long part_n = 1;   // entries per right-hand side of part
 };
 
 // Per-call scratch of one cycle: the iterates and right-hand sides of levels 1-3 and the
-// coarsest solve's update pool, global gather vectors (launches whose vectors do not fit
-// in LDS) and split-K partial products.  Nothing in it needs to
+// coarsest solve's update pool and split-K partial products.  Nothing in it needs to
 // start at zero: every entry is written before it is read within the call.  Sized for
 // rc right-hand sides in lock-step.
 struct CycleScratch {
   void *x1a = nullptr, *x1b = nullptr, *b2 = nullptr, *x2a = nullptr, *x2b = nullptr, *b3 = nullptr,
        *x3 = nullptr;
-  void *upd = nullptr, *gvec = nullptr, *part = nullptr;
+  void *upd = nullptr, *part = nullptr;
 };
 
 // kernel classes timed with HIP events when timing is on
@@ -185,7 +183,6 @@ struct helm_ctx {
   long long kt_cnt[KT_N] = {0};
   std::vector<Pending> pending;
   std::vector<hipEvent_t> evpool;
-  size_t lds_limit = 65536;     // LDS bytes for substitution vectors
   int nd_win = 1024;            // rows of an inversion window of the factorisation (HELM_ND_WIN)
   bool tuned = false;           // schedule parameters came from the autotuner cache
   int nd_leaf = 0, nd_root = 0;  // nested-dissection leaf size and root merge limit in use
@@ -246,7 +243,7 @@ int validate(const helm_grid* g, const helm_mg* mg) {
 }
 
 // kernels one substitution step launches (a split-K step: tiles, row sums)
-int nd_step_kernels(int kind) { return kind == 3 ? 2 : 1; }
+int nd_step_kernels(int kind) { return kind == 2 ? 2 : 1; }
 int nd_kernels(const std::vector<NDLaunchDev>& Ls) {
   int k = 0;
   for (const NDLaunchDev& L : Ls) k += nd_step_kernels(L.kind);
@@ -319,13 +316,13 @@ int env_int(const char* name, int dflt) {
 // schedule parameters of the coarsest solve picked by the autotuner: the JSON file named
 // by HELM_TUNE_CACHE maps "nd:<dim>:<n0>x<n1>x<n2>:<f32|f64>" (the coarsest solve's
 // precision; ":r<radius>" appended when the coarsest stencil radius is not 1) to an object
-// with the integers "leaf", "root" and "splitk_kb" and the strings "cuts", "merge" and
+// with the integers "leaf", "root" and "splitk_kb" and the strings "merge" and
 // "boxes" among its members (others, nested objects and arrays included, are skipped);
 // returns false when the file or the key is absent
 struct TunedND {
   int leaf = -1, root = -1, splitk_kb = -1;
-  std::string cuts, merge, boxes;
-  bool has_cuts = false, has_merge = false, has_boxes = false;
+  std::string merge, boxes;
+  bool has_merge = false, has_boxes = false;
 };
 
 // the members of the JSON object starting at txt[ob] == '{' that sit directly in it:
@@ -408,56 +405,62 @@ bool tuned_nd(const helm_ctx* c, TunedND& t) {
   num("leaf", t.leaf);
   num("root", t.root);
   num("splitk_kb", t.splitk_kb);
-  str("cuts", t.cuts, t.has_cuts);
   str("merge", t.merge, t.has_merge);
   str("boxes", t.boxes, t.has_boxes);
   return true;
 }
 
-std::vector<int> parse_cuts(const char* v) {
-  std::vector<int> cuts;
+std::vector<int> parse_list(const char* v) {
+  std::vector<int> list;
   if (!strcmp(v, "none")) {
-    cuts.push_back(-1);
-    return cuts;
+    list.push_back(-1);
+    return list;
   }
   for (const char* p = v; *p;) {
     char* e = nullptr;
     long h = strtol(p, &e, 10);
     if (e == p) break;
-    cuts.push_back((int)h);
+    list.push_back((int)h);
     p = *e == ',' ? e + 1 : e;
   }
-  return cuts;
+  return list;
 }
 
-// nested-dissection parameters: environment (HELM_ND_LEAF, HELM_ND_ROOT, HELM_ND_CUTS,
-// HELM_ND_MERGE), else the autotuner's cache, else defaults and the planner's cost model
+// nested-dissection parameters: environment (HELM_ND_LEAF, HELM_ND_ROOT, HELM_ND_MERGE,
+// HELM_ND_SPLITK_KB), else the autotuner's cache, else defaults
 void build_plan(helm_ctx* c) {
   TunedND tn;
   const bool tuned = tuned_nd(c, tn);
-  const int leaf = env_int("HELM_ND_LEAF", tuned && tn.leaf > 0 ? tn.leaf : (c->grid.dim == 3 ? 8 : 32));
-  const int merge = env_int("HELM_ND_ROOT", tuned && tn.root > 0 ? tn.root : (c->grid.dim == 3 ? 1 : 1100));
-  const int lds = env_int("HELM_ND_LDS", 65536);
-  // cuts: heights closing the tree-block launches ("3,6,8"), "none" for none, empty for
-  // the cost model's choice
-  std::vector<int> cuts;
-  if (const char* v = getenv("HELM_ND_CUTS"))
-    cuts = parse_cuts(v);
-  else if (tuned && tn.has_cuts)
-    cuts = parse_cuts(tn.cuts.c_str());
+  // Defaults without a cache entry.  A substitution is a chain of one launch per level and
+  // direction, so merging levels pays while the levels are bound by latency, until the merged
+  // fronts' extra entries and factorisation time outweigh it (microseconds per FGMRES
+  // iteration, no merge / odd levels / two of three):
+  //   5-point 2D: 600x640 FP64 250 / 207 / 182, 900x516 with 4 sources 539 / - / 347; leaves
+  //   of 64 nodes, 32 on large grids (1024^2: 276 against 282 us)
+  //   7-point 3D: 80x72x64 314 / 258 / 247 with set-ups of 1.8 / 2.0 / 3.1 ms, 96^3 391 / 338 /
+  //   317 with 4.1 / 5.1 / 7.4 ms: odd levels on small grids, none on larger ones
+  //   compact stack: its slabs of 2 or 3 planes make merged fronts too large (1024^2: 844 us
+  //   and a set-up of 9.5 ms without, 908 us and 24.6 ms with two of three)
+  const bool d3 = c->grid.dim == 3;
+  const long long N3 = c->g3.tot;
+  const int leaf = env_int("HELM_ND_LEAF", tuned && tn.leaf > 0 ? tn.leaf : N3 <= (d3 ? 100000 : 40000) ? 64 : 32);
+  const int merge = env_int("HELM_ND_ROOT", tuned && tn.root > 0 ? tn.root : (d3 ? 1 : 1100));
   // merged heights: "1,3,5" (heights of the dissection tree whose fronts join their
   // parents), "none" or empty for none
   std::vector<int> mh;
   {
     const char* v = getenv("HELM_ND_MERGE");
     std::string mv = v ? std::string(v) : (tuned && tn.has_merge ? tn.merge : std::string());
-    if (!mv.empty() && mv != "none") mh = parse_cuts(mv.c_str());
+    if (!mv.empty() && mv != "none") mh = parse_list(mv.c_str());
+    if (!v && !tuned && !c->compact && (!d3 || N3 <= 12000))
+      for (int h = 1; h <= 40; ++h)
+        if (d3 ? h % 2 : h % 3) mh.push_back(h);
   }
   // box variants of the cycle kernels: "a,b,c,d" (HELM_BOXES, else the cache; default 0)
   {
     const char* v = getenv("HELM_BOXES");
     std::string bv = v ? std::string(v) : (tuned && tn.has_boxes ? tn.boxes : std::string());
-    std::vector<int> bx = bv.empty() ? std::vector<int>() : parse_cuts(bv.c_str());
+    std::vector<int> bx = bv.empty() ? std::vector<int>() : parse_list(bv.c_str());
     for (int q = 0; q < 4; ++q) {
       c->box[q] = q < (int)bx.size() ? bx[q] : 0;
       const int nmax = (q % 2 == 0) ? 6 : 5;     // sweeps: 6 variants, restrictions: 5
@@ -472,13 +475,12 @@ void build_plan(helm_ctx* c) {
   c->tuned = tuned;
   c->nd_leaf = leaf;
   c->nd_root = merge;
-  // heights above the tree blocks with at least this many factor bytes use split-K launches
+  // heights with at least this many factor bytes use split-K launches: below, one row-block
+  // launch is shorter than tiles and row sums (256^3: 3.66 ms per iteration with 96 MB, 4.71 with
+  // 4 MB; 1024^2 compact: 0.84 ms without split-K, 1.16 with 16 MB)
   const long long splitk =
-      (long long)env_int("HELM_ND_SPLITK_KB", tuned && tn.splitk_kb > 0 ? tn.splitk_kb : 4096) * 1024;
-  // tree-block work-groups of at most HELM_ND_TREE_WAVES wavefronts: 16 in 2D; 8 in 3D, where
-  // the many small subtrees run two work-groups per CU (measured 3 % faster at 256^3)
-  const int tree_waves = env_int("HELM_ND_TREE_WAVES", c->grid.dim == 3 ? 8 : 16);
-  nd_plan(c->g3, leaf, 16, merge, (int)c->ndsz, lds, cuts, splitk, c->plan, tree_waves, mh, c->r3);
+      (long long)env_int("HELM_ND_SPLITK_KB", tuned && tn.splitk_kb > 0 ? tn.splitk_kb : 98304) * 1024;
+  nd_plan(c->g3, leaf, merge, (int)c->ndsz, splitk, c->plan, mh, c->r3);
   // inversion windows of the factorisation: 16 to 1024 rows, a multiple of 16
   c->nd_win = std::max(16, std::min(1024, env_int("HELM_ND_WIN", 1024) / 16 * 16));
   NDPlan& P = c->plan;
@@ -529,7 +531,6 @@ CycleScratch carve_scratch(const helm_ctx* c, Carver& cv, int rc) {
   w.b3 = cv.take<char>(r * ns * c->g3.tot);       // the coarsest solve's vectors: its precision
   w.x3 = cv.take<char>(r * ns * c->g3.tot);
   w.upd = cv.take<char>(r * ns * std::max<long long>(1, c->plan.upd_total));
-  w.gvec = d.gvec_n ? cv.take<char>(r * ns * d.gvec_n) : nullptr;
   w.part = cv.take<char>(r * ns * d.part_n);
   return w;
 }
@@ -560,7 +561,6 @@ size_t carve(helm_ctx* c, void* ws) {
   d.fronts = cv.take<NDFrontDev>(P.fronts.size());
   d.idx = cv.take<int>(P.idx.size());
   d.maps = cv.take<int>(std::max<size_t>(1, P.maps.size()));
-  d.cptr = cv.take<int>(std::max<size_t>(1, P.cptr.size()));
   d.cidx = cv.take<int>(std::max<size_t>(1, P.cidx.size()));
   d.children = cv.take<int>(std::max<size_t>(1, P.children.size()));
   d.child_map_off = cv.take<long long>(std::max<size_t>(1, P.child_map_off.size()));
@@ -584,51 +584,22 @@ size_t carve(helm_ctx* c, void* ws) {
       const NDLaunch& L = Ls[l];
       NDLaunchDev& D = d.launch[fb][l];
       D.kind = L.kind;
-      D.threads = L.threads;
-      D.lds_bytes = L.lds_bytes;
+      D.gath = cv.take<NDGather>(std::max<size_t>(1, L.gath.size()));
       if (L.kind == 2) {
-        D.ntasks = (int)L.tasks.size();
-        D.tasks = cv.take<NDTask>(std::max<size_t>(1, L.tasks.size()));
-        D.stages = cv.take<NDStage>(std::max<size_t>(1, L.stages.size()));
-        D.gath = cv.take<NDGather>(std::max<size_t>(1, L.gath.size()));
-        D.segs = cv.take<NDSeg>(std::max<size_t>(1, L.segs.size()));
-        D.outs = cv.take<NDOut>(std::max<size_t>(1, L.outs.size()));
-        D.dst = cv.take<int>(std::max<size_t>(1, L.dst.size()));
-      } else if (L.kind == 3) {
-        D.ngath = (int)L.gath.size();
         D.ntiles = (int)L.tiles.size();
         D.nrt = (int)L.rtiles.size();
-        D.gath = cv.take<NDGather>(std::max<size_t>(1, L.gath.size()));
         D.tiles = cv.take<NDTile>(std::max<size_t>(1, L.tiles.size()));
         D.rtiles = cv.take<NDRowTile>(std::max<size_t>(1, L.rtiles.size()));
         part_max = std::max(part_max, L.p_elems);
       } else {
-        D.ntasks = (int)L.task_off.size() - 1;
-        D.task_off = cv.take<int>(L.task_off.size());
-        D.items = cv.take<NDItem>(L.items.size());
-        D.gath = cv.take<NDGather>(std::max<size_t>(1, L.gath.size()));
+        D.nrows = (int)L.rows.size();
+        D.rb = L.rb;
+        D.waves = L.waves;
+        D.max_k = L.max_k;
+        D.rows = cv.take<NDRow>(std::max<size_t>(1, L.rows.size()));
       }
     }
   }
-  // global fall-back vectors for launches whose vectors do not fit in LDS
-  // (a subtree task holds one vector per wavefront)
-  long long gcap = 0, gneed = 0;
-  for (int fb = 0; fb < 2; ++fb)
-    for (size_t l = 0; l < (fb == 0 ? P.fwd : P.bwd).size(); ++l) {
-      const NDLaunch& L = (fb == 0 ? P.fwd : P.bwd)[l];
-      if (L.kind != 1) continue;
-      const size_t need = (size_t)L.max_rows_vec * c->ndsz;
-      d.launch[fb][l].shm = need <= c->lds_limit ? std::max<size_t>(need, 16) : 0;
-      // 1024-thread work-groups (64 k-splits) where a vector exceeds 256 entries, if the
-      // launch fits the chip at once (decided at launch time with the right-hand sides)
-      d.launch[fb][l].threads = L.max_rows_vec > 256 ? 1024 : 256;
-      if (need > c->lds_limit) {
-        gcap = std::max<long long>(gcap, L.max_rows_vec);
-        gneed = std::max<long long>(gneed, (long long)(L.task_off.size() - 1));
-      }
-    }
-  d.gvec_cap = (int)gcap;
-  d.gvec_n = gcap * gneed;
   d.part_n = part_max;
   c->scr = carve_scratch(c, cv, (int)rc);
   // Krylov
@@ -725,26 +696,19 @@ void nd_solve(helm_ctx* c, const CycleScratch& w, const C* r, C* x, int conj, hi
   rh.vec = c->g3.tot;
   rh.upd = std::max<long long>(1, c->plan.upd_total);
   rh.part = d.part_n;
-  rh.gvec = d.gvec_n;
   // timing: one event pair around each direction's launches (they run back to back), so
   // that the per-launch average carries no per-launch event overhead
   hipEvent_t e0 = nullptr;
   if (c->timing) CK(hipEventRecord(e0 = ev_get(c), s));
-  for (const NDLaunchDev& L : d.launch[0]) {
-    C* gv = L.kind == 1 && L.shm == 0 ? (C*)w.gvec : nullptr;
-    nd_fwd<C>(L, d.fronts, d.idx, d.cptr, d.cidx, (const C*)d.L, (C*)w.upd, r, x, gv, d.gvec_cap, conj,
-              (C*)w.part, rh, s);
-  }
+  for (const NDLaunchDev& L : d.launch[0])
+    nd_fwd<C>(L, d.fronts, d.idx, d.cidx, (const C*)d.L, (C*)w.upd, r, x, conj, (C*)w.part, rh, s);
   hipEvent_t e1 = nullptr;
   if (c->timing) {
     CK(hipEventRecord(e1 = ev_get(c), s));
     c->pending.push_back(Pending{KT_ND_FWD, e0, e1, nd_kernels(d.launch[0])});
   }
-  for (const NDLaunchDev& L : d.launch[1]) {
-    C* gv = L.kind == 1 && L.shm == 0 ? (C*)w.gvec : nullptr;
-    nd_bwd<C>(L, d.fronts, d.idx, d.cidx, (const C*)d.W, (C*)w.upd, x, gv, d.gvec_cap, conj, (C*)w.part,
-              rh, s);
-  }
+  for (const NDLaunchDev& L : d.launch[1])
+    nd_bwd<C>(L, d.fronts, d.idx, d.cidx, (const C*)d.W, (C*)w.upd, x, conj, (C*)w.part, rh, s);
   if (c->timing && !d.launch[1].empty()) {
     hipEvent_t e2 = ev_get(c);
     CK(hipEventRecord(e2, s));
@@ -1389,7 +1353,6 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
     up(d.fronts, P.fronts, s);
     up(d.idx, P.idx, s);
     up(d.maps, P.maps, s);
-    up(d.cptr, P.cptr, s);
     up(d.cidx, P.cidx, s);
     up(d.children, P.children, s);
     up(d.child_map_off, P.child_map_off, s);
@@ -1406,22 +1369,10 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
       std::vector<NDLaunch>& Ls = fb == 0 ? P.fwd : P.bwd;
       for (size_t l = 0; l < Ls.size(); ++l) {
         NDLaunchDev& D = d.launch[fb][l];
-        if (Ls[l].kind == 2) {
-          up((NDTask*)D.tasks, Ls[l].tasks, s);
-          up((NDStage*)D.stages, Ls[l].stages, s);
-          up((NDGather*)D.gath, Ls[l].gath, s);
-          up((NDSeg*)D.segs, Ls[l].segs, s);
-          up((NDOut*)D.outs, Ls[l].outs, s);
-          up((int*)D.dst, Ls[l].dst, s);
-        } else if (Ls[l].kind == 3) {
-          up((NDGather*)D.gath, Ls[l].gath, s);
-          up((NDTile*)D.tiles, Ls[l].tiles, s);
-          up((NDRowTile*)D.rtiles, Ls[l].rtiles, s);
-        } else {
-          up((int*)D.task_off, Ls[l].task_off, s);
-          up((NDItem*)D.items, Ls[l].items, s);
-          up((NDGather*)D.gath, Ls[l].gath, s);
-        }
+        up((NDGather*)D.gath, Ls[l].gath, s);
+        up((NDRow*)D.rows, Ls[l].rows, s);
+        up((NDTile*)D.tiles, Ls[l].tiles, s);
+        up((NDRowTile*)D.rtiles, Ls[l].rtiles, s);
       }
     }
     numeric_setup(c.get(), slowness, 0, s);
@@ -1680,10 +1631,9 @@ int helm_get_info(helm_ctx* c, long long* out, int n) {
   long long v[29] = {c->g1.tot, c->g2.tot, c->g3.tot, (long long)P.fronts.size(), P.L_total, P.W_total, sB,
                      c->g3.tot, (long long)nd_kernels(c->nd.launch[0]), (long long)nd_kernels(c->nd.launch[1]),
                      (long long)c->ws_needed, maxF,
-                     (long long)c->csz, c->nd_leaf, c->nd_root, c->tuned ? 1 : 0, (long long)P.cuts.size(),
+                     (long long)c->csz, c->nd_leaf, c->nd_root, c->tuned ? 1 : 0, 0,
                      -1, -1, -1, -1, c->nd_merge, c->K2, c->K3, (long long)c->ndsz,
                      c->box[0], c->box[1], c->box[2], c->box[3]};
-  for (size_t i = 0; i < P.cuts.size() && i < 4; ++i) v[17 + i] = P.cuts[i];
   int m = std::min(n, 29);
   for (int i = 0; i < m; ++i) out[i] = v[i];
   return m;

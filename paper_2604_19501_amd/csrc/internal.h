@@ -220,47 +220,25 @@ struct NDAsm {          // F[row][col] += coef[cidx]
   long long cidx;
 };
 
-struct NDItem {         // one work item of a multi-block launch: rows [r0, r1) of a front
-  int front, r0, r1;
-  int stage;
-  // the front's fields the work item needs (copied, so a work-group reads one record)
-  int nS, nF, nB;
-  int g0;               // forward: the front's gather list (one entry per front row) in the launch's gath
-  int ld, pad;          // leading dimension of the block (ldL forward, ldW backward)
-  long long m_off;      // L_off (forward) or W_off (backward)
-  long long idx_off, inv_off, upd_off;
-};
-
-// Tree-block launches: one work-group walks the fronts of a subtree level by level.
-// Per level ("stage"): gather the fronts' input vectors into LDS, partial matrix-vector
-// products over row blocks of at most 64 rows and k ranges of at most 16 ("segments",
-// one wavefront each), then sum the partials of every row block and write the results
-// ("outputs").  A work-group first copies its task's schedule into LDS; indices inside
-// a task are relative to the task's first gather / segment / output / destination.
-struct NDTask {
-  int st0, st1, g0, g1, s0, s1, o0, o1, d0, d1;
-  int nlu;              // forward: entries of the LDS copy of the task's internal update vectors
+// Substitution launches: one per height and direction, of one of two kinds.
+//   row blocks   items of at most rb rows of a front, each by `waves` wavefronts that split the
+//                columns; the front's vector is gathered into LDS and the rows are finished
+//                in the same launch
+//   split-K      tiles of 256 rows x at most 128 columns write partial products, a second
+//                launch sums them; for heights with large blocks, which one work-group per
+//                row block would not spread over the chip
+struct NDGather {       // an entry of a front's vector: r[rid] (rid >= 0) + its children's updates
+  int rid, u0, u1, u2, u3;   // the first four updates inline (-1: none)
+  int ca, cb;           // the others: cidx[ca .. cb)
   int pad;
 };
-struct NDStage {
-  int g0, g1, s0, s1, o0, o1;
+struct NDRow {
+  long long m_off;      // first entry of the front's block (L forward, W backward)
+  long long idx_off;    // the front's node list
+  long long upd_off;    // its updates
+  int ld, r0, nr, K;    // leading dimension, rows [r0, r0 + nr), columns
+  int nS, g0;           // forward: the front's first entry in the launch's gather list
 };
-struct NDGather {       // vec[slot] = (rid >= 0 ? src[rid] : 0) + upd[u0] + upd[u1] + sum upd[cidx[ca .. cb))
-  int slot, rid, u0, u1, ca, cb;   // u0, u1: -1 none; <= -2 (tree blocks): LDS update entry -u - 2
-};
-struct NDSeg {          // part[pslot + l] = sum_{k0 <= k < k1} M[m_off + k ld + r0 + l] vec[vslot + k], l < nr
-  long long m_off;
-  int ld, r0, nr, k0, k1, vslot, pslot, pad;
-};
-struct NDOut {          // rows [r0, r0 + nr): y = sum of nparts partial blocks of 64; destinations dst[d ..)
-  int r0, nr, vslot, pslot, nparts, d;   // dst >= 0: x index; dst < 0: update index -dst - 1
-  int lu, lu_on;        // lu_on: row r0 + l's update also goes to LDS update entry lu + l
-};
-
-// Split-K launches for heights with large fronts: every front's input vector is gathered
-// once (flat gather list -> gather buffer), tiles of 256 rows x at most 128 columns write
-// partial products (one row per thread, so a column is read in 2 KB runs), and row
-// tiles sum their partials in a fixed order and write x or the update.
 struct NDTile {
   int front, r0, k0, k1;
   int pslot;            // partial sums P[pslot + t], t < 256
@@ -270,23 +248,14 @@ struct NDRowTile {
   int front, r0, nkt, pslot, voff, pad;
 };
 
-struct NDLaunch {       // one kernel launch of a substitution
-  int kind = 1;         // 1: row chunks of big fronts (one work-group per item); 2: tree blocks;
-                        // 3: split-K tiles (gather, tiles, row sums: three kernels)
-  std::vector<int> task_off;   // kind 1: items[task_off[t] ..); kind 2: stages[task_off[t] ..)
-  std::vector<NDItem> items;
-  int max_rows_vec = 0; // kind 1: vector entries per work-group (nF forward, nB backward)
-  std::vector<NDTask> tasks;
-  std::vector<NDStage> stages;
-  std::vector<NDGather> gath;
-  std::vector<NDSeg> segs;
-  std::vector<NDOut> outs;
-  std::vector<int> dst;
-  std::vector<NDTile> tiles;        // kind 3 (with gath: the flat gather list)
+struct NDLaunch {
+  int kind = 1;                     // 1: row blocks, 2: split-K
+  std::vector<NDGather> gath;       // per front one entry per row (forward) or column (backward)
+  std::vector<NDRow> rows;
+  int rb = 16, waves = 1, max_k = 0;   // rows of an item, its waves, most columns
+  std::vector<NDTile> tiles;
   std::vector<NDRowTile> rtiles;
-  long long p_elems = 0;
-  int lds_bytes = 0;    // kind 2: schedule + vectors + partials per work-group
-  int threads = 256;
+  long long p_elems = 0;            // partial products of the tiles
 };
 
 // several right-hand sides substituted by one launch (grid y): strides, in entries,
@@ -297,21 +266,13 @@ struct NDRhs {
   long long vec = 0;     // r and x (N3)
   long long upd = 0;     // update pool
   long long part = 0;    // split-K partial products
-  long long gvec = 0;    // row-chunk launches' global vectors
 };
 
 struct NDLaunchDev {    // device copy of an NDLaunch, as the kernels see it
-  int kind = 1, ntasks = 0, threads = 256, lds_bytes = 0;
-  size_t shm = 0;       // kind 1: dynamic LDS bytes for the gathered vector (0: global fall-back)
-  const int* task_off = nullptr;
-  const NDItem* items = nullptr;
-  const NDTask* tasks = nullptr;
-  const NDStage* stages = nullptr;
+  int kind = 1, nrows = 0, ntiles = 0, nrt = 0;
+  int rb = 16, waves = 1, max_k = 0;
   const NDGather* gath = nullptr;
-  const NDSeg* segs = nullptr;
-  const NDOut* outs = nullptr;
-  const int* dst = nullptr;
-  int ngath = 0, ntiles = 0, nrt = 0;
+  const NDRow* rows = nullptr;
   const NDTile* tiles = nullptr;
   const NDRowTile* rtiles = nullptr;
 };
@@ -329,22 +290,19 @@ struct NDPlan {
   long long L_alloc = 0, W_alloc = 0;   // entries of the padded L and W storage
   int max_nS = 0, max_nB = 0, max_nF = 0;
   std::vector<NDLaunch> fwd, bwd;
-  std::vector<int> cuts;                // heights closing the tree-block launches
 };
 
-// elem_bytes: bytes of a factor entry (cycle precision); lds_bytes: LDS available to a
-// tree block; cuts: heights closing the tree-block launches (empty: chosen by the cost
-// model, {-1}: no tree blocks)
-// splitk_bytes: heights above the tree blocks whose factor blocks hold at least this many
-// bytes (per direction) use split-K launches
-// tree_waves: the most wavefronts of a tree-block work-group (16 = 1024 threads)
+// elem_bytes: bytes of a factor entry
+// splitk_bytes: heights whose factor blocks hold at least this many bytes (per direction) use
+// split-K launches
 // merge_heights: heights of the dissection tree (leaves 0, before any merge) whose fronts are
 // merged into their parents (fewer levels, larger fronts)
 // radius: stencil radius of the coarsest operator (its (2 radius + 1)^dim coefficient planes,
 // plane k of offset d = sum_a (d_a + radius) (2 radius + 1)^a)
-void nd_plan(const Geom& g3, int leaf_max, int rows_chunk, int root_merge, int elem_bytes, int lds_bytes,
-             const std::vector<int>& cuts, long long splitk_bytes, NDPlan& plan, int tree_waves = 16,
+void nd_plan(const Geom& g3, int leaf_max, int root_merge, int elem_bytes, long long splitk_bytes, NDPlan& plan,
              const std::vector<int>& merge_heights = std::vector<int>(), int radius = 1);
-
+// LDS bytes of a row-block work-group for nr right-hand sides
+size_t nd_rows_lds(int rb, int waves, int max_k, int nr, size_t elem_bytes);
+#define ND_ROWS_LDS (128 * 1024)   // the most a row-block work-group may take for one right-hand side
 
 }  // namespace helm

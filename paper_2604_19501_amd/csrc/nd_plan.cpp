@@ -22,7 +22,6 @@
 #include <algorithm>
 #include <cassert>
 #include <cstdio>
-#include <functional>
 #include <map>
 #include <set>
 #include <numeric>
@@ -100,10 +99,13 @@ struct Builder {
 
 }  // namespace
 
-void nd_plan(const Geom& g3, int leaf_max, int rows_chunk, int root_merge, int elem_bytes, int lds_bytes,
-             const std::vector<int>& cuts, long long splitk_bytes, NDPlan& plan, int tree_waves,
+size_t nd_rows_lds(int rb, int waves, int max_k, int nr, size_t elem_bytes) {
+  const size_t ipw = (size_t)std::max(1, 4 / waves);     // items of a work-group (at least 4 waves)
+  return elem_bytes * nr * ipw * ((size_t)max_k + (size_t)waves * rb);
+}
+
+void nd_plan(const Geom& g3, int leaf_max, int root_merge, int elem_bytes, long long splitk_bytes, NDPlan& plan,
              const std::vector<int>& merge_heights, int radius) {
-  tree_waves = std::max(1, std::min(16, tree_waves));
   Builder bd;
   bd.g = g3;
   bd.leaf_max = std::max(leaf_max, 1);
@@ -203,7 +205,7 @@ void nd_plan(const Geom& g3, int leaf_max, int rows_chunk, int root_merge, int e
   plan.max_nS = plan.max_nB = plan.max_nF = 0;
   long long F = 0, L = 0, W = 0, U = 0, P = 0, La = 0, Wa = 0;
   const long long line = std::max(1, 128 / std::max(1, elem_bytes));   // entries per 128 bytes
-  auto pad_ld = [&](long long n) { return (n + line - 1) / line * line; };
+  auto pad_ld = [&](long long n) { return 4 * n <= 3 * line ? n : (n + line - 1) / line * line; };
   auto Bof = [&](int t) -> const std::vector<int>& { return bd.B[oid[t]]; };
   auto posF = [&](int t, int v) -> int {   // position of node v in front t's (S, B) list, -1 if absent
     if (owner[v] == t) return pos_in_S[v];
@@ -317,342 +319,64 @@ void nd_plan(const Geom& g3, int leaf_max, int rows_chunk, int root_merge, int e
   for (int t = 0; t < nf; ++t) plan.by_height[plan.fronts[t].height].push_back(t);
 
   // ---------------- solve schedules ----------------
-  // The lower part of the tree runs as tree-block launches: launch (c, b] gives every
-  // subtree of fronts with height in (c, b] to one work-group, which walks it level by
-  // level (forward ascending, backward descending) with work-group barriers.  Fronts
-  // above the last cut run one multi-block launch per height (rows_chunk rows per
-  // work-group).  The cuts minimise a cost model of launch and level latencies and of
-  // the bandwidth one work-group (tree blocks) or the whole chip (multi-block) can pull.
-  const int H = plan.max_height;
-  const int KS = 16;                                   // k range of one segment of 64 rows
-  auto nparts = [&](int K) { return std::max(1, (K + KS - 1) / KS); };
-  auto al16 = [](long long v) { return (v + 15) / 16 * 16; };
-  // LDS of one front in a stage: work entries (vector + partials) and schedule bytes
-  auto work_entries = [&](const NDFrontDev& f, int dir) -> long long {
-    const int R = dir == 0 ? f.nF : f.nS, K = dir == 0 ? f.nS : f.nB;
-    if (R == 0 || K == 0) return 0;
-    return (long long)(dir == 0 ? f.nF : f.nB) + 64LL * ((R + 63) / 64) * nparts(K);
-  };
-  auto sched_bytes = [&](const NDFrontDev& f, int dir) -> long long {
-    const int R = dir == 0 ? f.nF : f.nS, K = dir == 0 ? f.nS : f.nB;
-    if (R == 0 || K == 0) return 0;
-    const long long rb = (R + 63) / 64;
-    return (long long)sizeof(NDGather) * (dir == 0 ? f.nF : f.nB) + (long long)sizeof(NDSeg) * rb * nparts(K) +
-           (long long)sizeof(NDOut) * rb + 4LL * R + (long long)sizeof(NDStage);
-  };
-  std::vector<double> fbytes(nf);
-  for (int t = 0; t < nf; ++t) {
-    const NDFrontDev& f = plan.fronts[t];
-    fbytes[t] = (double)elem_bytes * ((double)f.nF * f.nS + (double)f.nS * f.nB) + 24.0 * (f.nF + f.nB);
-  }
-  // launch latency, latency of one level of a tree block (gather, products, outputs and
-  // their barriers), bandwidth of one tree-block work-group, of the chip and of one
-  // multi-block work-group; per direction
-  const double a_launch = 3e-6, a_stage = 5e-6, bw_block = 30e9, bw_chip = 4e12, bw_chunk = 40e9;
-  // task root of front t for cut b: its highest ancestor (itself included) of height <= b
-  auto task_root = [&](int t, int b) {
-    while (par[t] >= 0 && plan.fronts[par[t]].height <= b) t = par[t];
-    return t;
-  };
-  // fronts of heights (c, b] grouped by task; empty if some task does not fit in LDS
-  auto group = [&](int c, int b, std::vector<std::vector<int>>& tasks) -> bool {
-    tasks.clear();
-    std::vector<int> rootid(nf, -1);
-    for (int t = 0; t < nf; ++t) {
-      int h = plan.fronts[t].height;
-      if (h <= c || h > b) continue;
-      int r = task_root(t, b);
-      if (rootid[r] < 0) {
-        rootid[r] = (int)tasks.size();
-        tasks.emplace_back();
-      }
-      tasks[rootid[r]].push_back(t);
-    }
-    for (auto& tk : tasks)
-      for (int dir = 0; dir < 2; ++dir) {
-        long long sch = 0, lu = 0;
-        std::vector<long long> work(H + 1, 0);
-        for (int t : tk) {
-          sch += sched_bytes(plan.fronts[t], dir);
-          work[plan.fronts[t].height] += work_entries(plan.fronts[t], dir);
-          if (dir == 0 && par[t] >= 0 && plan.fronts[par[t]].height <= b) lu += plan.fronts[t].nB;
-          if (dir == 0) lu += plan.fronts[t].nF;       // the prefetched right-hand side entries
-          // backward: forwarded x_S of in-task ancestors (bound: every front's), prefetched
-          // x_B and x_S
-          if (dir == 1) lu += 2LL * plan.fronts[t].nS + plan.fronts[t].nB;
-        }
-        long long wmax = *std::max_element(work.begin(), work.end());
-        // (+ the alignment of the LDS areas: up to 15 entries each, and 64 bytes)
-        if (al16(sch) + 6 * 16 + 64 + (wmax + lu + 48) * elem_bytes > lds_bytes) return false;
-      }
-    return !tasks.empty();
-  };
-  auto cost_tree = [&](int c, int b) -> double {       // +inf if a task does not fit
-    std::vector<std::vector<int>> tasks;
-    if (!group(c, b, tasks)) return 1e30;
-    double tot = 2.0 * a_launch;
-    for (int h = c + 1; h <= b; ++h) {
-      double mx = 0.0;
-      bool any = false;
-      for (auto& tk : tasks) {
-        double acc = 0.0;
-        for (int t : tk)
-          if (plan.fronts[t].height == h) {
-            acc += fbytes[t];
-            any = true;
-          }
-        mx = std::max(mx, acc);
-      }
-      if (any) tot += 2.0 * a_stage + mx / bw_block;
-    }
-    return tot;
-  };
-  auto cost_chunks = [&](int h) -> double {
-    double by = 0.0, blocks = 0.0;
-    for (int t : plan.by_height[h]) {
-      by += fbytes[t];
-      blocks += (plan.fronts[t].nF + rows_chunk - 1) / rows_chunk;
-    }
-    if (plan.by_height[h].empty()) return 0.0;
-    return 2.0 * (a_launch + a_stage) + by / std::min(bw_chip, blocks * bw_chunk);
-  };
-  std::vector<int> cut;
-  if (!cuts.empty()) {
-    // requested cuts, ascending, up to the first whose tasks would not fit in LDS
-    std::vector<std::vector<int>> tmp;
-    for (int c : cuts) {
-      if (c < 0 || c > H || (!cut.empty() && c <= cut.back())) continue;
-      if (!group(cut.empty() ? -1 : cut.back(), c, tmp)) break;
-      cut.push_back(c);
-    }
-  } else {
-    // best[b + 1]: cost of tree-block launches covering heights <= b, from[]: its last cut
-    std::vector<double> best(H + 2, 1e30);
-    std::vector<int> from(H + 2, -2);
-    best[0] = 0.0;
-    for (int b = 0; b <= H; ++b)
-      for (int c = -1; c < b; ++c) {
-        if (best[c + 1] >= 1e29) continue;
-        double v = best[c + 1] + cost_tree(c, b);
-        if (v < best[b + 1]) {
-          best[b + 1] = v;
-          from[b + 1] = c;
-        }
-      }
-    std::vector<double> chunks(H + 2, 0.0);        // multi-block launches of heights > e
-    for (int h = H; h >= 0; --h) chunks[h] = chunks[h + 1] + cost_chunks(h);
-    double bestv = 1e30;
-    int beste = -1;
-    for (int e = -1; e <= H; ++e) {
-      double v = best[e + 1] + chunks[e + 1];
-      if (v < bestv) {
-        bestv = v;
-        beste = e;
-      }
-    }
-    for (int e = beste; e >= 0; e = from[e + 1]) cut.push_back(e);
-    std::reverse(cut.begin(), cut.end());
-  }
-  plan.cuts = cut;
-
+  // one launch per height and direction (split-K: two): forward ascending, backward descending
   plan.fwd.clear();
   plan.bwd.clear();
-  // front and S position owning each level-3 node (backward tree tasks forward x in LDS)
-  std::vector<int> node_front(g3.tot, -1), node_pos(g3.tot, -1);
-  for (int t = 0; t < nf; ++t) {
-    const NDFrontDev& f = plan.fronts[t];
-    for (int i = 0; i < f.nS; ++i) {
-      node_front[plan.idx[f.idx_off + i]] = t;
-      node_pos[plan.idx[f.idx_off + i]] = i;
+  // a front's gather list.  Forward: row i reads r at its node (i < nS) and the children's
+  // updates; backward: column j reads x at the boundary node
+  auto add_gather = [&](NDLaunch& L, const NDFrontDev& f, int dir) -> int {
+    const int g0 = (int)L.gath.size();
+    const int* ids = plan.idx.data() + f.idx_off;
+    if (dir == 1) {
+      for (int j = 0; j < f.nB; ++j) L.gath.push_back({ids[f.nS + j], -1, -1, -1, -1, 0, 0, 0});
+      return g0;
     }
-  }
-  std::vector<NDLaunch> bwd_tree;
-  int lo = -1;
-  for (int b : cut) {
-    std::vector<std::vector<int>> tasks;
-    group(lo, b, tasks);
-    NDLaunch fl, bl;
-    fl.kind = bl.kind = 2;
-    fl.threads = bl.threads = 64;
-    for (auto& tk : tasks) {
-      for (int dir = 0; dir < 2; ++dir) {
-        NDLaunch& L = dir == 0 ? fl : bl;
-        NDTask T;
-        T.st0 = (int)L.stages.size();
-        T.g0 = (int)L.gath.size();
-        T.s0 = (int)L.segs.size();
-        T.o0 = (int)L.outs.size();
-        T.d0 = (int)L.dst.size();
-        std::vector<std::vector<int>> byh(b + 1);
-        for (int u : tk) byh[plan.fronts[u].height].push_back(u);
-        long long wmax = 0;
-        // forward: the update vectors of fronts whose parent is in the task are also kept in
-        // LDS (entries lu_off[u] ..), where the parent's gathers read them
-        std::map<int, int> lu_off;
-        int nlu = 0;
-        // (only fronts that have work in this direction write their outputs; the others'
-        // values are read from global memory)
-        if (dir == 0) {
-          for (int u : tk)
-            if (par[u] >= 0 && plan.fronts[par[u]].height <= b && plan.fronts[u].nS > 0 && plan.fronts[u].nB > 0) {
-              lu_off[u] = nlu;
-              nlu += plan.fronts[u].nB;
-            }
-        } else {
-          // backward: the solution x_S of fronts with a descendant in the task is also kept
-          // in LDS (entries lu_off[a] + S position), where the descendants' gathers read it;
-          // a front without a boundary has no backward work (its x_S is final already)
-          std::set<int> inner;
-          for (int u : tk)
-            if (par[u] >= 0 && plan.fronts[par[u]].height <= b) inner.insert(par[u]);
-          for (int a : inner)
-            if (plan.fronts[a].nS > 0 && plan.fronts[a].nB > 0) {
-              lu_off[a] = nlu;
-              nlu += plan.fronts[a].nS;
-            }
-        }
-        // LDS entry of update index q from a child of f, or -1 when that child is outside
-        auto lds_of = [&](const NDFrontDev& f, int q) -> int {
-          for (int k = 0; k < f.nchild; ++k) {
-            const int c = plan.children[f.child_off + k];
-            const NDFrontDev& C = plan.fronts[c];
-            if (q >= C.upd_off && q < C.upd_off + C.nB) {
-              auto it = lu_off.find(c);
-              return it == lu_off.end() ? -1 : it->second + (int)(q - C.upd_off);
-            }
-          }
-          return -1;
-        };
-        for (int step = 0; step <= b - lo - 1; ++step) {
-          const int h = dir == 0 ? lo + 1 + step : b - step;
-          NDStage st{(int)L.gath.size() - T.g0, 0, (int)L.segs.size() - T.s0, 0, (int)L.outs.size() - T.o0, 0};
-          int vs = 0;
-          long long vec_total = 0;
-          for (int u : byh[h]) vec_total += work_entries(plan.fronts[u], dir) > 0
-                                                ? (dir == 0 ? plan.fronts[u].nF : plan.fronts[u].nB) : 0;
-          int ps = (int)vec_total;
-          for (int u : byh[h]) {
-            const NDFrontDev& f = plan.fronts[u];
-            const int R = dir == 0 ? f.nF : f.nS, K = dir == 0 ? f.nS : f.nB;
-            if (R == 0 || K == 0) continue;
-            const int* ids = plan.idx.data() + f.idx_off;
-            if (dir == 0) {
-              for (int i = 0; i < f.nF; ++i) {
-                int ca = plan.cptr[f.inv_off + i], cb = plan.cptr[f.inv_off + i + 1];
-                NDGather g{vs + i, i < f.nS ? ids[i] : -1, -1, -1, 0, 0};
-                auto enc = [&](int q) {
-                  const int l = lds_of(f, q);
-                  return l >= 0 ? -l - 2 : q;
-                };
-                if (ca < cb) g.u0 = enc(plan.cidx[ca++]);
-                if (ca < cb) g.u1 = enc(plan.cidx[ca++]);
-                g.ca = ca;
-                g.cb = cb;
-                L.gath.push_back(g);
-              }
-            } else {
-              for (int j = 0; j < f.nB; ++j) {
-                NDGather g{vs + j, ids[f.nS + j], -1, -1, 0, 0};
-                const int node = ids[f.nS + j];
-                auto it = lu_off.find(node_front[node]);
-                if (it != lu_off.end()) g.u0 = -(it->second + node_pos[node]) - 2;
-                L.gath.push_back(g);
-              }
-            }
-            for (int r0 = 0; r0 < R; r0 += 64) {
-              const int nr = std::min(64, R - r0);
-              // a wavefront covers 64 rows x 16 columns, 32 x 32 or 16 x 64
-              const int kse = nr <= 16 ? 4 * KS : nr <= 32 ? 2 * KS : KS;
-              const int np = std::max(1, (K + kse - 1) / kse);
-              for (int p = 0; p < np; ++p) {
-                NDSeg sg;
-                sg.m_off = dir == 0 ? f.L_off : f.W_off;
-                sg.ld = dir == 0 ? f.ldL : f.ldW;
-                sg.r0 = r0;
-                sg.nr = nr;
-                sg.k0 = p * kse;
-                sg.k1 = std::min(K, (p + 1) * kse);
-                sg.vslot = vs;
-                sg.pslot = ps + 64 * p;
-                sg.pad = 0;
-                L.segs.push_back(sg);
-              }
-              NDOut ob{r0, nr, vs, ps, np, (int)L.dst.size() - T.d0, 0, 0};
-              auto it = lu_off.find(u);
-              if (it != lu_off.end()) {
-                // forward: row i >= nS -> entry lu_off + i - nS; backward: row i -> lu_off + i
-                ob.lu = dir == 0 ? it->second - f.nS + r0 : it->second + r0;
-                ob.lu_on = 1;
-              }
-              L.outs.push_back(ob);
-              for (int i = r0; i < r0 + nr; ++i)
-                L.dst.push_back(dir == 1 || i < f.nS ? ids[i] : -(int)(f.upd_off + i - f.nS) - 1);
-              ps += 64 * np;
-            }
-            vs += dir == 0 ? f.nF : f.nB;
-          }
-          st.g1 = (int)L.gath.size() - T.g0;
-          st.s1 = (int)L.segs.size() - T.s0;
-          st.o1 = (int)L.outs.size() - T.o0;
-          wmax = std::max<long long>(wmax, ps);
-          if (st.s1 > st.s0) L.stages.push_back(st);
-        }
-        T.st1 = (int)L.stages.size();
-        T.g1 = (int)L.gath.size();
-        T.s1 = (int)L.segs.size();
-        T.o1 = (int)L.outs.size();
-        T.d1 = (int)L.dst.size();
-        const long long sch = al16((long long)sizeof(NDStage) * (T.st1 - T.st0)) +
-                              al16((long long)sizeof(NDGather) * (T.g1 - T.g0)) +
-                              al16((long long)sizeof(NDSeg) * (T.s1 - T.s0)) +
-                              al16((long long)sizeof(NDOut) * (T.o1 - T.o0)) + al16(4LL * (T.d1 - T.d0));
-        T.nlu = nlu;
-        T.pad = 0;
-        const long long need = sch +
-                               (wmax + nlu + al16(T.g1 - T.g0) + (dir == 1 ? al16(T.d1 - T.d0) : 0)) * elem_bytes +
-                               64;
-        if (need > lds_bytes) throw std::runtime_error("nd_plan: tree-block task exceeds LDS");
-        if (T.st1 > T.st0) {
-          L.tasks.push_back(T);
-          L.lds_bytes = std::max<int>(L.lds_bytes, (int)need);
-          // wavefronts: one per segment of the widest stage, at most 16
-          const int per = 1;
-          for (int st = T.st0; st < T.st1; ++st) {
-            const int ns = L.stages[st].s1 - L.stages[st].s0;
-            L.threads = std::max(L.threads, 64 * std::min(tree_waves, (ns + per - 1) / per));
-          }
-        }
-      }
+    for (int i = 0; i < f.nF; ++i) {
+      int ca = plan.cptr[f.inv_off + i];
+      const int cb = plan.cptr[f.inv_off + i + 1];
+      NDGather g{i < f.nS ? ids[i] : -1, -1, -1, -1, -1, 0, 0, 0};
+      for (int* u : {&g.u0, &g.u1, &g.u2, &g.u3})
+        if (ca < cb) *u = plan.cidx[ca++];
+      g.ca = ca;
+      g.cb = cb;
+      L.gath.push_back(g);
     }
-    fl.task_off.assign(1, 0);
-    bl.task_off.assign(1, 0);
-    plan.fwd.push_back(fl);
-    bwd_tree.push_back(bl);
-    lo = b;
-  }
-  std::vector<NDLaunch> bwd_high;
+    return g0;
+  };
+  // row blocks: a wave takes 64 rows x 16 columns, 32 x 32 or 16 x 64 at a time.  Wide items
+  // gather a front's vector less often, narrow ones spread long columns over more lanes; an
+  // item has enough waves (up to 16) for one pass.
+  auto build_rows = [&](NDLaunch& L, int h, int dir) {
+    L.kind = 1;
+    int K = 0, Rm = 0;
+    for (int t : plan.by_height[h]) {
+      const NDFrontDev& f = plan.fronts[t];
+      K = std::max(K, dir == 0 ? f.nS : f.nB);
+      Rm = std::max(Rm, dir == 0 ? f.nF : f.nS);
+    }
+    L.rb = K <= 64 ? 64 : K <= 256 ? 32 : 16;
+    while (L.rb > 16 && L.rb >= 2 * Rm) L.rb /= 2;
+    L.waves = 1;
+    while (L.waves < 16 && L.waves * 16 * (64 / L.rb) < K) L.waves *= 2;
+    L.max_k = K;
+    for (int t : plan.by_height[h]) {
+      const NDFrontDev& f = plan.fronts[t];
+      const int R = dir == 0 ? f.nF : f.nS, k = dir == 0 ? f.nS : f.nB;
+      if (R == 0 || k == 0) continue;      // (a front without a boundary: nothing backward)
+      const int g0 = dir == 0 ? add_gather(L, f, 0) : 0;
+      for (int r = 0; r < R; r += L.rb)
+        L.rows.push_back({dir == 0 ? f.L_off : f.W_off, f.idx_off, f.upd_off, dir == 0 ? f.ldL : f.ldW, r,
+                          std::min(L.rb, R - r), k, f.nS, g0});
+    }
+  };
   const int KT = 128;                                  // columns of a split-K tile
   auto build_splitk = [&](NDLaunch& L, int h, int dir) {
-    L.kind = 3;
+    L.kind = 2;
     for (int t : plan.by_height[h]) {
       const NDFrontDev& f = plan.fronts[t];
       const int R = dir == 0 ? f.nF : f.nS, K = dir == 0 ? f.nS : f.nB;
       if (R == 0 || K == 0) continue;
-      const int* ids = plan.idx.data() + f.idx_off;
-      const int voff = (int)L.gath.size();
-      if (dir == 0) {
-        for (int i = 0; i < f.nF; ++i) {
-          int ca = plan.cptr[f.inv_off + i], cb = plan.cptr[f.inv_off + i + 1];
-          NDGather g{voff + i, i < f.nS ? ids[i] : -1, -1, -1, 0, 0};
-          if (ca < cb) g.u0 = plan.cidx[ca++];
-          if (ca < cb) g.u1 = plan.cidx[ca++];
-          g.ca = ca;
-          g.cb = cb;
-          L.gath.push_back(g);
-        }
-      } else {
-        for (int j = 0; j < f.nB; ++j) L.gath.push_back({voff + j, ids[f.nS + j], -1, -1, 0, 0});
-      }
+      const int voff = add_gather(L, f, dir);
       const int nkt = (K + KT - 1) / KT;
       for (int r0 = 0; r0 < R; r0 += 256) {
         const int ps0 = (int)L.p_elems;
@@ -664,64 +388,28 @@ void nd_plan(const Geom& g3, int leaf_max, int rows_chunk, int root_merge, int e
       }
     }
   };
-  for (int h = lo + 1; h <= plan.max_height; ++h) {
-    NDLaunch fl, bl;
-    fl.kind = bl.kind = 1;
-    fl.task_off.push_back(0);
-    bl.task_off.push_back(0);
-    long long bf = 0, bb = 0;
-    for (int t : plan.by_height[h]) {
-      bf += (long long)plan.fronts[t].nF * plan.fronts[t].nS * elem_bytes;
-      bb += (long long)plan.fronts[t].nS * plan.fronts[t].nB * elem_bytes;
-    }
-    if (bf >= splitk_bytes) {
-      build_splitk(fl, h, 0);
-    } else {
+  std::vector<NDLaunch> bwd;
+  for (int h = 0; h <= plan.max_height; ++h) {
+    for (int dir = 0; dir < 2; ++dir) {
+      long long bytes = 0;
+      int K = 0;
       for (int t : plan.by_height[h]) {
         const NDFrontDev& f = plan.fronts[t];
-        // the front's gather list: row i reads r at its node (i < nS) and the children's
-        // updates, the first two inline
-        const int g0 = (int)fl.gath.size();
-        const int* ids = plan.idx.data() + f.idx_off;
-        for (int i = 0; i < f.nF; ++i) {
-          int ca = plan.cptr[f.inv_off + i];
-          const int cb = plan.cptr[f.inv_off + i + 1];
-          NDGather g{i, i < f.nS ? ids[i] : -1, -1, -1, 0, 0};
-          if (ca < cb) g.u0 = plan.cidx[ca++];
-          if (ca < cb) g.u1 = plan.cidx[ca++];
-          g.ca = ca;
-          g.cb = cb;
-          fl.gath.push_back(g);
-        }
-        for (int r = 0; r < f.nF; r += rows_chunk) {
-          fl.items.push_back({t, r, std::min(f.nF, r + rows_chunk), h, f.nS, f.nF, f.nB, g0, f.ldL, 0, f.L_off, f.idx_off,
-                              f.inv_off, f.upd_off});
-          fl.task_off.push_back((int)fl.items.size());
-        }
-        fl.max_rows_vec = std::max(fl.max_rows_vec, f.nF);
+        bytes += (long long)(dir == 0 ? f.nF : f.nB) * f.nS * elem_bytes;
+        K = std::max(K, dir == 0 ? f.nS : f.nB);
       }
+      if (bytes == 0) continue;
+      NDLaunch L;
+      // a vector too long for a row block's LDS takes split-K tiles whatever the size
+      const bool fits = nd_rows_lds(64, 16, K, 1, elem_bytes) <= ND_ROWS_LDS;
+      if (bytes >= splitk_bytes || !fits)
+        build_splitk(L, h, dir);
+      else
+        build_rows(L, h, dir);
+      (dir == 0 ? plan.fwd : bwd).push_back(L);
     }
-    if (bb >= splitk_bytes && bb > 0) {
-      build_splitk(bl, h, 1);
-    } else {
-      for (int t : plan.by_height[h]) {
-        const NDFrontDev& f = plan.fronts[t];
-        if (f.nB > 0)          // a front without boundary has nothing to back-substitute
-          for (int r = 0; r < f.nS; r += rows_chunk) {
-            bl.items.push_back({t, r, std::min(f.nS, r + rows_chunk), h, f.nS, f.nF, f.nB, 0, f.ldW, 0, f.W_off, f.idx_off,
-                                f.inv_off, f.upd_off});
-            bl.task_off.push_back((int)bl.items.size());
-          }
-        bl.max_rows_vec = std::max(bl.max_rows_vec, f.nB);
-      }
-    }
-    plan.fwd.push_back(fl);
-    if (!bl.items.empty() || !bl.tiles.empty()) bwd_high.push_back(bl);
   }
-  std::vector<NDLaunch> bwd_all(bwd_high.rbegin(), bwd_high.rend());
-  for (auto it = bwd_tree.rbegin(); it != bwd_tree.rend(); ++it)
-    if (!it->tasks.empty()) bwd_all.push_back(*it);
-  plan.bwd = bwd_all;
+  plan.bwd.assign(bwd.rbegin(), bwd.rend());
 }
 
 

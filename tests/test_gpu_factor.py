@@ -1,9 +1,10 @@
 """The coarsest level's factorisation at the edges of its panels, blocks and windows, against
-the oracle's sparse LU through helm_coarse_solve."""
+the oracle's sparse LU through helm_coarse_solve, and its substitution for several
+right-hand sides."""
 import numpy as np
 import pytest
 
-from tests.gpu_helpers import oracle_hierarchy, rel
+from tests.gpu_helpers import oracle_hierarchy, rect_problem, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +51,30 @@ def test_factorisation_panels_blocks_windows(monkeypatch, name, win, block, bloc
             ec = rel(s.coarse_solve(r, op=HELM_OP_C).cpu().numpy(), np.conj(H.lu3.solve(np.conj(r))))
             assert ec < tol, (prec, ec)
         s.close()
+
+
+@pytest.mark.parametrize("n,leaf,merge", [((128, 96), 8, "none"), ((128, 96), 64, "1,2,4,5"), ((192, 192), 32, "1,3,5"),
+                                          ((40, 32, 24), 8, "none"), ((48, 48, 40), 64, "1,3")])
+@pytest.mark.parametrize("splitk", [0, 1 << 30])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_substitution_shares_entries_over_right_hand_sides(monkeypatch, n, leaf, merge, splitk, prec):
+    """1 to 9 right-hand sides in one lock-step group (1, 2, 4 or 8 of them share a launch's
+    matrix entries): every solution equals the separate solve's bit for bit, with row-block
+    items of 16, 32 and 64 rows, one to several waves, and split-K tiles."""
+    import torch
+    monkeypatch.setenv("HELM_ND_LEAF", str(leaf))
+    monkeypatch.setenv("HELM_ND_MERGE", merge)
+    monkeypatch.setenv("HELM_ND_SPLITK_KB", str(splitk))
+    p = rect_problem(n)
+    print("shared entries", n, leaf, merge, splitk, prec, flush=True)
+    rng = np.random.default_rng(8)
+    qs = [rng.standard_normal(p.N) + 1j * rng.standard_normal(p.N) for _ in range(9)]
+    one = from_problem(p, nu=(1, 1), cycle_prec=prec)
+    ref = [one.solve(q, tol=1e-300, max_iter=3, op=HELM_OP_C)[0] for q in qs]
+    many = from_problem(p, nu=(1, 1), cycle_prec=prec, max_rhs=9)
+    for nr in (1, 2, 3, 5, 9):
+        xs, _ = many.solve_many(qs[:nr], tol=1e-300, max_iter=3, op=HELM_OP_C)
+        for k in range(nr):
+            assert torch.equal(xs[k], ref[k]), (nr, k)
+    one.close()
+    many.close()
