@@ -176,7 +176,7 @@ struct helm_ctx {
   char* hstate = nullptr;    // pinned host copy of the scalar blocks of the states (slot 0),
                              // slots 1, 2: read-backs of alternate queued iterations
   char* hstate_dev = nullptr;   // its device mapping
-  hipEvent_t itev[2] = {nullptr, nullptr};   // completion of the queued iterations
+  int packs = 0;                // read-backs queued so far (every state's seq once they are done)
   int timing = 0;
   double times[5] = {0, 0, 0, 0, 0};
   double kt_ms[KT_N] = {0};
@@ -203,7 +203,11 @@ struct helm_ctx {
   std::vector<hipGraphExec_t> gexec[2];
   double gtol[2] = {-1.0, -1.0};
   int gnr[2] = {0, 0};          // right-hand side count the graphs were captured for
-  int graphs = 1;
+  // iterations as captured graphs (1), as plain launches (0; HELM_GRAPHS forces either), or
+  // plain until the host is seen to be the slower side (-1): late_win counts the iterations of
+  // a window, late those whose read-back had come before the host had queued the next one
+  int graphs = -1;
+  int late = 0, late_win = 0;
   double arnoldi_guard = 1e-8;  // relative size of ||w - V c||^2 below which an Arnoldi column ends the cycle
 };
 
@@ -963,24 +967,39 @@ struct Cycle {
 // the scalar block of KrylovState, as read back by the host
 struct HostScalars {
   double bnorm, beta0, est, hnext, true_rel;
-  int its, done, final, nonfinite, kcols, maxit;
+  int its, done, final, nonfinite, kcols, maxit, seq, pad;
 };
 static_assert(sizeof(HostScalars) == offsetof(KrylovState, hist) - offsetof(KrylovState, bnorm),
               "HostScalars must mirror the scalar block of KrylovState");
-constexpr size_t HSLOT = 1024;   // bytes between the slots of hstate (16 right-hand sides)
-constexpr int RMAX = (int)(HSLOT / sizeof(HostScalars));
+constexpr int RMAX = 16;                                // right-hand sides of a lock-step group, at most
+constexpr size_t HSLOT = 2048;                          // bytes between the slots of hstate
+static_assert(RMAX * sizeof(HostScalars) <= HSLOT, "a slot holds every right-hand side");
 inline HostScalars* hs(helm_ctx* c, int slot = 0) { return (HostScalars*)(c->hstate + HSLOT * slot); }
-// the scalar blocks of the nr states into slot `slot` of hstate (asynchronous: one small
-// kernel writes them into the pinned buffer through its device mapping)
-void read_states_async(helm_ctx* c, int slot, hipStream_t s) {
+// wait until read-back number `want` of every state is in slot `slot`.  The device stores its
+// count last (pack_state), so the host needs no event and no stream synchronisation; now and
+// then it asks the stream, so that a failed launch ends the wait.
+void wait_states(helm_ctx* c, int slot, int want, hipStream_t s) {
+  for (int r = 0; r < c->nr; ++r) {
+    const volatile int* seq = &hs(c, slot)[r].seq;
+    for (long spin = 1; *seq - want < 0; ++spin) {
+      if (spin % 64 == 0) std::this_thread::yield();
+      if (spin % (1 << 16)) continue;
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipErrorNotReady) continue;
+      CK(e);
+      if (*seq - want < 0) throw DevErr("state read-back: the stream ended without it");
+    }
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+}
+// the scalar blocks of the nr states into slot 0 of hstate (one small kernel writes them into
+// the pinned buffer through its device mapping)
+void read_states(helm_ctx* c, hipStream_t s) {
   KrylovArgs a;
   a.st = c->st;
   a.nrhs = c->nr;
-  kr_pack_states(a, c->hstate_dev + HSLOT * slot, s);
-}
-void read_states(helm_ctx* c, hipStream_t s) {
-  read_states_async(c, 0, s);
-  CK(hipStreamSynchronize(s));
+  kr_pack_states(a, c->hstate_dev, s);
+  wait_states(c, 0, ++c->packs, s);
 }
 
 KrylovArgs make_kargs(helm_ctx* c, int op) {
@@ -1070,9 +1089,14 @@ int solve_impl(helm_ctx* c, int op, int nr, const cd* b, cd* x, double tol, int 
     CK(hipEventCreate(&e1));
     CK(hipEventRecord(e0, s));
   }
-  const bool use_graphs = c->graphs && !c->timing;
+  // Plain launches leave no gap between iterations; a graph's boundary costs 5 to 12 us of idle
+  // device (per FGMRES iteration, graphs / plain: 1024^2 264 / 252 us, 600x640 FP64 177 / 169,
+  // 256^2 107 / 102) and its capture 0.7 to 5 ms of a context's first solve.  Where launches are
+  // what the device waits for (128^2 with (2,2) sweeps: 111 / 117) the context goes over to
+  // graphs once half of a window of 64 iterations came late.
+  const bool use_graphs = c->graphs > 0 && !c->timing;
   if (use_graphs) iter_graphs<R>(c, op, tol);
-  kr_init(a, max_iter, s);
+  kr_init(a, max_iter, c->packs, s);
   kr_residual(a, x, b, 1, s);
   read_states(c, s);
   std::vector<int> status(nr, HELM_OK), its(nr, 0), restarts(nr, 0), kc(nr, 0);
@@ -1107,33 +1131,47 @@ int solve_impl(helm_ctx* c, int op, int nr, const cd* b, cd* x, double tol, int 
   };
   while (active()) {
     kr_scale_v0(a, s);
-    if (use_graphs) {
+    if (!c->timing) {
       // iteration q + 1 is queued before the states of iteration q are read back, so the
       // device does not wait for the host between iterations.  An iteration queued after
       // a right-hand side's last one finds its done flag set: its Krylov kernels return at
       // once and leave its basis, Hessenberg column and counters as they are.
       auto queue = [&](int j) {
-        CK(hipGraphLaunch(c->gexec[op][j], s));
-        // (the graph ends with the read-back of its states into slot 1 + (j & 1))
-        CK(hipEventRecord(c->itev[j & 1], s));
+        // (the iteration ends with the read-back of its states into slot 1 + (j & 1))
+        if (use_graphs) {
+          CK(hipGraphLaunch(c->gexec[op][j], s));
+        } else {
+          cyc.template run<C>(c->V + j * NJ, (C*)c->Z + j * NJ);
+          kr_arnoldi(a, (const char*)c->Z + j * NJ * c->csz, c->f32, j, tol, c->hstate_dev + HSLOT * (1 + (j & 1)),
+                     c->tail_fused, s);
+        }
+        ++c->packs;
       };
-      for (hipEvent_t& e : c->itev)
-        if (!e) CK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+      const int base = c->packs;
       int q = 0, k = 0;          // iterations of this cycle queued, read
       queue(q++);
       while (k < q) {
         if (q < m) queue(q++);
-        CK(hipEventSynchronize(c->itev[k & 1]));
+        if (c->graphs < 0 && k + 1 < q) {
+          // (state 0's read-back: already there means that the device waits for the host)
+          if (*(const volatile int*)&hs(c, 1 + (k & 1))[0].seq - (base + k + 1) >= 0) ++c->late;
+          if (++c->late_win == 64) {
+            if (c->late >= 32) c->graphs = 1;        // from the next solve on
+            c->late = c->late_win = 0;
+          }
+        }
+        wait_states(c, 1 + (k & 1), base + k + 1, s);
         std::memcpy(hs(c), hs(c, 1 + (k & 1)), sizeof(HostScalars) * nr);
         ++k;
         if (all_done(hs(c))) break;
       }
     } else {
       for (int j = 0; j < m; ++j) {
-        if (c->timing) kr_hold(150, s);     // the iteration's launches are queued before they run
+        kr_hold(150, s);     // the iteration's launches are queued before they run
         cyc.template run<C>(c->V + j * NJ, (C*)c->Z + j * NJ);
         TIMED(c, KT_APPLY_DOT, s, kr_arnoldi(a, (const char*)c->Z + j * NJ * c->csz, c->f32, j, tol,
                                              c->hstate_dev, c->tail_fused, s));
+        ++c->packs;
         CK(hipStreamSynchronize(s));
         if (all_done(hs(c))) break;
       }
@@ -1226,7 +1264,7 @@ int stationary_impl(helm_ctx* c, int op, const cd* b, cd* x, double tol, int max
   KrylovArgs a = make_kargs(c, op);
   Cycle<R> cyc(c, op, s);
   const long long N = c->g1.tot;
-  kr_init(a, max_iter, s);
+  kr_init(a, max_iter, c->packs, s);
   kr_residual(a, x, b, 1, s);         // V_0 = b - op(H) x, ||b||, ||V_0||
   read_states(c, s);
   const double bnorm = hs(c)->bnorm;
@@ -1331,7 +1369,7 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
     c->shift = *shift;
     c->omega = omega;
     c->rcap = rcap;
-    c->graphs = env_int("HELM_GRAPHS", 1);
+    c->graphs = env_int("HELM_GRAPHS", -1);
     c->l2_chain = env_int("HELM_L2_CHAIN", 1);
     // HELM_ARNOLDI_GUARD (tests): the cancellation threshold of the Arnoldi norm formula
     if (const char* g = getenv("HELM_ARNOLDI_GUARD")) c->arnoldi_guard = atof(g);
@@ -1341,7 +1379,8 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
     if (ws_bytes < need) return fail(HELM_EWORKSPACE, "workspace too small: %zu < %zu", ws_bytes, need);
     c->ws_needed = need;
     carve(c.get(), ws);
-    CK(hipHostMalloc((void**)&c->hstate, 4096, hipHostMallocMapped | hipHostMallocCoherent));
+    CK(hipHostMalloc((void**)&c->hstate, 3 * HSLOT, hipHostMallocMapped | hipHostMallocCoherent));
+    std::memset(c->hstate, 0, 3 * HSLOT);
     CK(hipHostGetDevicePointer((void**)&c->hstate_dev, c->hstate, 0));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     CK(hipEventCreate(&e0));
@@ -1447,8 +1486,6 @@ int helm_destroy(helm_ctx* ctx) {
   if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
   for (hipStream_t t : ctx->bstreams) (void)hipStreamDestroy(t);
   if (ctx->hstate) (void)hipHostFree(ctx->hstate);
-  for (hipEvent_t e : ctx->itev)
-    if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : ctx->evpool) (void)hipEventDestroy(e);
   delete ctx;
   return HELM_OK;

@@ -24,6 +24,9 @@ struct KrylovState {
   int nonfinite;
   int kcols;          // Arnoldi columns completed in the current cycle
   int maxit;          // iteration limit (the column that reaches it ends the solve)
+  int seq;            // read-backs of this state so far (the last word of the host's copy, stored
+                      // behind the others: a copy is complete once its seq has come)
+  int pad;
   double hist[KMAXIT];
   cd G[(KMAXM + 1) * (KMAXM + 1)];   // Gram matrix of the stored basis, leading dimension KMAXM + 1
   int ticket;         // blocks of the current final-sum launch that have stored their sum
@@ -48,7 +51,8 @@ struct KrylovArgs {
   double guard;        // ||w - V c||^2 below guard ||w||^2 ends the restart cycle (cancellation)
 };
 
-void kr_init(const KrylovArgs& a, int max_iter, hipStream_t s);
+// seq: the read-back count to continue from
+void kr_init(const KrylovArgs& a, int max_iter, int seq, hipStream_t s);
 void kr_residual(const KrylovArgs& a, const cd* x, const cd* b, int with_b, hipStream_t s);
 void kr_scale_v0(const KrylovArgs& a, hipStream_t s);
 // pack_dst: host-mapped slot that receives the scalar blocks of the states after the

@@ -241,11 +241,25 @@ __device__ inline void givens(cd a, cd b, double& c, cd& s, cd& r) {
   r = t * ph;
 }
 
-// the scalar block (bnorm .. hist) of state r into slot r of the host-mapped dst
-__device__ __forceinline__ void pack_state(const KrylovState* st, char* dst, int r) {
+// the scalar block (bnorm .. hist) of state r into slot r of the host-mapped dst, by the
+// block's first wavefront: one store of the words by as many lanes, and once it has reached
+// memory the read-back count behind them.  The host polls that word, so that no event stands
+// between two iterations (recorded behind every graph of 20 short kernels an event left the
+// device idle for 4.5 us more).
+__device__ __forceinline__ void pack_state(KrylovState* st, char* dst, int r) {
   constexpr int W = (int)((offsetof(KrylovState, hist) - offsetof(KrylovState, bnorm)) / 4);
+  constexpr int S = (int)((offsetof(KrylovState, seq) - offsetof(KrylovState, bnorm)) / 4);
+  static_assert(S < 64, "one word per lane");
+  if (threadIdx.x >= 64) return;
   const int* src = (const int*)((const char*)st + offsetof(KrylovState, bnorm));
-  for (int q = threadIdx.x; q < W; q += blockDim.x) ((int*)dst)[r * W + q] = src[q];
+  int* out = (int*)dst + r * W;
+  if (threadIdx.x < S) __hip_atomic_store(out + threadIdx.x, src[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (threadIdx.x == 0) {
+    const int n = st->seq + 1;
+    st->seq = n;
+    __hip_atomic_store(out + S, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 static_assert(KMAXM <= 64, "one lane per row of the Arnoldi column");
@@ -444,8 +458,7 @@ __global__ void __launch_bounds__(256) k_fin_givens(KrylovArgs a, int j, double 
 // level-2 coefficients).
 // With pack_dst, the first block of each right-hand side also packs its state (final after
 // the column's finish) into the host-mapped slot, so that the stores to host memory drain
-// while this pass streams instead of delaying it; the host reads the slot after an event
-// recorded behind the launch, whose completion makes them visible (no fence of system scope).
+// while this pass streams instead of delaying it.
 template <typename CZ, int CMP>
 __global__ void __launch_bounds__(256) k_arnoldi_update(KrylovArgs a, const CZ* __restrict__ z, int j,
                                                         char* pack_dst) {
@@ -562,7 +575,7 @@ __global__ void k_zero_c128(cd* __restrict__ x, long long n) {
     x[i] = mk(0.0, 0.0);
 }
 
-__global__ void k_init_state(KrylovState* st, int maxit) {
+__global__ void k_init_state(KrylovState* st, int maxit, int seq) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     st += blockIdx.y;
     st->its = 0;
@@ -571,16 +584,14 @@ __global__ void k_init_state(KrylovState* st, int maxit) {
     st->final = 0;
     st->kcols = 0;
     st->maxit = maxit;
+    st->seq = seq;
     st->ticket = 0;
   }
 }
 
-// the scalar blocks (bnorm .. hist) of the nrhs states, packed one after the other into
-// host-visible memory (pinned, written through), for the host to read after an event
-// (the host reads dst after synchronising with the stream or an event behind this launch,
-// which makes the stores visible: no fence of system scope)
-__global__ void k_pack_states(const KrylovState* st, char* dst, int nrhs) {
-  for (int r = 0; r < nrhs; ++r) pack_state(st + r, dst, r);
+// the scalar blocks of the nrhs states (one block each) into host-visible memory
+__global__ void __launch_bounds__(64) k_pack_states(KrylovState* st, char* dst) {
+  pack_state(st + blockIdx.x, dst, blockIdx.x);
 }
 
 // right-hand sides in mask: finished, done from now on
@@ -601,13 +612,13 @@ __global__ void k_hold(int rounds) {
 // ------------------------------------------------------------- launchers ----
 void kr_hold(int rounds, hipStream_t s) { hipLaunchKernelGGL(k_hold, dim3(1), dim3(64), 0, s, rounds); }
 void kr_pack_states(const KrylovArgs& a, void* host_dst, hipStream_t s) {
-  hipLaunchKernelGGL(k_pack_states, dim3(1), dim3(256), 0, s, a.st, (char*)host_dst, a.nrhs);
+  hipLaunchKernelGGL(k_pack_states, dim3(a.nrhs), dim3(64), 0, s, a.st, (char*)host_dst);
 }
 void kr_finalize(const KrylovArgs& a, unsigned mask, hipStream_t s) {
   hipLaunchKernelGGL(k_finalize, dim3(1, a.nrhs), dim3(1), 0, s, a.st, mask);
 }
-void kr_init(const KrylovArgs& a, int max_iter, hipStream_t s) {
-  hipLaunchKernelGGL(k_init_state, dim3(1, a.nrhs), dim3(1), 0, s, a.st, max_iter);
+void kr_init(const KrylovArgs& a, int max_iter, int seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_init_state, dim3(1, a.nrhs), dim3(1), 0, s, a.st, max_iter, seq);
 }
 void kr_residual(const KrylovArgs& a, const cd* x, const cd* b, int with_b, hipStream_t s) {
   if (a.op.compact)
