@@ -73,17 +73,32 @@ __device__ __forceinline__ int flat(const Geom& g, int i0, int i1, int i2) {
 //   and, 3D FP32 only, z-marching tiles (below): sweeps 4 and 5, restrictions 3 and 4
 //   (in 2D these variants run variant 0).
 // The FP64 cycle keeps variant 0 in 3D (the others exceed the block's LDS).
+//
+// Variant 0 on a small grid: with the default boxes a level of a few ten thousand nodes is
+// fewer blocks than the chip has CUs, and a block's chain of load, barrier, passes over its
+// halo and sums is then the whole time of a launch.  Boxes of one node per thread (sweeps
+// 2D 16 x 16, 3D 16 x 4 x 4) and of a quarter of the coarse nodes (restrictions 2D 8 x 8,
+// 3D 4 x 4 x 2) cut the chain and fill four times as many CUs; their halos cost more
+// traffic, so they end where the default boxes give each CU two blocks (small_grid).
+// Cycle in us, default / small boxes: 32^3 FP64 128 / 88, 64^3 182 / 135, 64^3 FP32
+// 170 / 120, 96^3 331 / 319, 128^3 (level 2 only) 651 / 627; 2D nu = (2, 2) 128^2 FP32
+// 80 / 72, 256^2 FP64 96 / 84.  Where the line lies: 64^3 and 128^3 FP64 gain up to 460
+// boxes (139 / 135 us, 651 / 627); 80^3 with its 690 on the small ones 188 / 189 us, 112^3
+// with its 2000 452 / 461.
+constexpr int SMALL_S = 6, SMALL_R = 5;      // their variant numbers (not selectable)
+constexpr int SMALL_GRID_BLOCKS = 512;
 template <int DIM, int V> struct SBox {
-  static constexpr int x = DIM == 2 ? (V == 0 || V == 3 ? 32 : 64) : (V == 2 ? 64 : 32);
-  static constexpr int y = DIM == 2 ? (V == 0 ? 16 : V == 1 ? 8 : V == 2 ? 16 : 32) : (V == 3 ? 16 : 8);
+  static constexpr int x = V == SMALL_S ? 16 : DIM == 2 ? (V == 0 || V == 3 ? 32 : 64) : (V == 2 ? 64 : 32);
+  static constexpr int y = V == SMALL_S ? (DIM == 2 ? 16 : 4)
+                           : DIM == 2   ? (V == 0 ? 16 : V == 1 ? 8 : V == 2 ? 16 : 32)
+                                        : (V == 3 ? 16 : 8);
   static constexpr int z = DIM == 2 ? 1 : (V == 1 ? 8 : 4);
 };
 template <int DIM, int V> struct RBox {
-  static constexpr int x = DIM == 2 ? (V == 1 ? 32 : 16) : (V == 1 ? 16 : 8);
-  static constexpr int y = DIM == 2 ? (V == 2 ? 16 : 8) : (V == 2 ? 8 : 4);
-  static constexpr int z = DIM == 2 ? 1 : 4;
+  static constexpr int x = V == SMALL_R ? (DIM == 2 ? 8 : 4) : DIM == 2 ? (V == 1 ? 32 : 16) : (V == 1 ? 16 : 8);
+  static constexpr int y = V == SMALL_R ? (DIM == 2 ? 8 : 4) : DIM == 2 ? (V == 2 ? 16 : 8) : (V == 2 ? 8 : 4);
+  static constexpr int z = DIM == 2 ? 1 : V == SMALL_R ? 2 : 4;
 };
-constexpr int N_SBOX = 6, N_RBOX = 5;
 // z-marching tiles: an xy tile of output nodes over z consecutive planes
 //   sweeps       30 x 14 nodes, 16 (variant 4) or 4 (variant 5) planes
 //   restrictions 14 x 6 coarse nodes, 8 (variant 3) or 4 (variant 4) coarse planes
@@ -1095,6 +1110,14 @@ void sweep_z(const Op& op, int xin, const typename Op::C* x, const CB* b, typena
 #undef SW
 }
 
+// variant 0 takes the small boxes while the default ones (Box, over the grid g they tile)
+// are fewer than SMALL_GRID_BLOCKS, whatever the number of right-hand sides: a lock-step
+// solve rounds as its single solves do
+template <class Box>
+bool small_grid(const Geom& g, int box) {
+  return box == 0 && tiles(g, Box::x, Box::y, Box::z).ntiles < SMALL_GRID_BLOCKS;
+}
+
 template <int DIM, class Op, typename CB, typename CO>
 void sweep_dim(const Op& op, int xin, const typename Op::C* x, const CB* b, typename Op::Real w_in,
                const Geom& gc, const typename Op::C* e, typename Op::Real w, CO* out, int nrhs, hipStream_t s) {
@@ -1102,7 +1125,9 @@ void sweep_dim(const Op& op, int xin, const typename Op::C* x, const CB* b, type
   // the z-marching variants are 3D (variant 0 in 2D), and a sweep from nothing (xin 0,
   // which materialises zero) keeps the box kernel
   const int v = (DIM == 3 && sizeof(typename Op::C) == 16) ? 0 : op.A.box_sweep;
-  if constexpr (DIM == 3 && sizeof(typename Op::C) == 16) {
+  if (op.A.small_sweep && small_grid<SBox<DIM, 0>>(op.geom(), op.A.box_sweep)) {
+    sweep_box<DIM, Op, CB, CO, SMALL_S>(op, xin, x, b, w_in, gc, e, w, out, nrhs, s);
+  } else if constexpr (DIM == 3 && sizeof(typename Op::C) == 16) {
     sweep_box<DIM, Op, CB, CO, 0>(op, xin, x, b, w_in, gc, e, w, out, nrhs, s);
   } else if constexpr (DIM == 3) {
     switch (xin == 0 ? 0 : v) {
@@ -1152,7 +1177,9 @@ void restrict_z(const Op& op, int xin, const typename Op::C* x, const CB* b, typ
 template <int DIM, class Op, typename CB>
 void restrict_dim(const Op& op, int xin, const typename Op::C* x, const CB* b, typename Op::Real w_in,
                   const Geom& g2, typename Op::C* b2, int nrhs, hipStream_t s) {
-  if constexpr (DIM == 3 && sizeof(typename Op::C) == 16) {
+  if (op.A.small_restrict && small_grid<RBox<DIM, 0>>(g2, op.A.box_restrict)) {
+    restrict_box<DIM, Op, CB, SMALL_R>(op, xin, x, b, w_in, g2, b2, nrhs, s);
+  } else if constexpr (DIM == 3 && sizeof(typename Op::C) == 16) {
     restrict_box<DIM, Op, CB, 0>(op, xin, x, b, w_in, g2, b2, nrhs, s);
   } else if constexpr (DIM == 3) {
     // the z-marching variants take an iterate (xin X or Z); restricting b alone keeps the

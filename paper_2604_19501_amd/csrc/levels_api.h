@@ -35,6 +35,7 @@ struct L1 {
   const C* dg = nullptr;   // the FP32 cycle: its diagonal precomputed at set-up (of the
                            // operator, not of its conjugate), read instead of m
   int box_sweep = 0, box_restrict = 0;   // box-shape variants of the tiled kernels
+  int small_sweep = 1, small_restrict = 1;   // variant 0 may take the small boxes
   // the coefficient and the diagonal from the node's squared slowness mm = m[f]
   __device__ __forceinline__ C coef_m(R mm, int i0, int i1, int i2) const {
     R sig = layer_sigma_r<R>(op, i0, i1, i2);
@@ -60,6 +61,7 @@ struct L2 {
                      // 13 directions after it
   int conj;          // use conj(coef) (adjoint)
   int box_sweep = 0, box_restrict = 0;   // box-shape variants of the tiled kernels
+  int small_sweep = 1, small_restrict = 1;   // variant 0 may take the small boxes
   __device__ __forceinline__ C get(int k, long long i) const {
     C c = coef[(long long)k * g.tot + i];
     if (conj) c.y = -c.y;
