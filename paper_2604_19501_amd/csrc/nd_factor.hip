@@ -36,6 +36,7 @@
 // window, Q'[i, K] = Q0[i, K] Q'[pm[K], K] (k_inv_outer).
 #include <algorithm>
 #include <stdexcept>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -124,12 +125,31 @@ __device__ __forceinline__ cd csubmul(cd a, cd b, cd c) {
   return mk(fma(b.y, c.y, fma(-b.x, c.x, a.x)), fma(-b.y, c.x, fma(-b.x, c.y, a.y)));
 }
 
-// lane l's v, in scalar registers
-__device__ __forceinline__ double lane_d(double v, int l) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                          __builtin_amdgcn_readlane(__double2loint(v), l));
+// lane L (of each row of 16 lanes)'s v
+template <int L>
+__device__ __forceinline__ cd row_cd(cd v) {
+  const double x = __builtin_amdgcn_update_dpp(0.0, v.x, 0x150 + L, 0xf, 0xf, true);
+  const double y = __builtin_amdgcn_update_dpp(0.0, v.y, 0x150 + L, 0xf, 0xf, true);
+  return mk(x, y);
 }
-__device__ __forceinline__ cd lane_cd(cd v, int l) { return mk(lane_d(v.x, l), lane_d(v.y, l)); }
+// slots [J, J1) of a panel's rows less ck times the pivot row's entries (lane l of rl: slot l);
+// ROT: slot j takes what is left of slot j + 1
+template <int ROT, int J, int J1, int KS, int R>
+__device__ __forceinline__ void panel_update(cd (&a)[R][KS], const cd (&ck)[R], cd rl) {
+  if constexpr (J < J1) {
+    const cd rj = row_cd<J + ROT>(rl);
+#pragma unroll
+    for (int r = 0; r < R; ++r) a[r][J] = csubmul(a[r][J + ROT], ck[r], rj);
+    panel_update<ROT, J + 1, J1, KS, R>(a, ck, rl);
+  }
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>());
+  }
+}
 
 // A row's key for the pivot search: the leading bits of |Q[i][k]|^2 (a positive double's bits
 // order as its value) with the row in the last 10, lower rows first among equals.  The chosen
@@ -140,150 +160,182 @@ __device__ __forceinline__ unsigned pivot_key(cd a, bool open, int row) {
   return open ? hb | (unsigned)(1023 - row) : 0u;
 }
 
-// Panel [w0 + k0, + KB) of the window's rows, one work-group of NT threads per front: thread
-// t owns rows t + r NT, r < R, with their KB panel entries in registers.  Bound by the chain
-// of its pivots: each is the new column's keys, a wave maximum by DPP, the waves' candidate
-// rows into LDS, one barrier, a division and the rank-1 update.  Every wave publishes its
-// own best row with its key before the barrier, so one barrier per pivot serves both the
-// search and the pivot row (two LDS sets alternate), and without row swaps no other row is
-// exchanged.  The column loop stays rolled (unrolled it overflows the instruction cache), so
-// a thread's entries are kept rotated: before pivot kk slot j holds column (kk + j) mod KB.
+// Panel [w0 + k0, + KB) of the window's rows, one work-group of NT threads per front.  The
+// threads are Q groups of NR: group q owns the columns q, q + Q, ... (KS = KB / Q of them) and
+// its thread t the rows t + r NR, r < R, with those entries in registers.  Bound by the chain
+// of its pivots, each of them
+//   the new column's keys and, by DPP, the wave's best (the group that owns the column, while
+//   the others still update theirs), its entries into LDS;  barrier;
+//   the pivot row, KS entries by each of its Q threads, into LDS;  barrier;
+//   the rank-1 update, the next pivot's column first.
+// Q groups: the rows of a small front fill one wave per 64, so that the update and the row's way
+// through LDS (24 cycles per entry of a single lane) would run on one SIMD of four; over more
+// rows the waves suffice and Q is 1.  The division of a thread's own candidate and the search
+// stand before the first barrier, which the other columns' update shares; the pivot row
+// reaches the update by DPP.  Without row swaps no other row is exchanged.  The column loop
+// stays rolled but for one pivot of each group (unrolled it overflows the instruction cache),
+// so the entries are kept rotated: after m such rounds slot j holds the group's column
+// (m + j) mod KS.
 // Rows pass through LDS 8 columns (a cache line) at a time on their way in and out: taken
 // directly, every 16-byte access of a wave would touch 64 lines.
-// A thread divides for its own candidate while the wave searches, and the pivot row reaches
-// the update as scalars (one LDS read per lane and lane reads): with a division after the
-// barrier and LDS broadcasts a panel of 16 columns took 28.8 us over 512 rows and 38.7 us
-// over 1024, now 25 and 33.  Per pivot (512 rows, cycle counter): about 1000 cycles to
-// search and publish, 440 across the barrier, 1150 for the update.
-template <int KB, int R, int NT>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 2)))
-k_inv_panel(NDInv v, int w, int k0, int par) {
-  constexpr int NW = NT / 64, CB = 8, LS = CB + 1;
-  __shared__ cd s_row[2][NW][KB];
-  __shared__ unsigned s_key[2][NW];
-  __shared__ int s_ok[2][NW], s_piv[KB];
-  int bad = 0;
-  __shared__ cd s_t[NT * LS];
+template <int KB, int Q, int R, int NT>
+__global__ void __launch_bounds__(NT) k_inv_panel(NDInv v, int w, int k0, int par) {
+  constexpr int NR = NT / Q, KS = KB / Q, GW = NR / 64, CB = 8, CQ = CB / Q, LS = CB + 1;
+  static_assert(NR % 64 == 0 && CB % Q == 0 && KS >= 2 && KS <= 16 && (KS & (KS - 1)) == 0, "panel split");
+  __shared__ cd s_row[KB];                 // the pivot row, by group and slot
+  __shared__ unsigned s_key[GW];
+  __shared__ int s_piv[KB];
+  __shared__ cd s_t[NR * LS];
+  static_assert(R <= LS, "the column fits the staging buffer");
+  cd* s_col = s_t;                         // the pivot column, by row
   const InvFront f = inv_front(v, blockIdx.x, w);
   if (k0 >= f.wn) return;
-  const int kbb = min(KB, f.wn - k0), t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int kbb = min(KB, f.wn - k0), t = threadIdx.x, lane = t & 63;
+  const int q = __builtin_amdgcn_readfirstlane(t / NR), tr = t - q * NR;
   const cd* __restrict__ src = f.q(par) + (long long)f.w0 * f.ld(par) + f.w0 + k0;
   cd* __restrict__ dst = f.q(par ^ 1) + (long long)f.w0 * f.ld(par ^ 1) + f.w0 + k0;
-  const long long ls = f.ld(par), ldd = f.ld(par ^ 1);
-  cd a[R][KB];
+  const unsigned ls = (unsigned)f.ld(par), ldd = (unsigned)f.ld(par ^ 1);
+  int bad = 0;
+  cd a[R][KS];
   bool open[R];
-  // entry (row e / 8, column e % 8) of a pass of NT rows and 8 columns, e = t + NT u
+  // entry (row e / 8, column e % 8) of a pass of NR rows and 8 columns, e = t + NT u
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int c = 0; c < KB; c += CB)
+    for (int c = 0; c < KS; c += CQ)
 #pragma unroll
-      for (int u = 0; u < CB; ++u) {
+      for (int u = 0; u < CQ; ++u) {
         const int e = t + NT * u;
-        a[r][c + u] = src[min(r * NT + e / CB, f.wn - 1) * ls + min(c + e % CB, kbb - 1)];
+        // byte offsets of a window stay far below 4 GB (1024 rows)
+        const unsigned off = 16u * ((unsigned)min(r * NR + e / CB, f.wn - 1) * ls + min(c * Q + e % CB, kbb - 1));
+        a[r][c + u] = *(const cd*)((const char*)src + off);
       }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int i = r * NT + t;
+    const int i = r * NR + tr;
     open[r] = i < f.wn && f.ip[f.w0 + min(i, f.wn - 1)] < 0;
 #pragma unroll
-    for (int c = 0; c < KB; c += CB) {
+    for (int c = 0; c < KS; c += CQ) {
       __syncthreads();
 #pragma unroll
-      for (int u = 0; u < CB; ++u) {
+      for (int u = 0; u < CQ; ++u) {
         const int e = t + NT * u;
         s_t[e / CB * LS + e % CB] = a[r][c + u];
       }
       __syncthreads();
 #pragma unroll
-      for (int u = 0; u < CB; ++u) a[r][c + u] = s_t[t * LS + u];
+      for (int u = 0; u < CQ; ++u) a[r][c + u] = s_t[tr * LS + q + Q * u];
     }
   }
-  unsigned kr[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) kr[r] = pivot_key(a[r][0], open[r], r * NT + t);
-  for (int kk = 0; kk < kbb; ++kk) {
-    const int b = kk & 1;
-    // this thread's candidate and its reciprocal: the division overlaps the wave's search
+  // slot 0 into LDS; the wave's best key; the reciprocal of this thread's best row in it (zero
+  // or NaN: ok is 0 and the pivot taken as 1)
+  cd ri = mk(1.0, 0.0);
+  bool ok = true;
+  auto search = [&]() {
     cd c0 = a[0][0];
-    unsigned key = kr[0];
+    unsigned key = pivot_key(a[0][0], open[0], tr);
+    if (Q > 1) s_col[tr] = a[0][0];
 #pragma unroll
     for (int r = 1; r < R; ++r) {
-      const bool up = kr[r] > key;
+      const unsigned kr = pivot_key(a[r][0], open[r], r * NR + tr);
+      const bool up = kr > key;
       c0.x = up ? a[r][0].x : c0.x;
       c0.y = up ? a[r][0].y : c0.y;
-      key = up ? kr[r] : key;
+      key = up ? kr : key;
+      if (Q > 1) s_col[r * NR + tr] = a[r][0];
     }
-    const double d = abs2(c0);
-    const double di = 1.0 / d;
     const unsigned wk = wave_umax(key);
-    const int wrow = 1023 - (int)(wk & 1023u);
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (r * NT + t == wrow) {
-#pragma unroll
-        for (int j = 1; j < KB; ++j) s_row[b][wv][j] = a[r][j];
-        // slot 0: the reciprocal of the pivot (a zero or NaN pivot is recorded and taken as 1)
-        s_row[b][wv][0] = d > 0.0 ? mk(c0.x * di, -c0.y * di) : mk(1.0, 0.0);
-        s_ok[b][wv] = d > 0.0;
-      }
-    if (lane == 0) s_key[b][wv] = wk;
-    __syncthreads();
-    unsigned bk = s_key[b][0];
-#pragma unroll
-    for (int q = 1; q < NW; ++q) bk = max(bk, s_key[b][q]);
-    bk = (unsigned)__builtin_amdgcn_readfirstlane((int)bk);
-    const int p = 1023 - (int)(bk & 1023u);            // the pivot row, counted from w0
-    const int pw = (p & (NT - 1)) >> 6;
-    // lane l takes entry l mod KB of the pivot row; the entries then pass as scalars
-    const cd rl = s_row[b][pw][t & (KB - 1)];
-    const cd inv = lane_cd(rl, 0);
-    if (t == 0) {
-      s_piv[kk] = p;
-      if (!s_ok[b][pw]) bad = 1;
-    }
-    cd ck[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      ck[r] = a[r][0] * inv;
-      if (r * NT + t == p) {                           // the pivot row: -row / pivot, 1 / pivot
-        ck[r] = inv;
-        open[r] = false;
-#pragma unroll
-        for (int j = 1; j < KB; ++j) a[r][j] = mk(0.0, 0.0);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j + 1 < KB; ++j) {
-      const cd rj = lane_cd(rl, j + 1);
-#pragma unroll
-      for (int r = 0; r < R; ++r) a[r][j] = csubmul(a[r][j + 1], ck[r], rj);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      a[r][KB - 1] = ck[r];
-      kr[r] = pivot_key(a[r][0], open[r], r * NT + t);
-    }
-  }
-  if (t == 0 && bad) atomicOr(v.err, 1);
+    if (lane == 0) s_key[tr >> 6] = wk;
+    const double d = abs2(c0), di = 1.0 / d;
+    ok = d > 0.0;
+    ri = ok ? mk(c0.x * di, -c0.y * di) : mk(1.0, 0.0);
+    asm("" : "+v"(ri.x), "+v"(ri.y));      // divided here, not by the winner after the barrier
+  };
   __syncthreads();
+  if (q == 0) search();
+  __syncthreads();
+  // one pivot of each group in turn, each group's in its slot 0; the last one's update also
+  // rotates the slots
+  for (int k1 = 0; k1 < kbb; k1 += Q)
+    static_for<Q>([&](auto qc) {
+      constexpr int QO = decltype(qc)::value, LAST = QO == Q - 1;
+      const int kk = k1 + QO;
+      if (kk >= kbb) return;               // uniform: a last panel of fewer columns
+      unsigned bk = s_key[0];
+#pragma unroll
+      for (int g = 1; g < GW; ++g) bk = max(bk, s_key[g]);
+      cd ck[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) ck[r] = Q > 1 ? s_col[r * NR + tr] : mk(a[r][0].x, a[r][0].y);
+      const int p = 1023 - (__builtin_amdgcn_readfirstlane((int)bk) & 1023);   // the pivot row, from w0
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (r * NR + tr == p) {
+#pragma unroll
+          for (int j = 1; j < KS; ++j) s_row[q * KS + j] = a[r][j];
+          if (q == QO) {
+            s_row[q * KS] = ri;                        // the reciprocal of the pivot
+            if (!ok) bad = 1;                          // a zero or NaN pivot is recorded
+            s_piv[kk] = p;
+          } else {
+            s_row[q * KS] = a[r][0];
+          }
+          // the pivot row becomes -row / pivot, 1 / pivot: ck below is 1 / pivot for it
+          open[r] = false;
+#pragma unroll
+          for (int j = 0; j < KS; ++j) a[r][j] = mk(0.0, 0.0);
+        }
+      __syncthreads();
+      const cd rl = s_row[q * KS + (t & (KS - 1))];
+      const cd inv = s_row[QO * KS];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        ck[r] = ck[r] * inv;
+        if (r * NR + tr == p) ck[r] = inv;
+      }
+      // the pivot's column becomes ck; the next pivot's column first, so that its search and
+      // division overlap the other columns
+      cd s0[R];
+      const cd r0 = row_cd<0>(rl);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        s0[r] = csubmul(a[r][0], ck[r], r0);
+        if (q == QO) s0[r] = ck[r];
+      }
+      if constexpr (LAST) {
+        panel_update<1, 0, 1, KS, R>(a, ck, rl);
+        if (q == 0) search();
+        panel_update<1, 1, KS - 1, KS, R>(a, ck, rl);
+#pragma unroll
+        for (int r = 0; r < R; ++r) a[r][KS - 1] = s0[r];
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) a[r][0] = s0[r];
+        if (q == QO + 1) search();
+        panel_update<0, 1, KS, KS, R>(a, ck, rl);
+      }
+      __syncthreads();
+    });
+  if (bad) atomicOr(v.err, 1);
   if (t < kbb) {
     f.pm[f.w0 + k0 + t] = f.w0 + s_piv[t];
     f.ip[f.w0 + s_piv[t]] = f.w0 + k0 + t;
   }
-  // slot j now holds column (kbb + j) mod KB
+  // slot j of group g now holds its column (m + j) mod KS, after m rotations
+  const int m = kbb / Q;
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int c = 0; c < KB; c += CB) {
+    for (int c = 0; c < KS; c += CQ) {
       __syncthreads();
 #pragma unroll
-      for (int u = 0; u < CB; ++u) s_t[t * LS + u] = a[r][c + u];
+      for (int u = 0; u < CQ; ++u) s_t[tr * LS + q + Q * u] = a[r][c + u];
       __syncthreads();
 #pragma unroll
-      for (int u = 0; u < CB; ++u) {
-        const int e = t + NT * u, i = r * NT + e / CB, col = (kbb + c + e % CB) % KB;
-        if (i < f.wn && col < kbb) dst[i * ldd + col] = s_t[e / CB * LS + e % CB];
+      for (int u = 0; u < CQ; ++u) {
+        const int e = t + NT * u, i = r * NR + e / CB;
+        const int col = e % Q + Q * ((m + c + e % CB / Q) % KS);
+        if (i < f.wn && col < kbb) *(cd*)((char*)dst + 16u * ((unsigned)i * ldd + col)) = s_t[e / CB * LS + e % CB];
       }
     }
 }
@@ -637,20 +689,25 @@ void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, long long max_nb2
                      child_map_off, maps, v.F, slot);
 }
 
-// columns of a panel over a window of up to rows rows: 32 while a thread owns one row, then
-// 16 (R x KB entries of 4 registers each stay within a wave's 512)
+// columns of a panel over a window of up to rows rows, and its split (k_inv_panel): 32 columns
+// while their entries leave a thread at most 16, then 16.  A panel in us, split into 4 / 2
+// groups or whole rows per thread: 64 rows 26.6 / 28.8 / 33, 128 rows 31.3 / 35.4 / 36,
+// 256 rows 41.4 / 40.2 / 50; of 16 columns over 512 rows, 2 groups / whole rows 22.2 / 21.6,
+// over 1024 34.6 / 31.7.
 static int panel_cols(int rows) { return rows <= 256 ? 32 : 16; }
 static void inv_panel(const NDInv& v, int nids, int rows, int w, int k0, int par, hipStream_t s) {
+#define PANEL(KB, Q, R, NT) \
+  hipLaunchKernelGGL((k_inv_panel<KB, Q, R, NT>), dim3(nids), dim3(NT), 0, s, v, w, k0, par)
   if (rows <= 64)
-    hipLaunchKernelGGL((k_inv_panel<32, 1, 64>), dim3(nids), dim3(64), 0, s, v, w, k0, par);
+    PANEL(32, 4, 1, 256);
   else if (rows <= 128)
-    hipLaunchKernelGGL((k_inv_panel<32, 1, 128>), dim3(nids), dim3(128), 0, s, v, w, k0, par);
+    PANEL(32, 4, 2, 256);
   else if (rows <= 256)
-    hipLaunchKernelGGL((k_inv_panel<32, 1, 256>), dim3(nids), dim3(256), 0, s, v, w, k0, par);
+    PANEL(32, 2, 1, 512);
   else if (rows <= 512)
-    hipLaunchKernelGGL((k_inv_panel<16, 2, 256>), dim3(nids), dim3(256), 0, s, v, w, k0, par);
+    PANEL(16, 1, 1, 512);
   else if (rows <= 1024)
-    hipLaunchKernelGGL((k_inv_panel<16, 2, 512>), dim3(nids), dim3(512), 0, s, v, w, k0, par);
+    PANEL(16, 1, 2, 512);
   else
     throw std::runtime_error("nd_invert: window of more than 1024 rows");
 }
