@@ -609,7 +609,7 @@ size_t carve(helm_ctx* c, void* ws) {
   // Krylov
   c->V = cv.take<cd>(rc * (m + 1) * g1.tot);
   c->Z = cv.take<char>(rc * cs * (size_t)m * g1.tot);
-  long long nblk = (g1.tot + 256 * KNPT - 1) / (256 * KNPT);
+  const long long nblk = kr_blocks(g1.tot);
   c->part = cv.take<cd>(rc * (2 * KMAXM + 3) * nblk);
   c->st = cv.take<KrylovState>(rc);
   c->Bm = rc > 1 ? cv.take<cd>(rc * g1.tot) : nullptr;
@@ -1019,7 +1019,7 @@ KrylovArgs make_kargs(helm_ctx* c, int op) {
   a.V = c->V;
   a.ldv = (long long)c->nr * c->g1.tot;
   a.part = c->part;
-  a.nblk = (int)((c->g1.tot + 256 * KNPT - 1) / (256 * KNPT));
+  a.nblk = (int)kr_blocks(c->g1.tot);
   a.pcap = a.nblk;
   a.st = c->st;
   a.nrhs = c->nr;

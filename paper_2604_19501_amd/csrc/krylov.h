@@ -6,7 +6,13 @@ namespace helm {
 
 #define KMAXM 64
 #define KMAXIT 4096
-#define KNPT 4            // nodes per thread in the reduction kernels
+#define KNPT 4            // nodes per thread of the node kernels
+// small grids: one node per thread (kr_npt in krylov.hip)
+int kr_npt(long long N);
+inline long long kr_blocks(long long N) {
+  const long long per = 256LL * kr_npt(N);
+  return (N + per - 1) / per;
+}
 
 struct KrylovState {
   cd H[(KMAXM + 1) * KMAXM];   // Hessenberg, column-major, leading dimension KMAXM + 1
@@ -44,7 +50,7 @@ struct KrylovArgs {
   long long ldv;
   cd* part;       // partial sums, value-major: part[i * pcap + block]
   int pcap;
-  int nblk;            // blocks of the node kernels = ceil(N / (256 * KNPT))
+  int nblk;            // blocks of the node kernels = kr_blocks(N)
   KrylovState* st;
   int nrhs;
   long long pstride;

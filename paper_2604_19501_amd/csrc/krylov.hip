@@ -20,6 +20,7 @@
 // two-stage (per-block partials, then a fixed-order sum), so the results are bitwise
 // reproducible run to run.
 #include <cstddef>
+#include <type_traits>
 
 #include "krylov.h"
 #include "wide.h"
@@ -74,9 +75,12 @@ __device__ __forceinline__ RhsPtr at_rhs(const KrylovArgs& a) {
   return RhsPtr{a.V + r * a.op.g.tot, a.st + r, a.part + r * a.pstride};
 }
 
+template <int NPT>
 __device__ __forceinline__ long long node_of(int q) {
-  return ((long long)blockIdx.x * KNPT + q) * 256 + threadIdx.x;
+  return ((long long)blockIdx.x * NPT + q) * 256 + threadIdx.x;
 }
+// basis vectors in flight per thread of the Arnoldi passes
+template <int NPT> constexpr int KPF = NPT == 1 ? 4 : 1;
 
 // CMP: the compact fourth-order operator (no conjugate form), a separate instantiation of
 // every kernel that applies H: inlined into the 5/7-point kernels as a run-time branch it
@@ -121,53 +125,61 @@ __device__ __forceinline__ void store_partials(cd (*red)[2 * KMAXM + 3], int nv,
 
 // w = H z_j (FP64); partials of <V_i, w> (values 0..j), <V_i, V_j> (values j+1..2j+1) and
 // ||w||^2 (value 2j+2, real part).  Nodes past the end are clamped to the last node and
-// weighted 0; basis vector i + 1 is loaded while vector i is reduced, and V_j, loaded
-// first for the Gram column, serves as the last vector (read from memory once).  The
+// weighted 0; the next KPF basis vectors are in flight while vector i is reduced, and V_j,
+// loaded first for the Gram column, serves as the last vector (read from memory once).  The
 // V_0..V_{j-1} loads are non-temporal: the basis (about 17 MB per vector at 1025^2) is
 // larger than the caches, and streaming it through them would displace what the cycle
 // reuses (measured: 1 % more solves per second at 1025^2 with these loads non-temporal).
-template <typename CZ, int CMP>
+template <typename CZ, int CMP, int NPT>
 __global__ void __launch_bounds__(256) k_arnoldi_dots(KrylovArgs a, const CZ* __restrict__ z, int j) {
+  constexpr int PF = KPF<NPT>;
   __shared__ cd red[4][2 * KMAXM + 3];
   const RhsPtr p = at_rhs(a);
   z += blockIdx.y * a.op.g.tot;
   if (p.st->done) return;          // an iteration queued after convergence: nothing to do
   const long long N = a.op.g.tot;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  long long f[KNPT];
-  double on[KNPT];
-  for (int q = 0; q < KNPT; ++q) {
-    long long t = node_of(q);
+  long long f[NPT];
+  double on[NPT];
+  for (int q = 0; q < NPT; ++q) {
+    long long t = node_of<NPT>(q);
     on[q] = t < N ? 1.0 : 0.0;
     f[q] = t < N ? t : N - 1;
   }
-  cd w[KNPT], vj[KNPT], nx[KNPT];
-  for (int q = 0; q < KNPT; ++q) {
+  cd w[NPT], vj[NPT], nx[PF][NPT];
+  for (int q = 0; q < NPT; ++q) {
     vj[q] = on[q] * p.V[(long long)j * a.ldv + f[q]];
-    if (j > 0) nx[q] = ld_nt(p.V + f[q]);
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+      if (u < j) nx[u][q] = ld_nt(p.V + (long long)u * a.ldv + f[q]);
   }
   double nw = 0.0;
-  for (int q = 0; q < KNPT; ++q) {
+  for (int q = 0; q < NPT; ++q) {
     w[q] = on[q] * apply_h<CMP>(a, z, f[q]);
     nw += abs2(w[q]);
   }
-  for (int i = 0; i <= j; ++i) {
-    // V_i: the prefetched vector, or V_j itself (the weights of clamped nodes are 0 in w
-    // and vj, so their partial terms vanish either way)
-    cd vi[KNPT];
-    for (int q = 0; q < KNPT; ++q) vi[q] = i < j ? nx[q] : vj[q];
-    if (i + 1 < j)                                                // uniform over the block
-      for (int q = 0; q < KNPT; ++q) nx[q] = ld_nt(p.V + (long long)(i + 1) * a.ldv + f[q]);
-    cd s1 = mk(0.0, 0.0), s2 = mk(0.0, 0.0);
-    for (int q = 0; q < KNPT; ++q) {
-      s1 += cmulc(vi[q], w[q]);
-      s2 += cmulc(vi[q], vj[q]);
-    }
-    s1 = wsum(s1);
-    s2 = wsum(s2);
-    if (lane == 0) {
-      red[wv][i] = s1;
-      red[wv][j + 1 + i] = s2;
+  for (int i0 = 0; i0 <= j; i0 += PF) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      const int i = i0 + u;
+      if (i > j) break;                                             // uniform over the block
+      // V_i: the prefetched vector, or V_j itself (the weights of clamped nodes are 0 in w
+      // and vj, so their partial terms vanish either way)
+      cd vi[NPT];
+      for (int q = 0; q < NPT; ++q) vi[q] = i < j ? nx[u][q] : vj[q];
+      if (i + PF < j)
+        for (int q = 0; q < NPT; ++q) nx[u][q] = ld_nt(p.V + (long long)(i + PF) * a.ldv + f[q]);
+      cd s1 = mk(0.0, 0.0), s2 = mk(0.0, 0.0);
+      for (int q = 0; q < NPT; ++q) {
+        s1 += cmulc(vi[q], w[q]);
+        s2 += cmulc(vi[q], vj[q]);
+      }
+      s1 = wsum(s1);
+      s2 = wsum(s2);
+      if (lane == 0) {
+        red[wv][i] = s1;
+        red[wv][j + 1 + i] = s2;
+      }
     }
   }
   cd t = wsum(mk(nw, 0.0));
@@ -176,7 +188,7 @@ __global__ void __launch_bounds__(256) k_arnoldi_dots(KrylovArgs a, const CZ* __
 }
 
 // r = b - H x (FP64) into V_0; partials of (||r||^2, ||b||^2) in slot 0
-template <int CMP>
+template <int CMP, int NPT>
 __global__ void __launch_bounds__(256) k_residual(KrylovArgs a, const cd* __restrict__ x,
                                                   const cd* __restrict__ b) {
   __shared__ cd lds[4];
@@ -185,8 +197,8 @@ __global__ void __launch_bounds__(256) k_residual(KrylovArgs a, const cd* __rest
   b += blockIdx.y * a.op.g.tot;
   const long long N = a.op.g.tot;
   cd v = mk(0.0, 0.0);
-  for (int q = 0; q < KNPT; ++q) {
-    long long f = node_of(q);
+  for (int q = 0; q < NPT; ++q) {
+    long long f = node_of<NPT>(q);
     if (f < N) {
       cd res = b[f] - apply_h<CMP>(a, x, f);
       p.V[f] = res;
@@ -459,9 +471,10 @@ __global__ void __launch_bounds__(256) k_fin_givens(KrylovArgs a, int j, double 
 // With pack_dst, the first block of each right-hand side also packs its state (final after
 // the column's finish) into the host-mapped slot, so that the stores to host memory drain
 // while this pass streams instead of delaying it.
-template <typename CZ, int CMP>
+template <typename CZ, int CMP, int NPT>
 __global__ void __launch_bounds__(256) k_arnoldi_update(KrylovArgs a, const CZ* __restrict__ z, int j,
                                                         char* pack_dst) {
+  constexpr int PF = KPF<NPT>;
   __shared__ cd sc[KMAXM + 1];
   __shared__ double sinv;
   const RhsPtr p = at_rhs(a);
@@ -472,27 +485,34 @@ __global__ void __launch_bounds__(256) k_arnoldi_update(KrylovArgs a, const CZ* 
   if (threadIdx.x == 0) sinv = p.st->hnext > 0.0 ? 1.0 / p.st->hnext : 0.0;
   const long long N = a.op.g.tot;
   const long long blk = (long long)gridDim.x - 1 - blockIdx.x;
-  long long f[KNPT];
-  bool ok[KNPT];
-  for (int q = 0; q < KNPT; ++q) {
-    long long t = (blk * KNPT + q) * 256 + threadIdx.x;
+  long long f[NPT];
+  bool ok[NPT];
+  for (int q = 0; q < NPT; ++q) {
+    long long t = (blk * NPT + q) * 256 + threadIdx.x;
     ok[q] = t < N;
     f[q] = ok[q] ? t : N - 1;
   }
-  cd w[KNPT], nx[KNPT];
-  for (int q = 0; q < KNPT; ++q) nx[q] = ld_nt(p.V + f[q]);
-  for (int q = 0; q < KNPT; ++q) w[q] = apply_h<CMP>(a, z, f[q]);
+  cd w[NPT], nx[PF][NPT];
+  for (int q = 0; q < NPT; ++q)
+#pragma unroll
+    for (int u = 0; u < PF; ++u) nx[u][q] = ld_nt(p.V + (long long)(u < j ? u : j) * a.ldv + f[q]);
+  for (int q = 0; q < NPT; ++q) w[q] = apply_h<CMP>(a, z, f[q]);
   __syncthreads();
-  for (int i = 0; i <= j; ++i) {
-    cd vi[KNPT];
-    for (int q = 0; q < KNPT; ++q) vi[q] = nx[q];
-    const long long in = (long long)(i < j ? i + 1 : j) * a.ldv;   // the last pass reloads V_j
-    for (int q = 0; q < KNPT; ++q) nx[q] = ld_nt(p.V + in + f[q]);
-    const cd ci = sc[i];
-    for (int q = 0; q < KNPT; ++q) w[q] -= ci * vi[q];
+  for (int i0 = 0; i0 <= j; i0 += PF) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      const int i = i0 + u;
+      if (i > j) break;                                             // uniform over the block
+      cd vi[NPT];
+      for (int q = 0; q < NPT; ++q) vi[q] = nx[u][q];
+      const long long in = (long long)(i + PF < j ? i + PF : j) * a.ldv;   // the last passes reload V_j
+      for (int q = 0; q < NPT; ++q) nx[u][q] = ld_nt(p.V + in + f[q]);
+      const cd ci = sc[i];
+      for (int q = 0; q < NPT; ++q) w[q] -= ci * vi[q];
+    }
   }
   const double si = sinv;
-  for (int q = 0; q < KNPT; ++q)
+  for (int q = 0; q < NPT; ++q)
     if (ok[q]) p.V[(long long)(j + 1) * a.ldv + f[q]] = si * w[q];
 }
 
@@ -512,12 +532,13 @@ __global__ void k_fin_residual(KrylovArgs a, int set_b) {
   if (!isfinite(b0)) st->nonfinite = 1;
 }
 
+template <int NPT>
 __global__ void __launch_bounds__(256) k_scale_v0(KrylovArgs a) {
   const RhsPtr p = at_rhs(a);
   double s = p.st->beta0 > 0.0 ? 1.0 / p.st->beta0 : 0.0;
   const long long N = a.op.g.tot;
-  for (int q = 0; q < KNPT; ++q) {
-    long long f = node_of(q);
+  for (int q = 0; q < NPT; ++q) {
+    long long f = node_of<NPT>(q);
     if (f < N) p.V[f] = s * p.V[f];
   }
 }
@@ -538,7 +559,7 @@ __global__ void k_solve_y(KrylovArgs a) {
 }
 
 // x += sum_i y_i Z_i
-template <typename CZ>
+template <typename CZ, int NPT>
 __global__ void __launch_bounds__(256) k_update_x(KrylovArgs a, const CZ* __restrict__ Z, long long ldz,
                                                   cd* __restrict__ x) {
   __shared__ cd sy[KMAXM];
@@ -549,8 +570,8 @@ __global__ void __launch_bounds__(256) k_update_x(KrylovArgs a, const CZ* __rest
   if (threadIdx.x < k) sy[threadIdx.x] = p.st->y[threadIdx.x];
   __syncthreads();
   const long long N = a.op.g.tot;
-  for (int q = 0; q < KNPT; ++q) {
-    long long f = node_of(q);
+  for (int q = 0; q < NPT; ++q) {
+    long long f = node_of<NPT>(q);
     if (f >= N) continue;
     cd acc = x[f];
     for (int i = 0; i < k; ++i) acc += sy[i] * to_d(Z[(long long)i * ldz + f]);
@@ -559,13 +580,13 @@ __global__ void __launch_bounds__(256) k_update_x(KrylovArgs a, const CZ* __rest
 }
 
 // x += z over nr right-hand sides (z in cycle precision)
-template <typename CZ>
+template <typename CZ, int NPT>
 __global__ void __launch_bounds__(256) k_add_z(KrylovArgs a, const CZ* __restrict__ z, cd* __restrict__ x) {
   const long long N = a.op.g.tot;
   z += blockIdx.y * N;
   x += blockIdx.y * N;
-  for (int q = 0; q < KNPT; ++q) {
-    long long f = node_of(q);
+  for (int q = 0; q < NPT; ++q) {
+    long long f = node_of<NPT>(q);
     if (f < N) x[f] += to_d(z[f]);
   }
 }
@@ -620,29 +641,44 @@ void kr_finalize(const KrylovArgs& a, unsigned mask, hipStream_t s) {
 void kr_init(const KrylovArgs& a, int max_iter, int seq, hipStream_t s) {
   hipLaunchKernelGGL(k_init_state, dim3(1, a.nrhs), dim3(1), 0, s, a.st, max_iter, seq);
 }
+// Nodes per thread.  Four keep a large grid's basis streaming with few partial sums and wave
+// reductions; on a small grid they leave one wave per SIMD or less, each waiting for one basis
+// vector at a time, where one node per thread has four vectors in flight.  Per FGMRES
+// iteration, four nodes / one: 64^2 64.0 / 58.6 us, 200^2 90.7 / 85.2, 256^2 108.9 / 104.5,
+// 300^2 FP64 113.8 / 110.1, then 400^2 114.6 / 115.3, 80^3 FP64 255 / 262, 720^2 165 / 174.
+constexpr long long KNPT_LINE = 131072;
+int kr_npt(long long N) { return N <= KNPT_LINE ? 1 : KNPT; }
+// f(NPT, CMP) with the grid's nodes per thread and the outer operator's kind as constants
+template <class F>
+static void kr_dispatch(const KrylovArgs& a, F f) {
+  using std::integral_constant;
+  typedef integral_constant<int, 1> C1;
+  typedef integral_constant<int, KNPT> C4;
+  typedef integral_constant<int, 0> P5;
+  if (kr_npt(a.op.g.tot) == 1) a.op.compact ? f(C1(), C1()) : f(C1(), P5());
+  else a.op.compact ? f(C4(), C1()) : f(C4(), P5());
+}
 void kr_residual(const KrylovArgs& a, const cd* x, const cd* b, int with_b, hipStream_t s) {
-  if (a.op.compact)
-    hipLaunchKernelGGL((k_residual<1>), dim3(a.nblk, a.nrhs), dim3(256), 0, s, a, x, b);
-  else
-    hipLaunchKernelGGL((k_residual<0>), dim3(a.nblk, a.nrhs), dim3(256), 0, s, a, x, b);
+  kr_dispatch(a, [&](auto npt, auto cmp) {
+    hipLaunchKernelGGL((k_residual<cmp(), npt()>), dim3(a.nblk, a.nrhs), dim3(256), 0, s, a, x, b);
+  });
   hipLaunchKernelGGL(k_fin_sum, dim3(1, a.nrhs), dim3(256), 0, s, a, offsetof(KrylovState, tmp));
   hipLaunchKernelGGL(k_fin_residual, dim3(1, a.nrhs), dim3(1), 0, s, a, with_b);
 }
 void kr_scale_v0(const KrylovArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_v0, dim3(a.nblk, a.nrhs), dim3(256), 0, s, a);
+  kr_dispatch(a, [&](auto npt, auto) {
+    hipLaunchKernelGGL((k_scale_v0<npt()>), dim3(a.nblk, a.nrhs), dim3(256), 0, s, a);
+  });
 }
 void kr_arnoldi(const KrylovArgs& a, const void* z, int z_f32, int j, double tol, void* pack_dst, int fused,
                 hipStream_t s) {
   dim3 g(a.nblk, a.nrhs);
-  const int cmp = a.op.compact;
-  if (z_f32 && !cmp)
-    hipLaunchKernelGGL((k_arnoldi_dots<cf, 0>), g, dim3(256), 0, s, a, (const cf*)z, j);
-  else if (!cmp)
-    hipLaunchKernelGGL((k_arnoldi_dots<cd, 0>), g, dim3(256), 0, s, a, (const cd*)z, j);
-  else if (z_f32)
-    hipLaunchKernelGGL((k_arnoldi_dots<cf, 1>), g, dim3(256), 0, s, a, (const cf*)z, j);
-  else
-    hipLaunchKernelGGL((k_arnoldi_dots<cd, 1>), g, dim3(256), 0, s, a, (const cd*)z, j);
+  kr_dispatch(a, [&](auto npt, auto cmp) {
+    if (z_f32)
+      hipLaunchKernelGGL((k_arnoldi_dots<cf, cmp(), npt()>), g, dim3(256), 0, s, a, (const cf*)z, j);
+    else
+      hipLaunchKernelGGL((k_arnoldi_dots<cd, cmp(), npt()>), g, dim3(256), 0, s, a, (const cd*)z, j);
+  });
   if (fused) {
     hipLaunchKernelGGL(k_fin_givens, dim3(2 * j + 3, a.nrhs), dim3(256), 0, s, a, j, tol);
   } else {
@@ -650,29 +686,31 @@ void kr_arnoldi(const KrylovArgs& a, const void* z, int z_f32, int j, double tol
     hipLaunchKernelGGL(k_givens, dim3(1, a.nrhs), dim3(64), 0, s, a, j, tol);
   }
   char* pk = (char*)pack_dst;
-  if (z_f32 && !cmp)
-    hipLaunchKernelGGL((k_arnoldi_update<cf, 0>), g, dim3(256), 0, s, a, (const cf*)z, j, pk);
-  else if (!cmp)
-    hipLaunchKernelGGL((k_arnoldi_update<cd, 0>), g, dim3(256), 0, s, a, (const cd*)z, j, pk);
-  else if (z_f32)
-    hipLaunchKernelGGL((k_arnoldi_update<cf, 1>), g, dim3(256), 0, s, a, (const cf*)z, j, pk);
-  else
-    hipLaunchKernelGGL((k_arnoldi_update<cd, 1>), g, dim3(256), 0, s, a, (const cd*)z, j, pk);
+  kr_dispatch(a, [&](auto npt, auto cmp) {
+    if (z_f32)
+      hipLaunchKernelGGL((k_arnoldi_update<cf, cmp(), npt()>), g, dim3(256), 0, s, a, (const cf*)z, j, pk);
+    else
+      hipLaunchKernelGGL((k_arnoldi_update<cd, cmp(), npt()>), g, dim3(256), 0, s, a, (const cd*)z, j, pk);
+  });
 }
 void kr_update_x(const KrylovArgs& a, const void* Z, int z_f32, long long ldz, cd* x, hipStream_t s) {
   hipLaunchKernelGGL(k_solve_y, dim3(1, a.nrhs), dim3(1), 0, s, a);
   dim3 g(a.nblk, a.nrhs);
-  if (z_f32)
-    hipLaunchKernelGGL((k_update_x<cf>), g, dim3(256), 0, s, a, (const cf*)Z, ldz, x);
-  else
-    hipLaunchKernelGGL((k_update_x<cd>), g, dim3(256), 0, s, a, (const cd*)Z, ldz, x);
+  kr_dispatch(a, [&](auto npt, auto) {
+    if (z_f32)
+      hipLaunchKernelGGL((k_update_x<cf, npt()>), g, dim3(256), 0, s, a, (const cf*)Z, ldz, x);
+    else
+      hipLaunchKernelGGL((k_update_x<cd, npt()>), g, dim3(256), 0, s, a, (const cd*)Z, ldz, x);
+  });
 }
 void kr_add_z(const KrylovArgs& a, const void* z, int z_f32, cd* x, hipStream_t s) {
   dim3 g(a.nblk, a.nrhs);
-  if (z_f32)
-    hipLaunchKernelGGL((k_add_z<cf>), g, dim3(256), 0, s, a, (const cf*)z, x);
-  else
-    hipLaunchKernelGGL((k_add_z<cd>), g, dim3(256), 0, s, a, (const cd*)z, x);
+  kr_dispatch(a, [&](auto npt, auto) {
+    if (z_f32)
+      hipLaunchKernelGGL((k_add_z<cf, npt()>), g, dim3(256), 0, s, a, (const cf*)z, x);
+    else
+      hipLaunchKernelGGL((k_add_z<cd, npt()>), g, dim3(256), 0, s, a, (const cd*)z, x);
+  });
 }
 void kr_zero(cd* x, long long n, hipStream_t s) {
   hipLaunchKernelGGL(k_zero_c128, dim3(1024), dim3(256), 0, s, x, n);
