@@ -27,11 +27,10 @@ void gal_coarse(const Geom& g, const cd* A, const Geom& gc, cd* out, hipStream_t
 void cast_d2f(const cd* a, cf* b, long long n, hipStream_t st);
 void cast_f2d(const cf* a, cd* b, long long n, hipStream_t st);
 void square_slowness(const double* kap, double* m64, float* m32, long long n, int is_m, hipStream_t st);
-void nd_zero(cd* p, long long n, hipStream_t s);
 void nd_fill_int(int* p, long long n, int x, hipStream_t s);
 void nd_assemble(const NDInv& v, int nids, int max_asm, const NDAsm* asmv, const cd* coef, hipStream_t s);
-void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, long long max_nb2, const int* children,
-               const long long* child_map_off, const int* maps, int slot, hipStream_t s);
+void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, int max_nF, const int* children,
+               const long long* child_map_off, const int* maps, hipStream_t s);
 // A^-1 of the height's fronts (in exchanged order), in blocks of block_cols columns; returns
 // the block width used, which nd_products takes
 int nd_invert(const NDInv& v, int nids, int max_nS, int max_wn, int block_cols, hipStream_t s);
@@ -125,9 +124,8 @@ struct Pending {
 };
 
 struct HeightInfo {
-  int start, count, max_asm, max_nS, max_nB, max_child;
+  int start, count, max_asm, max_nS, max_nB, max_nF;
   int max_wn;             // rows of the widest inversion window
-  long long max_nb2;
   long long s_bytes;      // the fronts' separator blocks, FP64 complex
 };
 
@@ -509,10 +507,7 @@ void build_plan(helm_ctx* c) {
       hi.max_nS = std::max(hi.max_nS, f.nS);
       hi.max_nB = std::max(hi.max_nB, f.nB);
       hi.max_wn = std::max(hi.max_wn, std::min(f.nS, win_size(f.nS, c->nd_win)));
-      int nbc = 0;
-      hi.max_child = std::max(hi.max_child, f.nchild);
-      for (int q = 0; q < f.nchild; ++q) nbc = std::max(nbc, P.fronts[P.children[f.child_off + q]].nB);
-      hi.max_nb2 = std::max(hi.max_nb2, (long long)nbc * nbc);
+      hi.max_nF = std::max(hi.max_nF, f.nF);
     }
     hi.s_bytes = (long long)sizeof(cd) * goff;
     c->T_elems = std::max(c->T_elems, toff);
@@ -631,16 +626,14 @@ cd shift_scalar(double alpha, double beta, double omega) {
 void nd_factor(helm_ctx* c, hipStream_t s) {
   NDDev& d = c->nd;
   NDPlan& P = c->plan;
-  nd_zero(d.F, P.F_total, s);
   nd_fill_int(d.iperm, P.perm_total, -1, s);
   nd_fill_int(d.err, 1, 0, s);
   for (size_t h = 0; h < c->hinfo.size(); ++h) {
     const HeightInfo& hi = c->hinfo[h];
     const NDInv v{d.hfr + hi.start, d.goff + hi.start, d.F, d.G, d.perm, d.iperm, d.err, c->nd_win};
     const long long* toff = d.toff + hi.start;
+    nd_extend(v, d.fronts, hi.count, hi.max_nF, d.children, d.child_map_off, d.maps, s);
     nd_assemble(v, hi.count, hi.max_asm, d.asmv, c->coef3_64, s);
-    for (int slot = 0; slot < hi.max_child; ++slot)
-      nd_extend(v, d.fronts, hi.count, hi.max_nb2, d.children, d.child_map_off, d.maps, slot, s);
     // panels grouped into blocks of HELM_ND_KB_OUTER columns: the panels of a block update
     // each other and the rest of the window takes one product per block, so the separator
     // blocks are streamed once per block instead of once per panel.  That pays once they

@@ -282,7 +282,6 @@ struct NDPlan {
   std::vector<NDFrontDev> fronts;
   std::vector<int> idx, maps, cptr, cidx, children;
   std::vector<long long> child_map_off;   // per entry of `children`: offset of its map
-  int max_children = 0;
   std::vector<NDAsm> asmv;
   std::vector<std::vector<int>> by_height;   // front ids per height
   int max_height = 0;

@@ -201,7 +201,6 @@ void nd_plan(const Geom& g3, int leaf_max, int root_merge, int elem_bytes, long 
   plan.children.clear();
   plan.child_map_off.clear();
   plan.max_height = 0;
-  plan.max_children = 0;
   plan.max_nS = plan.max_nB = plan.max_nF = 0;
   long long F = 0, L = 0, W = 0, U = 0, P = 0, La = 0, Wa = 0;
   const long long line = std::max(1, 128 / std::max(1, elem_bytes));   // entries per 128 bytes
@@ -222,7 +221,6 @@ void nd_plan(const Geom& g3, int leaf_max, int root_merge, int elem_bytes, long 
     f.nchild = (int)kids[t].size();
     f.height = height[t];
     plan.max_height = std::max(plan.max_height, f.height);
-    plan.max_children = std::max(plan.max_children, f.nchild);
     f.idx_off = (long long)plan.idx.size();
     plan.idx.insert(plan.idx.end(), bd.S[oid[t]].begin(), bd.S[oid[t]].end());
     plan.idx.insert(plan.idx.end(), Bof(t).begin(), Bof(t).end());
