@@ -724,11 +724,8 @@ void numeric_setup(helm_ctx* c, const double* medium, int is_m, hipStream_t s) {
   if (c->compact) {
     // the compact stack: A2 = R1 H_beta^{alpha2} P1, A3 = R2 (R1 H_beta^alpha P1) P2 with
     // its transfers (eqs. 2.2, 3.3-3.6), then the exact factorisation
-    wgal_fine(c->op, shift_scalar(shift->alpha2, shift->beta, omega), c->m64, c->g2, c->tr[0], c->ip[0], c->r2,
-              c->coef2_64, s);
-    if (c->f32) cast_d2f(c->coef2_64, c->coef2_32, (long long)c->K2 * c->g2.tot, s);
-    wgal_fine(c->op, shift_scalar(shift->alpha, shift->beta, omega), c->m64, c->g2, c->tr[0], c->ip[0], c->r2,
-              c->tmp2, s);
+    wgal_fine(c->op, shift_scalar(shift->alpha2, shift->beta, omega), shift_scalar(shift->alpha, shift->beta, omega),
+              c->m64, c->g2, c->tr[0], c->ip[0], c->r2, c->coef2_64, c->f32 ? c->coef2_32 : nullptr, c->tmp2, s);
     wgal_coarse(c->g2, c->tmp2, c->r2, c->g3, c->tr[1], c->ip[1], c->r3, c->coef3_64, s);
     nd_factor(c, s);
     return;

@@ -38,10 +38,10 @@ struct WFine {
 };
 
 // ---- set-up (FP64) ----
-// out (planes of radius rc on gc) = Rt-restriction of H_s (compact, fine grid op.g)
-// interpolated by Pt (P = 2^d Pt^T per axis)
-void wgal_fine(const FineOp& op, cd s, const double* m, const Geom& gc, const Transfer1D& Rt,
-               const Transfer1D& Pt, int rc, cd* out, hipStream_t st);
+// outa and outb (planes of radius rc on gc) = Rt-restriction of H_s (compact, fine grid op.g)
+// interpolated by Pt (P = 2^d Pt^T per axis), for s = sa and sb; outa32: outa in FP32, or null
+void wgal_fine(const FineOp& op, cd sa, cd sb, const double* m, const Geom& gc, const Transfer1D& Rt,
+               const Transfer1D& Pt, int rc, cd* outa, cf* outa32, cd* outb, hipStream_t st);
 // out = Rt A Pt for A given as planes of radius rin on g
 void wgal_coarse(const Geom& g, const cd* A, int rin, const Geom& gc, const Transfer1D& Rt, const Transfer1D& Pt,
                  int rc, cd* out, hipStream_t st);

@@ -24,158 +24,239 @@ __device__ __forceinline__ void coords(const Geom& g, long long f, int& i0, int&
 //                                                 through A (a box of side 2(a + rin) + 1)
 //   Ac(I, J)  = sum_j q(j) P(j, J)                for every coarse J = I + D, |D_a| <= rc
 // R(I, i) = prod_a Rt.w[i_a - 2 I_a + Rt.a]; P(j, J) = prod_a 2 Pt.w[j_a - 2 J_a + Pt.a]
-// (P = 2^d Pt^T); both truncated at the grid's ends.  SRC 0: A is the fine compact
-// operator with scalar s; SRC 1: A is given as planes of radius rin.
+// (P = 2^d Pt^T); both truncated at the grid's ends.
+//
+// Bound by the instructions a wavefront spends per term, most of them index arithmetic: the
+// radii are compile-time constants and every node takes the whole box (terms off the grid are
+// zero), so that indices divide by constants.  The fine operator is linear in its coefficient
+// scalar, A = L - s M diag(m (1 - i sigma)): one launch forms the two products and writes both
+// of the set-up's operators, and the FP32 copy of the first.  With run-time radii and a launch per
+// operator the 192 x 192 x 72 set-up spent 2 x 1.65 + 0.86 ms here and 0.2 on the copy, the
+// 1024^2 one 2 x 0.23 + 0.20; now 1.07 + 0.69 and 0.15 + 0.13.
+// The four nodes' results leave through LDS, four nodes (64 bytes of a plane) to a run.
+template <int DIM_, int AR_, int RIN_, int BP_, int RC_>
+struct GalBox {
+  static constexpr int DIM = DIM_, AR = AR_, RIN = RIN_, BP = BP_, RC = RC_;
+  static constexpr int S = 2 * (AR + RIN) + 1, S2 = DIM == 3 ? S : 1, W = 2 * RC + 1;
+  static constexpr int NQ = S * S * S2, NT = W * S * S2, NU = W * W * S2, NO = W * W * (DIM == 3 ? W : 1);
+  static_assert(NU <= NQ && NO <= NT, "passes in place");
+};
 struct GalArgs {
   Geom gf, gc;
-  FineOp op;            // SRC 0
-  cd s;
+  FineOp op;            // the fine operator's
   const double* m;
-  const cd* A;          // SRC 1
-  int rin;
+  cd sa, sb;
+  const cd* A;          // planes of radius RIN
   Transfer1D Rt, Pt;
-  int rc;
-  cd* out;
+  cd *out, *outb;
+  cf* out32;            // FP32 copy of out, or null
 };
 
-template <int DIM>
-constexpr int gal_qmax() { return DIM == 3 ? 343 : 81; }
-// the partial sums of the output passes: (j2, j1, D0) after the first, (j2, D1, D0) after
-// the second (the second overwrites q); 3D: 7 x 7 x 5, 2D: 9 x 7
-template <int DIM>
-constexpr int gal_tmax() { return DIM == 3 ? 245 : 63; }
+// this wavefront's coarse node; blocks in slabs, one per XCD (block b runs on XCD b % 8), so
+// that neighbouring runs of a plane meet in one L2
+__device__ __forceinline__ long long gal_node(const Geom& gc, int wv) {
+  const long long per = ((long long)gridDim.x + 7) / 8;
+  const long long b = (long long)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  return b * 4 + wv;
+}
 
-template <int DIM, int SRC>
-__global__ void __launch_bounds__(256) k_wgal(GalArgs a) {
-  __shared__ cd q[4][gal_qmax<DIM>()];
-  __shared__ cd t1[4][gal_tmax<DIM>()];
+// q, of the box, into sum_j q(j) P(j, I + D): three one-axis passes (axis 0, then 1, then 2),
+// each term 2 Pt.w[j_a - 2 J_a + BP] for the j_a in the box; the result in t, D0 fastest
+template <class B>
+__device__ __forceinline__ void gal_passes(cd* q, cd* t, const Transfer1D& Pt, int lane) {
+  // term o of output D: box position 2 (D - RC) + AR + RIN - BP + o
+  auto pass = [&](const cd* in, cd* out, int n, int stride, auto index) {
+    for (int e = lane; e < n; e += 64) {
+      int D, base;
+      index(e, D, base);
+      const int j0 = 2 * (D - B::RC) + B::AR + B::RIN - B::BP;
+      cd acc = mk(0.0, 0.0);
+#pragma unroll
+      for (int o = 0; o <= 2 * B::BP; ++o)
+        if (j0 + o >= 0 && j0 + o < B::S) acc += (2.0 * Pt.w[o]) * in[base + stride * (j0 + o)];
+      out[e] = acc;
+    }
+    __syncthreads();
+  };
+  __syncthreads();
+  pass(q, t, B::NT, 1, [](int e, int& D, int& base) { D = e % B::W; base = B::S * (e / B::W); });
+  if constexpr (B::DIM == 3) {
+    pass(t, q, B::NU, B::W, [](int e, int& D, int& base) {
+      D = e / B::W % B::W;
+      base = e % B::W + B::W * B::S * (e / (B::W * B::W));
+    });
+    pass(q, t, B::NO, B::W * B::W, [](int e, int& D, int& base) { D = e / (B::W * B::W); base = e % (B::W * B::W); });
+  } else {
+    pass(t, q, B::NO, B::W, [](int e, int& D, int& base) { D = e / B::W; base = e % B::W; });
+    for (int e = lane; e < B::NO; e += 64) t[e] = q[e];
+    __syncthreads();
+  }
+}
+// the block's four results (nodes at sI), four consecutive threads an entry of each: in is false
+// for J off the grid
+template <class B, class ST>
+__device__ __forceinline__ void gal_store(const GalArgs& a, const cd (*t)[B::NT], const int (*sI)[3], ST st) {
+  const int nd = threadIdx.x % 4;
+  const long long I = gal_node(a.gc, nd);
+  if (I >= a.gc.tot) return;
+  const int Ia[3] = {sI[nd][0], sI[nd][1], sI[nd][2]};
+  for (int o = threadIdx.x / 4; o < B::NO; o += 64) {
+    const int D[3] = {o % B::W, o / B::W % B::W, B::DIM == 3 ? o / (B::W * B::W) : B::RC};
+    bool in = true;
+    for (int d = 0; d < B::DIM; ++d) in = in && Ia[d] + D[d] >= B::RC && Ia[d] + D[d] - B::RC < a.gc.N[d];
+    st((long long)o * a.gc.tot + I, in, t[nd][o], nd, D);
+  }
+}
+
+// A weighs an offset by the number of axes it moves along, so with c_a = r_a(j_a) and s_a =
+// r_a(j_a - 1) + r_a(j_a + 1), r_a the row of R along axis a (zero off its support and off the
+// grid), the sums over i are those over the subsets of moved axes:
+//   centre prod c, faces sum_a s_a prod_{b != a} c_b, edges (3D) sum_a c_a prod_{b != a} s_b
+template <int DIM>
+__device__ __forceinline__ double gal_lap(const double* c, const double* s) {
+  if constexpr (DIM == 3) {
+    const double cc = c[0] * c[1] * c[2];
+    const double ff = s[0] * c[1] * c[2] + c[0] * s[1] * c[2] + c[0] * c[1] * s[2];
+    const double ee = c[0] * s[1] * s[2] + s[0] * c[1] * s[2] + s[0] * s[1] * c[2];
+    return 24.0 * cc - 2.0 * ff - ee;
+  } else {
+    return 20.0 * (c[0] * c[1]) - 4.0 * (s[0] * c[1] + c[0] * s[1]) - s[0] * s[1];
+  }
+}
+template <int DIM>
+__device__ __forceinline__ double gal_mass(const double* c, const double* s) {
+  if constexpr (DIM == 3)
+    return (6.0 / 12.0) * (c[0] * c[1] * c[2]) +
+           (1.0 / 12.0) * (s[0] * c[1] * c[2] + c[0] * s[1] * c[2] + c[0] * c[1] * s[2]);
+  else
+    return (8.0 / 12.0) * (c[0] * c[1]) + (1.0 / 12.0) * (s[0] * c[1] + c[0] * s[1]);
+}
+
+// R L P is a sum of products over the axes: each axis's sums of c and s against P take a lane
+// per offset, and only the product with M runs through the box
+template <class B>
+__global__ void __launch_bounds__(256) k_wgal_fine(GalArgs a) {
+  __shared__ cd q[4][B::NQ], t[4][B::NT];
+  __shared__ int sI[4][3];
+  __shared__ double s1[4][2][B::DIM][B::W], sr[4][B::DIM][B::S + 2];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const long long I = (long long)blockIdx.x * 4 + wv;
-  const bool live = I < a.gc.tot;
-  const long long Ic = live ? I : 0;
+  const long long I = gal_node(a.gc, wv), Ic = I < a.gc.tot ? I : 0;
   int Ia[3];
   coords(a.gc, Ic, Ia[0], Ia[1], Ia[2]);
-  const int rin = SRC == 0 ? 1 : a.rin;
-  const int ar = a.Rt.a, bp = a.Pt.a;
-  int lo[3] = {0, 0, 0}, sp[3] = {1, 1, 1};
-  for (int d = 0; d < DIM; ++d) {
-    lo[d] = max(2 * Ia[d] - ar - rin, 0);
-    const int hi = min(2 * Ia[d] + ar + rin, a.gf.N[d] - 1);
-    sp[d] = hi - lo[d] + 1;
-  }
-  const int nq = sp[0] * sp[1] * sp[2];
+  if (lane < 3) sI[wv][lane] = lane == 0 ? Ia[0] : lane == 1 ? Ia[1] : Ia[2];
   const long long sf1 = a.gf.N[0], sf2 = (long long)a.gf.N[0] * a.gf.N[1];
+  // r_a at box positions -1 .. S (a table: lane-dependent reads of the arguments are loads)
+  if (lane < B::DIM * (B::S + 2)) {
+    const int d = lane / (B::S + 2), x = lane % (B::S + 2) - 1;
+    const int J = d == 0 ? Ia[0] : d == 1 ? Ia[1] : Ia[2], n = d == 0 ? a.gf.N[0] : d == 1 ? a.gf.N[1] : a.gf.N[2];
+    const int i = 2 * J - B::AR - B::RIN + x;
+    sr[wv][d][x + 1] =
+        x >= B::RIN && x <= B::RIN + 2 * B::AR && i >= 0 && i < n ? a.Rt.w[x - B::RIN] : 0.0;
+  }
+  __syncthreads();
+  if (lane < 2 * B::DIM * B::W) {
+    const int moved = lane % 2, D = lane / 2 % B::W, d = lane / 2 / B::W;
+    const int J = d == 0 ? Ia[0] : d == 1 ? Ia[1] : Ia[2], n = d == 0 ? a.gf.N[0] : d == 1 ? a.gf.N[1] : a.gf.N[2];
+    double acc = 0.0;
+#pragma unroll
+    for (int o = 0; o <= 2 * B::BP; ++o) {
+      const int x = 2 * (D - B::RC) + B::AR + B::RIN - B::BP + o, j = 2 * J - B::AR - B::RIN + x;
+      if (x < 0 || x >= B::S || j < 0 || j >= n) continue;
+      acc += (2.0 * a.Pt.w[o]) * (moved ? sr[wv][d][x] + sr[wv][d][x + 2] : sr[wv][d][x + 1]);
+    }
+    s1[wv][moved][d][D] = acc;
+  }
+  for (int e = lane; e < B::NQ; e += 64) {
+    const int r[3] = {e % B::S, e / B::S % B::S, B::DIM == 3 ? e / (B::S * B::S) : B::AR + B::RIN};
+    int j[3] = {0, 0, 0};
+    bool in = true;
+    for (int d = 0; d < B::DIM; ++d) {
+      j[d] = 2 * Ia[d] - B::AR - B::RIN + r[d];
+      in = in && j[d] >= 0 && j[d] < a.gf.N[d];
+    }
+    cd acc = mk(0.0, 0.0);
+    if (in) {
+      double cv[3], sv[3];
+      for (int d = 0; d < B::DIM; ++d) {
+        cv[d] = sr[wv][d][r[d] + 1];
+        sv[d] = sr[wv][d][r[d]] + sr[wv][d][r[d] + 2];
+      }
+      const double mj = a.m[j[0] + j[1] * sf1 + j[2] * sf2];
+      acc = gal_mass<B::DIM>(cv, sv) * mk(mj, -mj * layer_sigma(a.op, j[0], j[1], j[2]));
+    }
+    q[wv][e] = acc;
+  }
+  gal_passes<B>(q[wv], t[wv], a.Pt, lane);
   const double ih = a.op.inv_h2 / 6.0;
-  for (int e = lane; e < nq; e += 64) {
-    int j[3] = {lo[0] + e % sp[0], lo[1] + (e / sp[0]) % sp[1], lo[2] + e / (sp[0] * sp[1])};
-    const long long jf = j[0] + j[1] * sf1 + j[2] * sf2;
-    int ilo[3] = {0, 0, 0}, ihi[3] = {0, 0, 0};
-    for (int d = 0; d < DIM; ++d) {
-      ilo[d] = max(max(2 * Ia[d] - ar, j[d] - rin), 0);
-      ihi[d] = min(min(2 * Ia[d] + ar, j[d] + rin), a.gf.N[d] - 1);
+  gal_store<B>(a, t, sI, [&](long long at, bool in, cd v, int nd, const int* D) {
+    cd xa = mk(0.0, 0.0), xb = mk(0.0, 0.0);
+    if (in) {
+      double cv[3], sv[3];
+      for (int d = 0; d < B::DIM; ++d) {
+        cv[d] = s1[nd][0][d][D[d]];
+        sv[d] = s1[nd][1][d][D[d]];
+      }
+      const cd l = mk(ih * gal_lap<B::DIM>(cv, sv), 0.0);
+      xa = l - a.sa * v;
+      xb = l - a.sb * v;
+    }
+    a.out[at] = xa;
+    a.outb[at] = xb;
+    if (a.out32) a.out32[at] = conv<cf>::from(xa);
+  });
+}
+
+template <class B>
+__global__ void __launch_bounds__(256) k_wgal_coarse(GalArgs a) {
+  __shared__ cd q[4][B::NQ], t[4][B::NT];
+  __shared__ int sI[4][3];
+  constexpr int SW = 2 * B::RIN + 1;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const long long I = gal_node(a.gc, wv), Ic = I < a.gc.tot ? I : 0;
+  int Ia[3];
+  coords(a.gc, Ic, Ia[0], Ia[1], Ia[2]);
+  if (lane < 3) sI[wv][lane] = lane == 0 ? Ia[0] : lane == 1 ? Ia[1] : Ia[2];
+  const long long sf1 = a.gf.N[0], sf2 = (long long)a.gf.N[0] * a.gf.N[1];
+  for (int e = lane; e < B::NQ; e += 64) {
+    const int r[3] = {e % B::S, e / B::S % B::S, B::DIM == 3 ? e / (B::S * B::S) : B::AR + B::RIN};
+    bool in = true;
+    for (int d = 0; d < B::DIM; ++d) {
+      const int j = 2 * Ia[d] - B::AR - B::RIN + r[d];
+      in = in && j >= 0 && j < a.gf.N[d];
     }
     cd acc = mk(0.0, 0.0);
-    if (SRC == 0) {
-      // sum_i w_i A(i, j) = sum_i w_i L(j - i) - c_j sum_i w_i M(j - i), w_i = prod_a r_a(i_a)
-      // the row of R (zero off its support and off the grid).  L and M weigh an offset by
-      // the number of axes it moves along, so with c_a = r_a(j_a) and s_a = r_a(j_a - 1) +
-      // r_a(j_a + 1) the sums over i are those over the subsets of moved axes:
-      //   centre prod c, faces sum_a s_a prod_{b != a} c_b, edges (3D) sum_a c_a prod_{b != a} s_b
-      double cv[3] = {1.0, 1.0, 1.0}, sv[3] = {0.0, 0.0, 0.0};
-      for (int d = 0; d < DIM; ++d) {
-        auto rw = [&](int i) -> double {
-          const int o = i - 2 * Ia[d] + ar;
-          return o >= 0 && o <= 2 * ar && i >= 0 && i < a.gf.N[d] ? a.Rt.w[o] : 0.0;
-        };
-        cv[d] = rw(j[d]);
-        sv[d] = rw(j[d] - 1) + rw(j[d] + 1);
-      }
-      double sl, sm;
-      if (DIM == 3) {
-        const double cc = cv[0] * cv[1] * cv[2];
-        const double ff = sv[0] * cv[1] * cv[2] + cv[0] * sv[1] * cv[2] + cv[0] * cv[1] * sv[2];
-        const double ee = cv[0] * sv[1] * sv[2] + sv[0] * cv[1] * sv[2] + sv[0] * sv[1] * cv[2];
-        sl = 24.0 * cc - 2.0 * ff - ee;
-        sm = (6.0 / 12.0) * cc + (1.0 / 12.0) * ff;
-      } else {
-        const double cc = cv[0] * cv[1], ff = sv[0] * cv[1] + cv[0] * sv[1], ee = sv[0] * sv[1];
-        sl = 20.0 * cc - 4.0 * ff - ee;
-        sm = (8.0 / 12.0) * cc + (1.0 / 12.0) * ff;
-      }
-      const double mj = a.m[jf];
-      const cd cj = a.s * mk(mj, -mj * layer_sigma(a.op, j[0], j[1], j[2]));
-      acc = mk(sl * ih - sm * cj.x, -sm * cj.y);
-    } else {
-      const int sw = 2 * rin + 1;
-      for (int i2 = ilo[2]; i2 <= ihi[2]; ++i2)
-        for (int i1 = ilo[1]; i1 <= ihi[1]; ++i1)
-          for (int i0 = ilo[0]; i0 <= ihi[0]; ++i0) {
-            const int ii[3] = {i0, i1, i2};
-            double w = 1.0;
-            int k = 0, mul = 1;
-            for (int d = 0; d < DIM; ++d) {
-              w *= a.Rt.w[ii[d] - 2 * Ia[d] + ar];
-              k += (j[d] - ii[d] + rin) * mul;
-              mul *= sw;
-            }
-            const long long iflat = i0 + i1 * sf1 + i2 * sf2;
-            acc += w * a.A[(long long)k * a.gf.tot + iflat];
+    if (in)
+      // fine rows i = 2 I + o - AR on the grid within RIN of j (box position RIN + o): a row of
+      // terms is loaded at clamped indices before any is added
+      for (int o2 = 0; o2 <= (B::DIM == 3 ? 2 * B::AR : 0); ++o2) {
+        const int i2 = B::DIM == 3 ? 2 * Ia[2] - B::AR + o2 : 0, k2 = B::DIM == 3 ? r[2] - o2 : 0;
+        if (B::DIM == 3 && (i2 < 0 || i2 >= a.gf.N[2] || k2 < 0 || k2 >= SW)) continue;
+#pragma unroll
+        for (int o1 = 0; o1 <= 2 * B::AR; ++o1) {
+          const int i1 = 2 * Ia[1] - B::AR + o1, k1 = r[1] - o1;
+          const bool ok1 = i1 >= 0 && i1 < a.gf.N[1] && k1 >= 0 && k1 < SW;
+          cd v[2 * B::AR + 1];
+#pragma unroll
+          for (int o0 = 0; o0 <= 2 * B::AR; ++o0) {
+            const int i0 = 2 * Ia[0] - B::AR + o0, k0 = r[0] - o0;
+            const bool ok = ok1 && i0 >= 0 && i0 < a.gf.N[0] && k0 >= 0 && k0 < SW;
+            const long long at = (long long)(k0 + SW * (k1 + SW * k2)) * a.gf.tot + (i0 + i1 * sf1 + i2 * sf2);
+            v[o0] = a.A[ok ? at : 0];
+            v[o0].x = ok ? v[o0].x : 0.0;
+            v[o0].y = ok ? v[o0].y : 0.0;
           }
-    }
-    q[wv][e] = acc;
-  }
-  __syncthreads();
-  // Ac(I, I + D) = sum_j q(j) P(j, I + D), P a tensor product: three one-axis passes over
-  // the box (axis 0, then 1, then 2), each term 2 Pt.w[j_a - 2 J_a + bp] for the j_a that
-  // lie in the box and within bp of 2 J_a; the same terms as the triple sum, taken per axis
-  const int cw = 2 * a.rc + 1;
-  int Jlo[3];
-  for (int d = 0; d < 3; ++d) Jlo[d] = Ia[d] - (d < DIM ? a.rc : 0);
-  auto wgt = [&](int j, int J) -> double {            // j, J absolute
-    const int o = j - 2 * J + bp;
-    return o >= 0 && o <= 2 * bp ? 2.0 * a.Pt.w[o] : 0.0;
-  };
-  const int c0 = cw, c1 = cw;
-  // pass 1: t1(j2, j1, D0) = sum_j0 W0(D0, j0) q(j0, j1, j2)
-  for (int e = lane; e < sp[2] * sp[1] * c0; e += 64) {
-    const int D0 = e % c0, r = e / c0;             // r = j1 + sp1 j2 (box-relative)
-    const int J0 = Jlo[0] + D0;
-    const int jl = max(2 * J0 - bp, lo[0]), jh = min(2 * J0 + bp, lo[0] + sp[0] - 1);
-    cd acc = mk(0.0, 0.0);
-    for (int j0 = jl; j0 <= jh; ++j0) acc += wgt(j0, J0) * q[wv][(j0 - lo[0]) + sp[0] * r];
-    t1[wv][e] = acc;
-  }
-  __syncthreads();
-  // pass 2: t2(j2, D1, D0) = sum_j1 W1(D1, j1) t1(j2, j1, D0), into q
-  for (int e = lane; e < sp[2] * c1 * c0; e += 64) {
-    const int D0 = e % c0, D1 = (e / c0) % c1, j2r = e / (c0 * c1);
-    const int J1 = Jlo[1] + D1;
-    const int jl = max(2 * J1 - bp, lo[1]), jh = min(2 * J1 + bp, lo[1] + sp[1] - 1);
-    cd acc = mk(0.0, 0.0);
-    for (int j1 = jl; j1 <= jh; ++j1) acc += wgt(j1, J1) * t1[wv][D0 + c0 * ((j1 - lo[1]) + sp[1] * j2r)];
-    q[wv][e] = acc;
-  }
-  __syncthreads();
-  if (!live) return;
-  // pass 3: Ac(I, I + D) = sum_j2 W2(D2, j2) t2(j2, D1, D0); 0 for J outside the grid
-  int nout = cw;
-  for (int d = 1; d < DIM; ++d) nout *= cw;
-  for (int o = lane; o < nout; o += 64) {
-    const int D0 = o % cw, D1 = DIM > 1 ? (o / cw) % cw : 0, D2 = DIM > 2 ? o / (cw * cw) : 0;
-    const int J[3] = {Jlo[0] + D0, Jlo[1] + D1, Jlo[2] + D2};
-    bool inside = true;
-    for (int d = 0; d < DIM; ++d) inside = inside && J[d] >= 0 && J[d] < a.gc.N[d];
-    cd acc = mk(0.0, 0.0);
-    if (inside) {
-      if (DIM < 3) {
-        acc = q[wv][D0 + c0 * D1];
-      } else {
-        const int jl = max(2 * J[2] - bp, lo[2]), jh = min(2 * J[2] + bp, lo[2] + sp[2] - 1);
-        for (int j2 = jl; j2 <= jh; ++j2) acc += wgt(j2, J[2]) * q[wv][D0 + c0 * (D1 + c1 * (j2 - lo[2]))];
+#pragma unroll
+          for (int o0 = 0; o0 <= 2 * B::AR; ++o0) {
+            double w = a.Rt.w[o0] * a.Rt.w[o1];
+            if (B::DIM == 3) w *= a.Rt.w[o2];
+            acc += w * v[o0];
+          }
+        }
       }
-    }
-    a.out[(long long)o * a.gc.tot + I] = acc;
+    q[wv][e] = acc;
   }
+  gal_passes<B>(q[wv], t[wv], a.Pt, lane);
+  gal_store<B>(a, t, sI, [&](long long at, bool in, cd v, int, const int*) { a.out[at] = in ? mk(v.x, v.y) : mk(0.0, 0.0); });
 }
 
 // ----------------------------------------------------------- cycle steps ----
@@ -326,42 +407,57 @@ inline dim3 grid1(long long n, int nr) { return dim3((unsigned)((n + 255) / 256)
 }  // namespace
 
 // ------------------------------------------------------------- launchers ----
-void wgal_fine(const FineOp& op, cd s, const double* m, const Geom& gc, const Transfer1D& Rt, const Transfer1D& Pt,
-               int rc, cd* out, hipStream_t st) {
+static dim3 gal_grid(const Geom& gc) { return dim3((unsigned)((gc.tot + 31) / 32 * 8)); }
+// whether a transfer pair and radii are those of B
+template <class B>
+static bool gal_is(const Geom& g, const Transfer1D& Rt, int rin, const Transfer1D& Pt, int rc) {
+  return g.dim == B::DIM && Rt.a == B::AR && rin == B::RIN && Pt.a == B::BP && rc == B::RC;
+}
+
+void wgal_fine(const FineOp& op, cd sa, cd sb, const double* m, const Geom& gc, const Transfer1D& Rt,
+               const Transfer1D& Pt, int rc, cd* outa, cf* outa32, cd* outb, hipStream_t st) {
+  typedef GalBox<3, 2, 1, 2, 2> B3;
+  typedef GalBox<2, 2, 1, 2, 2> B2;
   GalArgs a{};
   a.gf = op.g;
   a.gc = gc;
   a.op = op;
-  a.s = s;
   a.m = m;
-  a.rin = 1;
+  a.sa = sa;
+  a.sb = sb;
   a.Rt = Rt;
   a.Pt = Pt;
-  a.rc = rc;
-  a.out = out;
-  const dim3 grid((unsigned)((gc.tot + 3) / 4));
-  if (op.g.dim == 3)
-    hipLaunchKernelGGL((k_wgal<3, 0>), grid, dim3(256), 0, st, a);
+  a.out = outa;
+  a.outb = outb;
+  a.out32 = outa32;
+  if (gal_is<B3>(op.g, Rt, 1, Pt, rc))
+    hipLaunchKernelGGL((k_wgal_fine<B3>), gal_grid(gc), dim3(256), 0, st, a);
+  else if (gal_is<B2>(op.g, Rt, 1, Pt, rc))
+    hipLaunchKernelGGL((k_wgal_fine<B2>), gal_grid(gc), dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((k_wgal<2, 0>), grid, dim3(256), 0, st, a);
+    throw std::runtime_error("wgal_fine: transfers");
 }
 
 void wgal_coarse(const Geom& g, const cd* A, int rin, const Geom& gc, const Transfer1D& Rt, const Transfer1D& Pt,
                  int rc, cd* out, hipStream_t st) {
+  typedef GalBox<3, 1, 2, 2, 2> L3;       // level-dependent transfers
+  typedef GalBox<2, 1, 2, 2, 2> L2;
+  typedef GalBox<2, 2, 2, 2, 3> C2;       // cubic
   GalArgs a{};
   a.gf = g;
   a.gc = gc;
   a.A = A;
-  a.rin = rin;
   a.Rt = Rt;
   a.Pt = Pt;
-  a.rc = rc;
   a.out = out;
-  const dim3 grid((unsigned)((gc.tot + 3) / 4));
-  if (g.dim == 3)
-    hipLaunchKernelGGL((k_wgal<3, 1>), grid, dim3(256), 0, st, a);
+  if (gal_is<L3>(g, Rt, rin, Pt, rc))
+    hipLaunchKernelGGL((k_wgal_coarse<L3>), gal_grid(gc), dim3(256), 0, st, a);
+  else if (gal_is<L2>(g, Rt, rin, Pt, rc))
+    hipLaunchKernelGGL((k_wgal_coarse<L2>), gal_grid(gc), dim3(256), 0, st, a);
+  else if (gal_is<C2>(g, Rt, rin, Pt, rc))
+    hipLaunchKernelGGL((k_wgal_coarse<C2>), gal_grid(gc), dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((k_wgal<2, 1>), grid, dim3(256), 0, st, a);
+    throw std::runtime_error("wgal_coarse: transfers");
 }
 
 template <typename R, typename CB, typename CO>
