@@ -787,7 +787,7 @@ struct Cycle {
     // the 2D cycle with one pre- and one post-sweep sweeps in the fused kernels (l2_chain,
     // cycle_tail) except where several instances share the device: there the separate sweeps
     // keep the boxes whose rounding the fused ones share, so that a batch's solutions are
-    // those of its single solves, bit by bit (16 x 16 boxes differ in the last place); nor
+    // those of its single solves, bit by bit (in FP64 other boxes can differ in the last place); nor
     // does such a device, already full, gain from the small restrictions (167.8 / 166.7 ms
     // for 6 instances of 8 right-hand sides)
     A1.small_sweep = A2.small_sweep = !(c->g2.dim == 2 && c->mg.nu_pre == 1 && c->mg.nu_post == 1);

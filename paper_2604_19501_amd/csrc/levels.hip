@@ -26,10 +26,30 @@ namespace helm {
 // a / d for the Jacobi updates: in the FP32 cycle one hardware reciprocal of |d|^2 (about
 // 1 ulp) replaces two IEEE divisions; FP64 keeps the exact quotient
 __device__ __forceinline__ cf jdiv(cf a, cf d) {
-  const float r = __builtin_amdgcn_rcpf(d.x * d.x + d.y * d.y);
-  return mk((a.x * d.x + a.y * d.y) * r, (a.y * d.x - a.x * d.y) * r);
+  const float r = __builtin_amdgcn_rcpf(fmaf(d.y, d.y, d.x * d.x));
+  return mk(fmaf(a.y, d.y, a.x * d.x) * r, fmaf(-a.x, d.y, a.y * d.x) * r);
 }
-__device__ __forceinline__ cd jdiv(cd a, cd d) { return cdiv(a, d); }
+__device__ __forceinline__ cd jdiv(cd a, cd d) {
+  const double r = fma(d.y, d.y, d.x * d.x);
+  return mk(fma(a.y, d.y, a.x * d.x) / r, fma(-a.x, d.y, a.y * d.x) / r);
+}
+// Products and sums of the level kernels as stated FMAs: left to the compiler, two kernels that
+// take the same sums would round differently wherever it contracts them differently.
+__device__ __forceinline__ float sfma(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double sfma(double a, double b, double c) { return fma(a, b, c); }
+// a b, c + a b, and x + w z for a real w
+template <class C>
+__device__ __forceinline__ C cmulf(C a, C b) {
+  return mk(sfma(-a.y, b.y, a.x * b.x), sfma(a.x, b.y, a.y * b.x));
+}
+template <class C>
+__device__ __forceinline__ C cfma(C c, C a, C b) {
+  return mk(sfma(-a.y, b.y, sfma(a.x, b.x, c.x)), sfma(a.y, b.x, sfma(a.x, b.y, c.y)));
+}
+template <class C, class R>
+__device__ __forceinline__ C axpy(C x, R w, C z) {
+  return mk(sfma(w, z.x, x.x), sfma(w, z.y, x.y));
+}
 
 // contiguous-slab block order: hardware dispatches block b to XCD b % 8
 __device__ __forceinline__ long long xcd_block(long long nblocks) {
@@ -143,14 +163,14 @@ struct Op1 {
   __device__ __forceinline__ C ax(const C* xs, int k, int sy, int sz, long long, C D) const {
     C nb = (xs[k - 1] + xs[k + 1]) + (xs[k - sy] + xs[k + sy]);
     if (DIM == 3) nb += xs[k - sz] + xs[k + sz];
-    return D * xs[k] - (R)A.op.inv_h2 * nb;
+    return axpy(cmulf(D, xs[k]), -(R)A.op.inv_h2, nb);
   }
   // 3D, the planes below / at / above the node staged apart (z-marching tiles); the same
   // sums in the same order as ax
   __device__ __forceinline__ C ax3(const C* xm, const C* x0, const C* xp, int k, int sy, long long, C D) const {
     C nb = (x0[k - 1] + x0[k + 1]) + (x0[k - sy] + x0[k + sy]);
     nb += xm[k] + xp[k];
-    return D * x0[k] - (R)A.op.inv_h2 * nb;
+    return axpy(cmulf(D, x0[k]), -(R)A.op.inv_h2, nb);
   }
 };
 
@@ -169,7 +189,7 @@ struct Op2 {
   __device__ __forceinline__ Aux aux(long long f) const { return coef_at(DIM == 2 ? 4 : 13, f); }
   __device__ __forceinline__ C diag_aux(Aux d, int, int, int) const { return d; }
   __device__ __forceinline__ C ax(const C* xs, int k, int sy, int sz, long long f, C D) const {
-    C acc = D * xs[k];
+    C acc = cmulf(D, xs[k]);
 #pragma unroll
     for (int d2 = (DIM == 3 ? -1 : 0); d2 <= (DIM == 3 ? 1 : 0); ++d2)
 #pragma unroll
@@ -178,12 +198,12 @@ struct Op2 {
         for (int d0 = -1; d0 <= 1; ++d0) {
           if (d0 == 0 && d1 == 0 && d2 == 0) continue;
           const int kk = (d0 + 1) + 3 * (d1 + 1) + (DIM == 3 ? 9 * (d2 + 1) : 0);
-          acc += coef_at(kk, f) * xs[k + d0 + sy * d1 + sz * d2];
+          acc = cfma(acc, coef_at(kk, f), xs[k + d0 + sy * d1 + sz * d2]);
         }
     return acc;
   }
   __device__ __forceinline__ C ax3(const C* xm, const C* x0, const C* xp, int k, int sy, long long f, C D) const {
-    C acc = D * x0[k];
+    C acc = cmulf(D, x0[k]);
 #pragma unroll
     for (int d2 = -1; d2 <= 1; ++d2)
 #pragma unroll
@@ -193,7 +213,7 @@ struct Op2 {
           if (d0 == 0 && d1 == 0 && d2 == 0) continue;
           const int kk = (d0 + 1) + 3 * (d1 + 1) + 9 * (d2 + 1);
           const C* pl = d2 < 0 ? xm : d2 > 0 ? xp : x0;
-          acc += coef_at(kk, f) * pl[k + d0 + sy * d1];
+          acc = cfma(acc, coef_at(kk, f), pl[k + d0 + sy * d1]);
         }
     return acc;
   }
@@ -287,7 +307,7 @@ __device__ __forceinline__ void stage_xin(const Op& op, const C* __restrict__ x,
       C v = mk((R)0, (R)0);
       if (XIN & XIN_X) v += rx[(XIN & XIN_X) ? u : 0];
       if (XIN & XIN_Z)
-        v += w_in * jdiv(conv<C>::from(rb[(XIN & XIN_Z) ? u : 0]), op.diag_aux(ra[(XIN & XIN_Z) ? u : 0], j0, j1, j2));
+        v = axpy(v, w_in, jdiv(conv<C>::from(rb[(XIN & XIN_Z) ? u : 0]), op.diag_aux(ra[(XIN & XIN_Z) ? u : 0], j0, j1, j2)));
       if (XIN & XIN_E) v += prolong_lds<DIM>(es, ex, ey, c0, c1, c2, j0, j1, j2);
       if (!inside(g, i0, i1, i2)) v = mk((R)0, (R)0);
       if ((int)threadIdx.x + 256 * u < tot) xs[k] = v;
@@ -306,7 +326,7 @@ __device__ __forceinline__ void stage_xin(const Op& op, const C* __restrict__ x,
       const int f = flat(g, j0, j1, j2);
       C v = mk((R)0, (R)0);
       if (XIN & XIN_X) v += x[f];
-      if (XIN & XIN_Z) v += w_in * jdiv(conv<C>::from(b[f]), op.diag(f, j0, j1, j2));
+      if (XIN & XIN_Z) v = axpy(v, w_in, jdiv(conv<C>::from(b[f]), op.diag(f, j0, j1, j2)));
       if (XIN & XIN_E) v += prolong_lds<DIM>(es, ex, ey, c0, c1, c2, j0, j1, j2);
       if (!inside(g, i0, i1, i2)) v = mk((R)0, (R)0);
       if ((int)threadIdx.x + 256 * it < tot) xs[k] = v;
@@ -395,7 +415,7 @@ __global__ void __launch_bounds__(256) k_sweep(Op op, const typename Op::C* __re
       clamp_node(g, j0, j1, j2);
       C v = prolong_lds<DIM>(es, EX, EY, c0, c1, c2, j0, j1, j2);
       if (XIN & XIN_X) v += rx[it];
-      if (XIN & XIN_Z) v += w_in * jdiv(conv<C>::from(rb[it]), op.diag_aux(ra[it], j0, j1, j2));
+      if (XIN & XIN_Z) v = axpy(v, w_in, jdiv(conv<C>::from(rb[it]), op.diag_aux(ra[it], j0, j1, j2)));
       if (!inside(g, i0, i1, i2)) v = mk((R)0, (R)0);
       if ((int)threadIdx.x + 256 * it < STOT) xs[k] = v;
     }
@@ -413,7 +433,7 @@ __global__ void __launch_bounds__(256) k_sweep(Op op, const typename Op::C* __re
     const int f = flat(g, i0, i1, i2);
     const int kk = (a + 1) + SX * ((q % TY + 1) + SY * (DIM == 3 ? q / TY + 1 : 0));
     const C r = bo[it] - op.ax(xs, kk, SX, SX * SY, f, Do[it]);
-    out[f] = conv<CO>::from(xs[kk] + w * jdiv(r, Do[it]));
+    out[f] = conv<CO>::from(axpy(xs[kk], w, jdiv(r, Do[it])));
   }
 }
 
@@ -614,7 +634,7 @@ __global__ void __launch_bounds__(256) k_sweep_z(Op op, const typename Op::C* __
       const C bb = conv<C>::from(rb[s][u]);
       C v = mk((R)0, (R)0);
       if (XIN & XIN_X) v += rx[s][u];
-      if (XIN & XIN_Z) v += w_in * jdiv(bb, D);
+      if (XIN & XIN_Z) v = axpy(v, w_in, jdiv(bb, D));
       if (XIN & XIN_E) v += prolong_lds<3>(es, EX, EY, c0, c1, c2, sl[u].j0, sl[u].j1, jz);
       if (!(sl[u].in && inz)) v = mk((R)0, (R)0);
       if ((int)threadIdx.x + 256 * u < PL) dst[sl[u].k] = v;
@@ -646,7 +666,7 @@ __global__ void __launch_bounds__(256) k_sweep_z(Op op, const typename Op::C* __
       if (sl[u].own) {
         const int f = base + sl[u].fxy;
         const C r = bA[u] - op.ax3(xm, x0, xp, sl[u].k, SX, f, DA[u]);
-        out[f] = conv<CO>::from(x0[sl[u].k] + w * jdiv(r, DA[u]));
+        out[f] = conv<CO>::from(axpy(x0[sl[u].k], w, jdiv(r, DA[u])));
       }
       bA[u] = bB[u];
       DA[u] = DB[u];
@@ -723,7 +743,7 @@ __global__ void __launch_bounds__(256) k_restrict_z(Op op, const typename Op::C*
       const C bb = conv<C>::from(rb[s][u]);
       C v = mk((R)0, (R)0);
       if (XIN & XIN_X) v += rx[s][u];
-      if (XIN & XIN_Z) v += w_in * jdiv(bb, D);
+      if (XIN & XIN_Z) v = axpy(v, w_in, jdiv(bb, D));
       if (!(sl[u].in && inz)) v = mk((R)0, (R)0);
       if ((int)threadIdx.x + 256 * u < PL) dst[sl[u].k] = v;
       bo[u] = bb;
@@ -814,25 +834,26 @@ __global__ void __launch_bounds__(256) k_restrict_z(Op op, const typename Op::C*
 // halo of 3, xa = one Jacobi sweep of x0 on halo 2, xb = one sweep of xa on halo 1 (written
 // for the box's own fine nodes [2 O, 2 O + 2 C)), r = b - A xb on the footprint and
 // b3 = R r.  The sums are those of k_sweep and k_restrict, in their order.
-template <class Op, int XIN>
-__global__ void __launch_bounds__(256) k_l2_chain(Op op, const typename Op::C* __restrict__ x,
-                                                  const typename Op::C* __restrict__ b, typename Op::Real w_in,
-                                                  Geom gc, const typename Op::C* __restrict__ e, typename Op::Real w,
-                                                  typename Op::C* __restrict__ xb_out, typename Op::C* __restrict__ b3,
-                                                  TileGrid tg) {
+//
+// A node keeps its thread through all of them (NPT nodes each of the halo-3 footprint), so its
+// coefficients and right-hand side are read once, all in flight before the first barrier, and
+// what follows runs in LDS.  With 256 threads, each phase over its own nodes, the coefficients
+// were read three times, behind a barrier each.  Cycle in us, before / now: 128^2 48.5 / 44.0,
+// 256^2 FP64 63.5 / 58.5, 512^2 98 / 92.5, 768^2 130 / 126.
+template <class Op, int XIN, int NT>
+__global__ void __launch_bounds__(NT) k_l2_chain(Op op, const typename Op::C* __restrict__ x,
+                                                 const typename Op::C* __restrict__ b, typename Op::Real w_in,
+                                                 Geom gc, const typename Op::C* __restrict__ e, typename Op::Real w,
+                                                 typename Op::C* __restrict__ xb_out, typename Op::C* __restrict__ b3,
+                                                 TileGrid tg) {
   typedef typename Op::C C;
   typedef typename Op::Real R;
   constexpr int CX = RBox<2, 0>::x, CY = RBox<2, 0>::y;
-  constexpr int RX = 2 * CX + 1, RY = 2 * CY + 1;           // residual footprint
-  constexpr int AX = RX + 6, AY = RY + 6;                   // x0: halo 3
-  constexpr int BX = RX + 4, BY = RY + 4;                   // xa: halo 2
-  constexpr int DX = RX + 2, DY = RY + 2;                   // xb: halo 1
-  constexpr int EX = AX / 2 + 2, EY = AY / 2 + 2;           // e on x0's coarse footprint
+  constexpr int AX = 2 * CX + 7, AY = 2 * CY + 7;           // the residuals' footprint with a halo of 3
+  constexpr int EX = AX / 2 + 2, EY = AY / 2 + 2;           // e on its coarse footprint
+  constexpr int NPT = (AX * AY + NT - 1) / NT;
   __shared__ C es[EX * EY];
-  __shared__ C x0[AX * AY];
-  __shared__ C xa[BX * BY];
-  __shared__ C xb[DX * DY];
-  __shared__ C rs[RX * RY];
+  __shared__ C xs[AX * AY], ys[AX * AY];
   const Geom& g = op.geom();
   const long long ry = blockIdx.y;
   if (XIN & XIN_X) x += ry * g.tot;
@@ -842,9 +863,23 @@ __global__ void __launch_bounds__(256) k_l2_chain(Op op, const typename Op::C* _
   b3 += ry * gc.tot;
   int O0, O1, O2;
   if (!tile_origin(tg, CX, CY, 1, O0, O1, O2)) return;
-  const int f0 = 2 * O0 - 1, f1 = 2 * O1 - 1;               // the footprint's origin
-  const int c0 = (f0 - 3) >> 1, c1 = (f1 - 3) >> 1;         // floor: may be negative
-  for (int k = threadIdx.x; k < EX * EY; k += 256) {
+  const int f0 = 2 * O0 - 4, f1 = 2 * O1 - 4;               // the footprint's origin
+  const int c0 = f0 >> 1, c1 = f1 >> 1;                     // floor: may be negative
+  int fl[NPT], depth[NPT];                                  // node; how far inside the footprint (< 0: off the grid)
+  C bv[NPT], xv[NPT], cf9[NPT][9];
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    const int k = (int)threadIdx.x + NT * u, a = k % AX, q = k / AX;
+    int j0 = f0 + a, j1 = f1 + q, j2 = 0;
+    depth[u] = k >= AX * AY || !inside(g, j0, j1, 0) ? -1 : min(min(a, AX - 1 - a), min(q, AY - 1 - q));
+    clamp_node(g, j0, j1, j2);
+    fl[u] = flat(g, j0, j1, 0);
+    bv[u] = b[fl[u]];
+    if (XIN & XIN_X) xv[u] = x[fl[u]];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) cf9[u][c] = op.coef_at(c, fl[u]);
+  }
+  for (int k = threadIdx.x; k < EX * EY; k += NT) {
     const int j0 = c0 + k % EX, j1 = c1 + k / EX;
     int l0 = j0, l1 = j1, l2 = 0;
     clamp_node(gc, l0, l1, l2);
@@ -853,53 +888,63 @@ __global__ void __launch_bounds__(256) k_l2_chain(Op op, const typename Op::C* _
     es[k] = v;
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < AX * AY; k += 256) {
-    const int i0 = f0 - 3 + k % AX, i1 = f1 - 3 + k / AX;
-    int j0 = i0, j1 = i1, j2 = 0;
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    const int k = (int)threadIdx.x + NT * u;
+    if (k >= AX * AY) continue;
+    int j0 = f0 + k % AX, j1 = f1 + k / AX, j2 = 0;
     clamp_node(g, j0, j1, j2);
-    const int f = flat(g, j0, j1, 0);
     C v = prolong_lds<2>(es, EX, EY, c0, c1, 0, j0, j1, 0);
-    if (XIN & XIN_X) v += x[f];
-    if (XIN & XIN_Z) v += w_in * jdiv(b[f], op.diag(f, j0, j1, 0));
-    if (!inside(g, i0, i1, 0)) v = mk((R)0, (R)0);
-    x0[k] = v;
+    if (XIN & XIN_X) v += xv[u];
+    if (XIN & XIN_Z) v = axpy(v, w_in, jdiv(bv[u], cf9[u][4]));
+    if (depth[u] < 0) v = mk((R)0, (R)0);
+    xs[k] = v;
   }
   __syncthreads();
-  // one Jacobi sweep from src (stride sx, the node's centre at (a + 1, q + 1)) into dst
-  auto sweep = [&](const C* src, int sx, C* dst, int nx, int ny, int o0, int o1, bool write_out) {
-    for (int k = threadIdx.x; k < nx * ny; k += 256) {
-      const int a = k % nx, q = k / nx;
-      const int i0 = o0 + a, i1 = o1 + q;
+  // (A src) at the thread's node u, in the order of Op2::ax
+  auto ax = [&](const C* src, int k, int u) {
+    C acc = cmulf(cf9[u][4], src[k]);
+#pragma unroll
+    for (int d1 = -1; d1 <= 1; ++d1)
+#pragma unroll
+      for (int d0 = -1; d0 <= 1; ++d0) {
+        if (d0 == 0 && d1 == 0) continue;
+        acc = cfma(acc, cf9[u][(d0 + 1) + 3 * (d1 + 1)], src[k + d0 + AX * d1]);
+      }
+    return acc;
+  };
+  // xa on depth 1 and more, xb on depth 2 and more; zero off the grid
+  auto sweep = [&](const C* src, C* dst, int dep, bool write_out) {
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      const int k = (int)threadIdx.x + NT * u, a = k % AX, q = k / AX;
+      if (k >= AX * AY) continue;
       C v = mk((R)0, (R)0);
-      if (inside(g, i0, i1, 0)) {
-        const int f = flat(g, i0, i1, 0);
-        const C D = op.diag(f, i0, i1, 0);
-        const int kk = (a + 1) + sx * (q + 1);
-        const C r = b[f] - op.ax(src, kk, sx, 0, f, D);
-        v = src[kk] + w * jdiv(r, D);
-        if (write_out && i0 >= 2 * O0 && i0 < 2 * (O0 + CX) && i1 >= 2 * O1 && i1 < 2 * (O1 + CY)) xb_out[f] = v;
+      if (depth[u] >= dep) {
+        const C r = bv[u] - ax(src, k, u);
+        v = axpy(src[k], w, jdiv(r, cf9[u][4]));
+        if (write_out && a >= 4 && a < 4 + 2 * CX && q >= 4 && q < 4 + 2 * CY) xb_out[fl[u]] = v;
       }
       dst[k] = v;
     }
   };
-  sweep(x0, AX, xa, BX, BY, f0 - 2, f1 - 2, false);
+  sweep(xs, ys, 1, false);
   __syncthreads();
-  sweep(xa, BX, xb, DX, DY, f0 - 1, f1 - 1, true);
+  sweep(ys, xs, 2, true);
   __syncthreads();
-  for (int k = threadIdx.x; k < RX * RY; k += 256) {
-    const int a = k % RX, q = k / RX;
-    const int i0 = f0 + a, i1 = f1 + q;
+#pragma unroll
+  for (int u = 0; u < NPT; ++u) {
+    const int k = (int)threadIdx.x + NT * u;
+    if (k >= AX * AY) continue;
     C v = mk((R)0, (R)0);
-    if (inside(g, i0, i1, 0)) {
-      const int f = flat(g, i0, i1, 0);
-      const C D = op.diag(f, i0, i1, 0);
-      v = b[f];
-      v -= op.ax(xb, (a + 1) + DX * (q + 1), DX, 0, f, D);
+    if (depth[u] >= 3) {
+      v = bv[u];
+      v -= ax(xs, k, u);
     }
-    rs[k] = v;
+    ys[k] = v;
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < CX * CY; k += 256) {
+  for (int k = threadIdx.x; k < CX * CY; k += NT) {
     const int a = k % CX, q = k / CX;
     const int I0 = O0 + a, I1 = O1 + q;
     if (!inside(gc, I0, I1, 0)) continue;
@@ -910,7 +955,7 @@ __global__ void __launch_bounds__(256) k_l2_chain(Op op, const typename Op::C* _
 #pragma unroll
       for (int d0 = -1; d0 <= 1; ++d0) {
         const R w0 = d0 == 0 ? (R)0.5 : (R)0.25;
-        acc += (w0 * w1 * (R)1) * rs[(2 * a + 1 + d0) + RX * (2 * q + 1 + d1)];
+        acc += (w0 * w1 * (R)1) * ys[(2 * a + 4 + d0) + AX * (2 * q + 4 + d1)];
       }
     }
     b3[flat(gc, I0, I1, 0)] = acc;
@@ -981,7 +1026,7 @@ __global__ void __launch_bounds__(256) k_cycle_tail(Op1<2, R> o1, Op2<2, R> o2, 
       const C D = o2.diag(f, i0, i1, 0);
       const int kk = (a + 1) + YX * (q + 1);
       const C r = b2[f] - o2.ax(y2, kk, YX, 0, f, D);
-      v = y2[kk] + w2 * jdiv(r, D);
+      v = axpy(y2[kk], w2, jdiv(r, D));
     }
     e2s[k] = v;
   }
@@ -992,7 +1037,7 @@ __global__ void __launch_bounds__(256) k_cycle_tail(Op1<2, R> o1, Op2<2, R> o2, 
     clamp_node(g1, j0, j1, j2);
     const int f = flat(g1, j0, j1, 0);
     C v = prolong_lds<2>(e2s, EX, EY, c0, c1, 0, j0, j1, 0);
-    v += w1 * jdiv(conv<C>::from(b1[f]), o1.diag(f, j0, j1, 0));
+    v = axpy(v, w1, jdiv(conv<C>::from(b1[f]), o1.diag(f, j0, j1, 0)));
     if (!inside(g1, i0, i1, 0)) v = mk((R)0, (R)0);
     xs[k] = v;
   }
@@ -1006,7 +1051,7 @@ __global__ void __launch_bounds__(256) k_cycle_tail(Op1<2, R> o1, Op2<2, R> o2, 
     const C D = o1.diag(f, i0, i1, 0);
     const int kk = (a + 1) + SX * (q + 1);
     const C r = bo - o1.ax(xs, kk, SX, 0, f, D);
-    out[f] = conv<CO>::from(xs[kk] + w1 * jdiv(r, D));
+    out[f] = conv<CO>::from(axpy(xs[kk], w1, jdiv(r, D)));
   }
 }
 
@@ -1260,10 +1305,11 @@ void l2_chain(const L2<R>& A, int xin, const typename cplx<R>::type* x, const ty
               const Geom& gc, const typename cplx<R>::type* e, R w, typename cplx<R>::type* xb,
               typename cplx<R>::type* b3, int nrhs, hipStream_t s) {
   TileGrid tg = tiles(gc, RBox<2, 0>::x, RBox<2, 0>::y, 1);
-  dim3 grid(grid_tiles(tg), nrhs), blk(256);
+  constexpr int NT = 512;       // 1024 measured the same
+  dim3 grid(grid_tiles(tg), nrhs), blk(NT);
   if (xin == (XIN_Z | XIN_E))
-    hipLaunchKernelGGL((k_l2_chain<Op2<2, R>, XIN_Z | XIN_E>), grid, blk, 0, s, Op2<2, R>{A}, x, b, w_in, gc, e, w,
-                       xb, b3, tg);
+    hipLaunchKernelGGL((k_l2_chain<Op2<2, R>, XIN_Z | XIN_E, NT>), grid, blk, 0, s, Op2<2, R>{A}, x, b, w_in, gc, e,
+                       w, xb, b3, tg);
   else
     throw std::runtime_error("l2_chain: the chain starts from the virtual first sweep (xin Z | E)");
 }
