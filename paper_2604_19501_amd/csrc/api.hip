@@ -454,7 +454,10 @@ void build_plan(helm_ctx* c) {
     const char* v = getenv("HELM_ND_MERGE");
     std::string mv = v ? std::string(v) : (tuned && tn.has_merge ? tn.merge : std::string());
     if (!mv.empty() && mv != "none") mh = parse_list(mv.c_str());
-    if (!v && !tuned && !c->compact && (!d3 || N3 <= 12000))
+    // the merged levels are part of the default schedule as a whole: a leaf size or root limit
+    // from the environment is taken as given, with no level merged unless it says so
+    const bool given = getenv("HELM_ND_LEAF") || getenv("HELM_ND_ROOT");
+    if (!v && !tuned && !given && !c->compact && (!d3 || N3 <= 12000))
       for (int h = 1; h <= 40; ++h)
         if (d3 ? h % 2 : h % 3) mh.push_back(h);
   }

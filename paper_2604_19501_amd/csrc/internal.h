@@ -191,7 +191,7 @@ struct NDFrontDev {
   long long asm_off;    // assembly entries
   int asm_cnt;
   // leading dimensions of L and W: nF and nS rounded up to 128 bytes, with L_off and W_off
-  // multiples of 128 bytes, so that a column run of a row chunk starts on a cache line
+  // multiples of 128 bytes, so that a run of a column starts on a cache line
   int ldL, ldW;
   int pad;
 };
