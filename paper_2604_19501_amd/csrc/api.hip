@@ -182,6 +182,9 @@ struct helm_ctx {
   std::vector<Pending> pending;
   std::vector<hipEvent_t> evpool;
   int nd_win = 1024;            // rows of an inversion window of the factorisation (HELM_ND_WIN)
+  int nd_hwin = 0;              // the first height with a separator of several windows
+  double nd_growth = 1.0;       // largest multiplier of a window (HELM_ND_GROWTH)
+  bool nd_whole = false;        // the last factorisation took the pivots from whole separators
   bool tuned = false;           // schedule parameters came from the autotuner cache
   int nd_leaf = 0, nd_root = 0;  // nested-dissection leaf size and root merge limit in use
   // the compact fourth-order stack: restriction (tr) and interpolating-restriction (ip, P =
@@ -488,11 +491,13 @@ void build_plan(helm_ctx* c) {
   nd_plan(c->g3, leaf, merge, (int)c->ndsz, splitk, c->plan, mh, c->r3);
   // inversion windows of the factorisation: 16 to 1024 rows, a multiple of 16
   c->nd_win = std::max(16, std::min(1024, env_int("HELM_ND_WIN", 1024) / 16 * 16));
+  if (const char* g = getenv("HELM_ND_GROWTH")) c->nd_growth = std::max(0.0, atof(g));
   NDPlan& P = c->plan;
   c->hlist.clear();
   c->hlist_toff.clear();
   c->hlist_goff.clear();
   c->hinfo.clear();
+  c->nd_hwin = P.max_height + 1;
   c->T_elems = c->G_elems = 0;
   for (int h = 0; h <= P.max_height; ++h) {
     HeightInfo hi{};
@@ -511,6 +516,7 @@ void build_plan(helm_ctx* c) {
       hi.max_nB = std::max(hi.max_nB, f.nB);
       hi.max_wn = std::max(hi.max_wn, std::min(f.nS, win_size(f.nS, c->nd_win)));
       hi.max_nF = std::max(hi.max_nF, f.nF);
+      if (f.nS > c->nd_win) c->nd_hwin = std::min(c->nd_hwin, h);
     }
     hi.s_bytes = (long long)sizeof(cd) * goff;
     c->T_elems = std::max(c->T_elems, toff);
@@ -572,7 +578,7 @@ size_t carve(helm_ctx* c, void* ws) {
   d.hfr = cv.take<NDFrontDev>(c->hlist.size());   // the fronts in height order (factorisation)
   d.toff = cv.take<long long>(c->hlist_toff.size());
   d.goff = cv.take<long long>(c->hlist_goff.size());
-  d.err = cv.take<int>(1);
+  d.err = cv.take<int>(2);
   d.F = cv.take<cd>(P.F_total);
   d.T = cv.take<cd>(std::max<long long>(1, c->T_elems));
   d.G = cv.take<cd>(std::max<long long>(1, c->G_elems));
@@ -626,14 +632,19 @@ cd shift_scalar(double alpha, double beta, double omega) {
   return mk(w2, -beta * w2);
 }
 
-void nd_factor(helm_ctx* c, hipStream_t s) {
+// whole: the heights from the first one with several inversion windows (c->nd_hwin) again, with
+// one window per separator (the fronts below are as the first pass left them)
+void nd_factor(helm_ctx* c, bool whole, hipStream_t s) {
   NDDev& d = c->nd;
   NDPlan& P = c->plan;
   nd_fill_int(d.iperm, P.perm_total, -1, s);
-  nd_fill_int(d.err, 1, 0, s);
-  for (size_t h = 0; h < c->hinfo.size(); ++h) {
+  if (!whole) nd_fill_int(d.err, 2, 0, s);
+  else nd_fill_int(d.err + 1, 1, 0, s);
+  for (int h = whole ? c->nd_hwin : 0; h < (int)c->hinfo.size(); ++h) {
     const HeightInfo& hi = c->hinfo[h];
-    const NDInv v{d.hfr + hi.start, d.goff + hi.start, d.F, d.G, d.perm, d.iperm, d.err, c->nd_win};
+    const int win = whole ? std::max(c->nd_win, (hi.max_nS + 15) / 16 * 16) : c->nd_win;
+    const NDInv v{d.hfr + hi.start, d.goff + hi.start, d.F, d.G, d.perm, d.iperm, d.err + (h >= c->nd_hwin),
+                  win, c->nd_growth * c->nd_growth};
     const long long* toff = d.toff + hi.start;
     nd_extend(v, d.fronts, hi.count, hi.max_nF, d.children, d.child_map_off, d.maps, s);
     nd_assemble(v, hi.count, hi.max_asm, d.asmv, c->coef3_64, s);
@@ -642,13 +653,33 @@ void nd_factor(helm_ctx* c, hipStream_t s) {
     // blocks are streamed once per block instead of once per panel.  That pays once they
     // hold HELM_ND_REG_BLOCK_MB megabytes; below, a pass costs about one launch.
     const bool blocked = hi.s_bytes >= (long long)env_int("HELM_ND_REG_BLOCK_MB", 32) * 1000000;
-    const int kout = nd_invert(v, hi.count, hi.max_nS, hi.max_wn, blocked ? env_int("HELM_ND_KB_OUTER", 128) : 1, s);
+    const int kout = nd_invert(v, hi.count, hi.max_nS, whole ? hi.max_nS : hi.max_wn,
+                               blocked ? env_int("HELM_ND_KB_OUTER", 128) : 1, s);
     // the 5/7-point stack's operators are complex symmetric
     if (!c->nd64)
       nd_products<cf>(v, hi.count, hi.max_nS, hi.max_nB, kout, !c->compact, toff, d.T, (cf*)d.L, (cf*)d.W, s);
     else
       nd_products<cd>(v, hi.count, hi.max_nS, hi.max_nB, kout, !c->compact, toff, d.T, (cd*)d.L, (cd*)d.W, s);
   }
+}
+
+// The outcome of the queued factorisation (waits for it).  Where a window of it had no good
+// pivots in its own rows, the factorisation is taken again with the pivots of a separator from
+// all its rows (a zero pivot met behind such a window may only be its consequence).
+int factor_status(helm_ctx* c, hipStream_t s) {
+  int err[2];            // below the first height with several windows, from it on
+  auto read = [&]() {
+    CK(hipMemcpyAsync(c->hstate, c->nd.err, sizeof(err), hipMemcpyDeviceToHost, s));
+    CK(hipStreamSynchronize(s));
+    std::memcpy(err, c->hstate, sizeof(err));
+  };
+  read();
+  c->nd_whole = !err[0] && (err[1] & ND_GROWTH);
+  if (c->nd_whole) {
+    nd_factor(c, true, s);
+    read();
+  }
+  return err[0] || err[1] ? fail(HELM_ESINGULAR, "zero pivot in the coarsest-grid elimination") : HELM_OK;
 }
 
 hipEvent_t ev_get(helm_ctx* c) {
@@ -730,7 +761,7 @@ void numeric_setup(helm_ctx* c, const double* medium, int is_m, hipStream_t s) {
     wgal_fine(c->op, shift_scalar(shift->alpha2, shift->beta, omega), shift_scalar(shift->alpha, shift->beta, omega),
               c->m64, c->g2, c->tr[0], c->ip[0], c->r2, c->coef2_64, c->f32 ? c->coef2_32 : nullptr, c->tmp2, s);
     wgal_coarse(c->g2, c->tmp2, c->r2, c->g3, c->tr[1], c->ip[1], c->r3, c->coef3_64, s);
-    nd_factor(c, s);
+    nd_factor(c, false, s);
     return;
   }
   if (c->f32) {
@@ -752,7 +783,7 @@ void numeric_setup(helm_ctx* c, const double* medium, int is_m, hipStream_t s) {
   gal_fine(c->op, shift_scalar(shift->alpha, shift->beta, omega), c->m64, c->g2, c->tmp2, s);
   gal_coarse(c->g2, c->tmp2, c->g3, c->coef3_64, s);
   // a3: exact factorisation
-  nd_factor(c, s);
+  nd_factor(c, false, s);
 }
 
 // iterate state of one level: x_in = [x] + [w D^-1 b] + [P e]
@@ -1417,6 +1448,8 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
     }
     numeric_setup(c.get(), slowness, 0, s);
     CK(hipEventRecord(e1, s));
+    const int st = factor_status(c.get(), s);
+    if (c->nd_whole) CK(hipEventRecord(e1, s));
     CK(hipStreamSynchronize(s));
     CK(hipGetLastError());
     float ms = 0;
@@ -1424,11 +1457,9 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
     c->times[4] = ms;
     CK(hipEventDestroy(e0));
     CK(hipEventDestroy(e1));
-    int err = 0;
-    CK(hipMemcpy(&err, d.err, sizeof(int), hipMemcpyDeviceToHost));
-    if (err) {
+    if (st) {
       (void)hipHostFree(c->hstate);
-      return fail(HELM_ESINGULAR, "zero pivot in the coarsest-grid elimination");
+      return st;
     }
   } catch (DevErr& e) {
     if (c->hstate) (void)hipHostFree(c->hstate);
@@ -1461,11 +1492,7 @@ static int refactor_impl(helm_ctx* c, const double* medium, int is_m, double ome
     c->omega = omega;
     c->shift = *shift;
     numeric_setup(c, medium, is_m, s);
-    int err = 0;
-    CK(hipMemcpyAsync(c->hstate, c->nd.err, sizeof(int), hipMemcpyDeviceToHost, s));
-    CK(hipStreamSynchronize(s));
-    std::memcpy(&err, c->hstate, sizeof(int));
-    if (err) return fail(HELM_ESINGULAR, "zero pivot in the coarsest-grid elimination");
+    if (int v = factor_status(c, s)) return v;
   } catch (DevErr& e) {
     return fail(HELM_EDEVICE, "%s", e.what());
   }
@@ -1666,13 +1693,13 @@ int helm_get_info(helm_ctx* c, long long* out, int n) {
     sB += f.nB;
     maxF = std::max<long long>(maxF, f.nF);
   }
-  long long v[29] = {c->g1.tot, c->g2.tot, c->g3.tot, (long long)P.fronts.size(), P.L_total, P.W_total, sB,
+  long long v[30] = {c->g1.tot, c->g2.tot, c->g3.tot, (long long)P.fronts.size(), P.L_total, P.W_total, sB,
                      c->g3.tot, (long long)nd_kernels(c->nd.launch[0]), (long long)nd_kernels(c->nd.launch[1]),
                      (long long)c->ws_needed, maxF,
                      (long long)c->csz, c->nd_leaf, c->nd_root, c->tuned ? 1 : 0, 0,
                      -1, -1, -1, -1, c->nd_merge, c->K2, c->K3, (long long)c->ndsz,
-                     c->box[0], c->box[1], c->box[2], c->box[3]};
-  int m = std::min(n, 29);
+                     c->box[0], c->box[1], c->box[2], c->box[3], c->nd_whole ? 1 : 0};
+  int m = std::min(n, 30);
   for (int i = 0; i < m; ++i) out[i] = v[i];
   return m;
 }

@@ -198,15 +198,21 @@ struct NDFrontDev {
 
 // the factorisation's device arrays for the fronts of one height (slot order): the front
 // matrices, the second copy of their separator blocks (offset goff per slot, nS x nS), the
-// pivot rows pm (perm_off + column) and their inverse ip (-1: not yet a pivot row), and the
-// rows of an inversion window (a multiple of 16, at most 1024)
+// pivot rows pm (perm_off + column) and their inverse ip (-1: not yet a pivot row), the rows of
+// an inversion window (a multiple of 16), and the square of the largest entry that a window may
+// leave in a row that is still to be pivoted (k_inv_outer)
 struct NDInv {
   const NDFrontDev* hf;
   const long long* goff;
   cd *F, *G;
   int *pm, *ip, *err;
   int win;
+  double growth2;
 };
+// bits of the error word: a zero or NaN pivot among all rows of a separator; a window whose own
+// rows hold no good pivots
+#define ND_SINGULAR 1
+#define ND_GROWTH 2
 
 // windows of a separator of nS rows: nwin of wsz rows (a multiple of 16; the last shorter)
 __host__ __device__ inline int win_count(int nS, int win) { return (nS + win - 1) / win; }

@@ -31,11 +31,21 @@
 //     Q[:, J] = Q0[:, J] (pivot rows: 0) - Q'[:, K] Q0[pm[K], J]           (k_inv_gemm),
 // read from one copy of A and written to the other (the front itself and a scratch copy,
 // parity 0 and 1), so that a launch reads no entry that it writes.  The pivots of a window's
-// columns come from the window's rows, as those of a front come from its own separator; the
-// rows of A outside the window take their part of the run's columns from the finished
-// window, Q'[i, K] = Q0[i, K] Q'[pm[K], K] (k_inv_outer).
+// columns come from the window's rows; the rows of A outside the window take their part of the
+// run's columns from the finished window, Q'[i, K] = Q0[i, K] Q'[pm[K], K] (k_inv_outer).
+//
+// Windows bound the rows that a panel searches and keeps in registers, but the rows of one may
+// hold no good pivots where the whole separator does: a window's block is the operator with
+// zero values beyond it, and near a resonance of that part of the grid it is singular (without
+// damping; 1536 rows, 2 windows, at such a frequency: the coarsest solve was wrong in every digit,
+// 1e-14 with pivots from all rows).  The loss shows as large entries Q'[i, K] in the rows still to
+// be pivoted, the multipliers of the window's elimination: the error grows about as their square
+// (largest multiplier 1.3, 4.6, 46, 460: 1.3, 26, 75, 25000 times that with pivots from all rows).
+// k_inv_outer reports any beyond 1, which pivoting over all rows keeps every step to, and the
+// factorisation is then taken again with one window per separator, whose panels search all its
+// rows (k_inv_panel_wide).  With an absorbing layer or a complex shift the multipliers stay below
+// 1 (0.25 to 1 at 144^3 to 256^3, G = 5 to 12); without either they reach 4 to 16.
 #include <algorithm>
-#include <stdexcept>
 #include <type_traits>
 
 #include "internal.h"
@@ -351,7 +361,7 @@ __global__ void __launch_bounds__(NT) k_inv_panel(NDInv v, int w, int k0, int pa
       }
       __syncthreads();
     });
-  if (bad) atomicOr(v.err, 1);
+  if (bad) atomicOr(v.err, f.nwin > 1 ? ND_GROWTH : ND_SINGULAR);
   if (t < kbb) {
     f.pm[f.w0 + k0 + t] = f.w0 + s_piv[t];
     f.ip[f.w0 + s_piv[t]] = f.w0 + k0 + t;
@@ -373,6 +383,117 @@ __global__ void __launch_bounds__(NT) k_inv_panel(NDInv v, int w, int k0, int pa
         if (i < f.wn && col < kbb) *(cd*)((char*)dst + 16u * ((unsigned)i * ldd + col)) = s_t[e / CB * LS + e % CB];
       }
     }
+}
+
+// A panel of any number of rows, one work-group per front, 8 threads per row: the panel is
+// copied and then exchanged in place, every pivot from all open rows; the threads of the next
+// pivot's column search it as they write it.  Taken where a window's own rows hold no good
+// pivots, so it is kept simple: bound by one CU's reads and writes of the panel per pivot, hence 8
+// columns (set-up of 256^3, 4225 rows: 96 ms, 240 with this pass, 287 with 16 columns; 160^3:
+// 15.9, 34.9, 42.1).
+#define WIDE_KB 8
+__global__ void __launch_bounds__(1024) k_inv_panel_wide(NDInv v, int w, int k0, int par) {
+  constexpr int KB = WIDE_KB, NT = 1024, NW = NT / 64;
+  __shared__ cd s_row[KB];
+  __shared__ double s_v[NW];
+  __shared__ int s_i[NW];
+  const InvFront f = inv_front(v, blockIdx.x, w);
+  if (k0 >= f.wn) return;
+  const int kbb = min(KB, f.wn - k0), t = threadIdx.x, lane = t & 63, c = t % KB;
+  const bool on = c < kbb;
+  const long long ls = f.ld(par), ld = f.ld(par ^ 1);
+  const cd* __restrict__ src = f.q(par) + f.w0 * ls + f.w0 + k0 + (on ? c : 0);
+  cd* __restrict__ dst = f.q(par ^ 1) + f.w0 * ld + f.w0 + k0 + (on ? c : 0);
+  int* __restrict__ ip = f.ip + f.w0;
+  // this thread's candidate of the column in search: the largest |entry|^2 among the open rows
+  // (zero and NaN: 0), the lower row among equals
+  double bv = -1.0;
+  int bi = f.wn - 1;
+  auto offer = [&](cd a, int i, int done) {
+    const double q = abs2(a), x = q > 0.0 ? q : 0.0;
+    if (x > bv && done < 0) {
+      bv = x;
+      bi = i;
+    }
+  };
+  // RU rows' loads in flight (past the last row: repeated, not used)
+  constexpr int RU = 8, RS = NT / KB;
+  for (int i0 = t / KB; i0 < f.wn; i0 += RU * RS) {
+    cd x[RU];
+    int done[RU];
+#pragma unroll
+    for (int u = 0; u < RU; ++u) {
+      const int i = min(i0 + u * RS, f.wn - 1);
+      x[u] = src[i * ls];
+      done[u] = ip[i];
+    }
+#pragma unroll
+    for (int u = 0; u < RU; ++u) {
+      const int i = i0 + u * RS;
+      if (i >= f.wn) break;
+      if (on) dst[i * ld] = x[u];
+      if (c == 0) offer(x[u], i, done[u]);
+    }
+  }
+  int bad = 0;
+  for (int kk = 0; kk < kbb; ++kk) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const double ov = __shfl_xor(bv, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      if (ov > bv || (ov == bv && oi < bi)) {
+        bv = ov;
+        bi = oi;
+      }
+    }
+    if (lane == 0) {
+      s_v[t >> 6] = bv;
+      s_i[t >> 6] = bi;
+    }
+    __syncthreads();
+    bv = s_v[0];
+    bi = s_i[0];
+    for (int g = 1; g < NW; ++g)
+      if (s_v[g] > bv || (s_v[g] == bv && s_i[g] < bi)) {
+        bv = s_v[g];
+        bi = s_i[g];
+      }
+    const int p = bi;
+    const bool ok = bv > 0.0;
+    if (!ok) bad = 1;
+    if (t < kbb) s_row[t] = dst[p * ld];
+    if (t == 0) {
+      f.pm[f.w0 + k0 + kk] = f.w0 + p;
+      ip[p] = f.w0 + k0 + kk;
+    }
+    __syncthreads();
+    const cd inv = ok ? cdiv(mk(1.0, 0.0), s_row[kk]) : mk(1.0, 0.0);
+    const cd rc = on ? s_row[c] : mk(0.0, 0.0);
+    bv = -1.0;
+    bi = f.wn - 1;
+    for (int i0 = t / KB; i0 < f.wn; i0 += RU * RS) {
+      cd x[RU];
+      int done[RU];
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const int i = min(i0 + u * RS, f.wn - 1);
+        x[u] = dst[i * ld];
+        done[u] = ip[i];
+      }
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const int i = i0 + u * RS;
+        const cd xk = mk(__shfl(x[u].x, (lane & ~(KB - 1)) + kk, 64), __shfl(x[u].y, (lane & ~(KB - 1)) + kk, 64));
+        const cd ck = i == p ? inv : xk * inv;
+        const cd y = c == kk ? ck : csubmul(i == p ? mk(0.0, 0.0) : x[u], ck, rc);
+        if (i >= f.wn || !on) continue;
+        dst[i * ld] = y;
+        if (c == kk + 1) offer(y, i, done[u]);
+      }
+    }
+    __syncthreads();
+  }
+  if (bad && t == 0) atomicOr(v.err, f.nwin > 1 ? ND_GROWTH : ND_SINGULAR);
 }
 
 // ------------------------------------------------------ complex FP64 products (MFMA) ----
@@ -559,6 +680,7 @@ GEMM_KERNEL k_inv_outer(NDInv v, int w, int par, int kout) {
     gemm_tile<GT>(
         s, N, acc, [&](int r, int k) { return tm + r < M && k < N ? A[(tm + r) * la + k] : mk(0.0, 0.0); },
         [&](int k, int c) { return tn + c < N && k < N ? B[pm[k] * lb + tn + c] : mk(0.0, 0.0); });
+  int big = 0;
   gemm_store<GT>(acc, no_old, [&](int r, int c, cd x, cd) {
     const int i = tm + r, j = tn + c;
     if (i >= M || j >= N) return;
@@ -566,8 +688,10 @@ GEMM_KERNEL k_inv_outer(NDInv v, int w, int par, int kout) {
       if (pr != po) O[i * lo + j] = B[i * lb + j];
     } else {
       O[i * lo + j] = x;
+      if (f.ip[i] < 0 && !(abs2(x) <= v.growth2)) big = 1;      // (NaN counts as large)
     }
   });
+  if (big) atomicOr(v.err, ND_GROWTH);
 }
 
 // the copy that holds a front's exchanged A once every window is done
@@ -726,7 +850,8 @@ void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, int max_nF, const
 // groups or whole rows per thread: 64 rows 26.6 / 28.8 / 33, 128 rows 31.3 / 35.4 / 36,
 // 256 rows 41.4 / 40.2 / 50; of 16 columns over 512 rows, 2 groups / whole rows 22.2 / 21.6,
 // over 1024 34.6 / 31.7.
-static int panel_cols(int rows) { return rows <= 256 ? 32 : 16; }
+
+static int panel_cols(int rows) { return rows <= 256 ? 32 : rows <= 1024 ? 16 : WIDE_KB; }
 static void inv_panel(const NDInv& v, int nids, int rows, int w, int k0, int par, hipStream_t s) {
 #define PANEL(KB, Q, R, NT) \
   hipLaunchKernelGGL((k_inv_panel<KB, Q, R, NT>), dim3(nids), dim3(NT), 0, s, v, w, k0, par)
@@ -741,7 +866,7 @@ static void inv_panel(const NDInv& v, int nids, int rows, int w, int k0, int par
   else if (rows <= 1024)
     PANEL(16, 1, 2, 512);
   else
-    throw std::runtime_error("nd_invert: window of more than 1024 rows");
+    hipLaunchKernelGGL(k_inv_panel_wide, dim3(nids), dim3(1024), 0, s, v, w, k0, par);
 }
 // A product's tiles are 64 x 64, or 32 x 32 where 64 x 64 ones would not give every CU one:
 // there the launch lasts as long as one tile (a 16-deep update of 577 columns: 16.3 us with
