@@ -198,11 +198,12 @@ __device__ __forceinline__ void static_for(F f) {
 
 // A row's key for the pivot search: the leading bits of |Q[i][k]|^2 (a positive double's bits
 // order as its value) with the row in the last 10, lower rows first among equals.  The chosen
-// pivot is within 2^-10 of the largest in |.|^2.  Zero, NaN and exchanged rows come last.
+// pivot is within 2^-10 of the largest in |.|^2.  Zero and NaN come last, but before exchanged rows
+// (key 0): the one row that is left is found even if it is row 1023 and holds no pivot.
 __device__ __forceinline__ unsigned pivot_key(cd a, bool open, int row) {
   const double v = abs2(a);
   const unsigned hb = v >= 0.0 ? (unsigned)__double2hiint(v) & ~1023u : 0u;
-  return open ? hb | (unsigned)(1023 - row) : 0u;
+  return open ? max(hb, 1024u) | (unsigned)(1023 - row) : 0u;
 }
 
 // Panel [w0 + k0, + KB) of the window's rows, one work-group of NT threads per front.  The

@@ -106,14 +106,16 @@ def test_pivots_from_whole_separators(monkeypatch, name, block, block_mb):
         s.close()
 
 
-def test_no_pivot_in_any_window_is_singular(monkeypatch):
-    """a medium that is not a number at the last node, over two windows: no pivot is left for the
-    coarsest grid's last row"""
+# separators that fill a panel's rows (64, 128, 256, 512, 1024) and two windows (1536)
+@pytest.mark.parametrize("n", [(28, 28), (28, 60), (60, 60), (60, 124), (124, 124), (124, 188)])
+def test_last_row_without_a_pivot_is_singular(monkeypatch, n):
+    """a medium that is not a number at the last node reaches only the last entry of the coarsest
+    operator's last row, the one that is left for the last column: a zero pivot is reported"""
     monkeypatch.setenv("HELM_ND_LEAF", "4000")
-    p = undamped((124, 188), 0.5)
+    p = undamped(n, 0.5)
     p.slowness = p.slowness.copy()
     p.slowness.ravel()[-1] = np.nan
-    print("no pivot", flush=True)
+    print("no pivot", n, flush=True)
     with pytest.raises(L.HelmError) as e:
         from_problem(p, cycle_prec="f64")
     assert e.value.code == L.HELM_ESINGULAR
