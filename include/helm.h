@@ -288,7 +288,8 @@ int helm_get_timing(helm_ctx* ctx, double* t, int n);
  * factors and vectors (the cycle's precision; 16 for the compact stack), [25..28] box-shape
  * variants of the tiled level-1 sweep, level-1 restriction, level-2 sweep and level-2
  * restriction kernels (5/7-point stack; HELM_BOXES or the autotuner's cache), [29] 1 if the
- * last factorisation took a separator's pivots from all its rows, 0 if from windows of them.
+ * last factorisation took a separator's pivots from all its rows, 0 if from windows of them,
+ * [30] captured iteration graphs held.
  * Returns the number of entries written (at most n). */
 int helm_get_info(helm_ctx* ctx, long long* out, int n);
 

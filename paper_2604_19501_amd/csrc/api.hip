@@ -205,10 +205,17 @@ struct helm_ctx {
   double gtol[2] = {-1.0, -1.0};
   int gnr[2] = {0, 0};          // right-hand side count the graphs were captured for
   // iterations as captured graphs (1), as plain launches (0; HELM_GRAPHS forces either), or
-  // plain until the host is seen to be the slower side (-1): late_win counts the iterations of
-  // a window, late those whose read-back had come before the host had queued the next one
+  // plain until the host is seen to be the slower side (-1).  That is kept per operator for the
+  // last tolerance and right-hand side count, and dropped with the graphs, so that a capture
+  // waits for a second solve that can use it: window counts the iterations of a window, late
+  // those whose read-back had come before the host had queued the next one
   int graphs = -1;
-  int late = 0, late_win = 0;
+  struct Launches {
+    double tol = -1.0;
+    int nr = 0, window = 0, late = 0;
+    bool graphs = false;
+  } launches[2];
+  int late_limit = 32;
   double arnoldi_guard = 1e-8;  // relative size of ||w - V c||^2 below which an Arnoldi column ends the cycle
 };
 
@@ -1057,6 +1064,7 @@ void drop_graphs(helm_ctx* c) {
     for (hipGraphExec_t g : c->gexec[op]) (void)hipGraphExecDestroy(g);
     c->gexec[op].clear();
     c->gtol[op] = -1.0;
+    c->launches[op] = helm_ctx::Launches();
   }
 }
 
@@ -1124,9 +1132,15 @@ int solve_impl(helm_ctx* c, int op, int nr, const cd* b, cd* x, double tol, int 
   // Plain launches leave no gap between iterations; a graph's boundary costs 5 to 12 us of idle
   // device (per FGMRES iteration, graphs / plain: 1024^2 264 / 252 us, 600x640 FP64 177 / 169,
   // 256^2 107 / 102) and its capture 0.7 to 5 ms of a context's first solve.  Where launches are
-  // what the device waits for (128^2 with (2,2) sweeps: 111 / 117) the context goes over to
-  // graphs once half of a window of 64 iterations came late.
-  const bool use_graphs = c->graphs > 0 && !c->timing;
+  // what the device waits for (128^2 with (2,2) sweeps: 111 / 117) solves of the same kind go over
+  // to graphs once half of a window of 64 iterations came late.
+  helm_ctx::Launches& lm = c->launches[op];
+  if (lm.tol != tol || lm.nr != nr) {
+    lm = helm_ctx::Launches();
+    lm.tol = tol;
+    lm.nr = nr;
+  }
+  const bool use_graphs = !c->timing && (c->graphs > 0 || (c->graphs < 0 && lm.graphs));
   if (use_graphs) iter_graphs<R>(c, op, tol);
   kr_init(a, max_iter, c->packs, s);
   kr_residual(a, x, b, 1, s);
@@ -1184,12 +1198,12 @@ int solve_impl(helm_ctx* c, int op, int nr, const cd* b, cd* x, double tol, int 
       queue(q++);
       while (k < q) {
         if (q < m) queue(q++);
-        if (c->graphs < 0 && k + 1 < q) {
+        if (c->graphs < 0 && !use_graphs && k + 1 < q) {
           // (state 0's read-back: already there means that the device waits for the host)
-          if (*(const volatile int*)&hs(c, 1 + (k & 1))[0].seq - (base + k + 1) >= 0) ++c->late;
-          if (++c->late_win == 64) {
-            if (c->late >= 32) c->graphs = 1;        // from the next solve on
-            c->late = c->late_win = 0;
+          if (*(const volatile int*)&hs(c, 1 + (k & 1))[0].seq - (base + k + 1) >= 0) ++lm.late;
+          if (++lm.window == 64) {
+            if (lm.late >= c->late_limit) lm.graphs = true;     // from the next solve on
+            lm.late = lm.window = 0;
           }
         }
         wait_states(c, 1 + (k & 1), base + k + 1, s);
@@ -1402,6 +1416,8 @@ static int setup_rcap(const helm_grid* grid, const double* slowness, double omeg
     c->omega = omega;
     c->rcap = rcap;
     c->graphs = env_int("HELM_GRAPHS", -1);
+    // HELM_GRAPHS_LATE (tests): late iterations of a window of 64 that bring graphs
+    c->late_limit = env_int("HELM_GRAPHS_LATE", 32);
     c->l2_chain = env_int("HELM_L2_CHAIN", 1);
     // HELM_ARNOLDI_GUARD (tests): the cancellation threshold of the Arnoldi norm formula
     if (const char* g = getenv("HELM_ARNOLDI_GUARD")) c->arnoldi_guard = atof(g);
@@ -1693,13 +1709,14 @@ int helm_get_info(helm_ctx* c, long long* out, int n) {
     sB += f.nB;
     maxF = std::max<long long>(maxF, f.nF);
   }
-  long long v[30] = {c->g1.tot, c->g2.tot, c->g3.tot, (long long)P.fronts.size(), P.L_total, P.W_total, sB,
+  long long v[31] = {c->g1.tot, c->g2.tot, c->g3.tot, (long long)P.fronts.size(), P.L_total, P.W_total, sB,
                      c->g3.tot, (long long)nd_kernels(c->nd.launch[0]), (long long)nd_kernels(c->nd.launch[1]),
                      (long long)c->ws_needed, maxF,
                      (long long)c->csz, c->nd_leaf, c->nd_root, c->tuned ? 1 : 0, 0,
                      -1, -1, -1, -1, c->nd_merge, c->K2, c->K3, (long long)c->ndsz,
-                     c->box[0], c->box[1], c->box[2], c->box[3], c->nd_whole ? 1 : 0};
-  int m = std::min(n, 30);
+                     c->box[0], c->box[1], c->box[2], c->box[3], c->nd_whole ? 1 : 0,
+                     (long long)(c->gexec[0].size() + c->gexec[1].size())};
+  int m = std::min(n, 31);
   for (int i = 0; i < m; ++i) out[i] = v[i];
   return m;
 }

@@ -23,7 +23,7 @@ from . import _lib as L
 INFO_KEYS = ("N1", "N2", "N3", "fronts", "L_entries", "W_entries", "upd_entries", "sep_entries",
              "fwd_launches", "bwd_launches", "workspace_bytes", "max_front", "cycle_complex_bytes",
              "nd_leaf", "nd_root", "nd_tuned", "nd_tree_launches")
-INFO_LEN = 30
+INFO_LEN = 31
 KERNEL_CLASSES = ("l1_sweep", "l1_restrict", "l2_sweep", "l2_restrict", "nd_fwd", "nd_bwd", "arnoldi", "l2_chain",
                   "cycle_tail")
 # their indices among the library's timing classes (helm_get_timing)
@@ -40,6 +40,7 @@ def parse_info(v) -> dict:
     out["coarse_complex_bytes"] = int(v[24])
     out["boxes"] = [int(v[25 + i]) for i in range(4)]
     out["whole_pivots"] = bool(v[29])
+    out["graphs"] = int(v[30])
     return out
 
 
