@@ -137,3 +137,27 @@ def test_single_instance_calls_refuse_a_batched_context():
     xs, infos = b.solve([probs[0].rhs(0), probs[1].rhs(0)], [0, 1], tol=1e-6, max_iter=400)
     assert all(i["status"] == 0 for i in infos)
     b.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("cycle,nu", [(2, (1, 1)), (2, (2, 2)), (1, (1, 1))])
+@pytest.mark.parametrize("sizes", [(64, 96, 128), (256, 384, 512)])
+def test_instances_take_the_single_solves_bits(sizes, cycle, nu, prec):
+    """several instances at once, whose cycles take separate kernels and default boxes where a
+    single solve takes the fused kernels and the small restriction boxes (below 512 default boxes of
+    a level): the same bits in both precisions and for both operators, unconverged or not"""
+    probs = [synth.config4_instance(i, per_size=1, sizes=sizes, n_src=2) for i in range(len(sizes))]
+    print("batch against single", sizes, cycle, nu, prec, flush=True)
+    b = BatchedSolver([instance_dict(p) for p in probs], cycle=cycle, nu=nu, cycle_prec=prec, max_rhs=2)
+    rhs = [p.rhs(k) for p in probs for k in range(2)]
+    inst = [i for i in range(len(probs)) for _ in range(2)]
+    for op in (L.HELM_OP_N, L.HELM_OP_C):
+        xs, infos = b.solve(rhs, inst, tol=1e-6, max_iter=30, op=op)
+        for i, p in enumerate(probs):
+            s = from_problem(p, cycle=cycle, nu=nu, cycle_prec=prec)
+            for k in range(2):
+                x1, i1 = s.solve(rhs[2 * i + k], tol=1e-6, max_iter=30, op=op)
+                assert i1["iterations"] == infos[2 * i + k]["iterations"]
+                assert torch.equal(x1, xs[2 * i + k]), (op, p.n, k, float((x1 - xs[2 * i + k]).abs().max()))
+            s.close()
+    b.close()
