@@ -448,7 +448,12 @@ void build_plan(helm_ctx* c) {
   // fronts' extra entries and factorisation time outweigh it (microseconds per FGMRES
   // iteration, no merge / odd levels / two of three):
   //   5-point 2D: 600x640 FP64 250 / 207 / 182, 900x516 with 4 sources 539 / - / 347; leaves
-  //   of 64 nodes, 32 on large grids (1024^2: 276 against 282 us)
+  //   of 64 nodes, 32 on large grids (1024^2: 276 against 282 us).  The merged fronts near the
+  //   root grow with the grid: set-up and iteration in ms with no merge / the odd levels up
+  //   to 9 / two of three at 2048^2 6.3 + 0.832 / 7.2 + 0.754 / 10.8 + 0.738, 5120x1024 6.4 +
+  //   0.994 / 7.4 + 0.907 / 17.0 + 0.904, 3072^2 10.4 + 1.766 / 11.4 + 1.684 / 49.6 + 1.725,
+  //   4096^2 17.0 + 3.216 / 18.4 + 3.202 / 46.1 + 3.311: two of three up to 2048^2, then the odd
+  //   levels up to 9
   //   7-point 3D: 80x72x64 314 / 258 / 247 with set-ups of 1.8 / 2.0 / 3.1 ms, 96^3 391 / 338 /
   //   317 with 4.1 / 5.1 / 7.4 ms: odd levels on small grids, none on larger ones
   //   compact stack: its slabs of 2 or 3 planes make merged fronts too large (1024^2: 844 us
@@ -468,8 +473,8 @@ void build_plan(helm_ctx* c) {
     // from the environment is taken as given, with no level merged unless it says so
     const bool given = getenv("HELM_ND_LEAF") || getenv("HELM_ND_ROOT");
     if (!v && !tuned && !given && !c->compact && (!d3 || N3 <= 12000))
-      for (int h = 1; h <= 40; ++h)
-        if (d3 ? h % 2 : h % 3) mh.push_back(h);
+      for (int h = 1; h <= (!d3 && N3 > 300000 ? 9 : 40); ++h)
+        if (d3 || N3 > 300000 ? h % 2 : h % 3) mh.push_back(h);
   }
   // box variants of the cycle kernels: "a,b,c,d" (HELM_BOXES, else the cache; default 0)
   {
