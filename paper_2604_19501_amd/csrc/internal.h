@@ -298,8 +298,8 @@ struct NDPlan {
 };
 
 // elem_bytes: bytes of a factor entry
-// splitk_bytes: heights whose factor blocks hold at least this many bytes (per direction) use
-// split-K launches
+// splitk_bytes: heights whose factor blocks hold at least this many bytes (per direction) and
+// more than ND_SPLITK_COLS columns use split-K launches; 0: every height does
 // merge_heights: heights of the dissection tree (leaves 0, before any merge) whose fronts are
 // merged into their parents (fewer levels, larger fronts)
 // radius: stencil radius of the coarsest operator (its (2 radius + 1)^dim coefficient planes,
@@ -308,6 +308,7 @@ void nd_plan(const Geom& g3, int leaf_max, int root_merge, int elem_bytes, long 
              const std::vector<int>& merge_heights = std::vector<int>(), int radius = 1);
 // LDS bytes of a row-block work-group for nr right-hand sides
 size_t nd_rows_lds(int rb, int waves, int max_k, int nr, size_t elem_bytes);
+#define ND_SPLITK_COLS 256
 #define ND_ROWS_LDS (128 * 1024)   // the most a row-block work-group may take for one right-hand side
 
 }  // namespace helm

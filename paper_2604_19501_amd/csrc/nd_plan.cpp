@@ -398,9 +398,16 @@ void nd_plan(const Geom& g3, int leaf_max, int root_merge, int elem_bytes, long 
       }
       if (bytes == 0) continue;
       NDLaunch L;
-      // a vector too long for a row block's LDS takes split-K tiles whatever the size
+      // Split-K is for heights of large blocks.  Many small fronts reach the bytes too, but fill
+      // a fraction of a 256 x 128 tile and spread over the chip by themselves: up to
+      // ND_SPLITK_COLS columns they take row blocks, which read such a block in one pass of 32 or
+      // 64 rows (a coarsest solve in ms, from any column count / from 257 on: 8192^2 3.29 / 1.81,
+      // 4096^2 0.79 / 0.51, 2048^2 compact 0.88 / 0.79, 256^3 FP64 1.52 / 1.43; from 65 to 2049 on
+      // the others are level within 3 %).  A vector too long for a row block's LDS takes tiles
+      // whatever the size.
+      const bool large = bytes >= splitk_bytes && (K > ND_SPLITK_COLS || splitk_bytes == 0);
       const bool fits = nd_rows_lds(64, 16, K, 1, elem_bytes) <= ND_ROWS_LDS;
-      if (bytes >= splitk_bytes || !fits)
+      if (large || !fits)
         build_splitk(L, h, dir);
       else
         build_rows(L, h, dir);

@@ -63,11 +63,34 @@ def test_every_schedule_is_exact_and_another(monkeypatch, dim, n):
             s.close()
 
 
-def test_row_blocks_of_long_vectors(monkeypatch):
-    """one front of 71 x 71 rows in row blocks: its FP64 vector takes 80 KB of LDS, more than the
-    64 KB that a launch may take unasked"""
-    apply(monkeypatch, (6000, 1, "none", 1 << 30))
-    p = rect_problem((280, 280))
+def test_split_k_takes_blocks_of_many_columns(monkeypatch):
+    """64 KB per height: heights of many small fronts (at most 256 columns) keep one row-block
+    launch each, one front of 1024 rows takes tiles and their sums"""
+    p = synth.config2(256)
+    H = oracle_hierarchy(p)
+    launches = {}
+    for kb in (64, 1 << 30):
+        apply(monkeypatch, (32, 1, "none", kb))
+        s = from_problem(p, cycle_prec="f64")
+        check(p, "f64", s, H)
+        launches[kb] = (s.info()["fwd_launches"], s.info()["bwd_launches"])
+        s.close()
+    print("split-K columns", launches, flush=True)
+    assert launches[64] == launches[1 << 30]
+    apply(monkeypatch, (4000, 1, "none", 64))
+    p = rect_problem((124, 124))
+    s = from_problem(p, cycle_prec="f64")
+    check(p, "f64", s, oracle_hierarchy(p))
+    assert s.info()["fwd_launches"] == 2
+    s.close()
+
+
+@pytest.mark.parametrize("n", [(280, 280), (332, 332)])
+def test_row_blocks_of_long_vectors(monkeypatch, n):
+    """one front of 71 x 71 or 84 x 84 rows in row blocks: its FP64 vector takes 80 or 113 KB of
+    LDS, more than the 64 KB that a launch may take unasked"""
+    apply(monkeypatch, (8000, 1, "none", 1 << 30))
+    p = rect_problem(n)
     H = oracle_hierarchy(p)
     for prec in ("f64", "f32"):
         print("long vectors", prec, flush=True)
