@@ -197,13 +197,16 @@ __device__ __forceinline__ void static_for(F f) {
 }
 
 // A row's key for the pivot search: the leading bits of |Q[i][k]|^2 (a positive double's bits
-// order as its value) with the row in the last 10, lower rows first among equals.  The chosen
-// pivot is within 2^-10 of the largest in |.|^2.  Zero and NaN come last, but before exchanged rows
-// (key 0): the one row that is left is found even if it is row 1023 and holds no pivot.
+// order as its value) with the row in the last B (10 up to 1024 rows), lower rows first among
+// equals.  The chosen pivot is within 2^(B - 20) of the largest in |.|^2.  Zero and NaN
+// come last, but before exchanged rows (key 0): the one row that is left is found even if it is the
+// last one and holds no pivot.
+template <int B>
 __device__ __forceinline__ unsigned pivot_key(cd a, bool open, int row) {
+  constexpr unsigned ROWS = 1u << B;
   const double v = abs2(a);
-  const unsigned hb = v >= 0.0 ? (unsigned)__double2hiint(v) & ~1023u : 0u;
-  return open ? max(hb, 1024u) | (unsigned)(1023 - row) : 0u;
+  const unsigned hb = v >= 0.0 ? (unsigned)__double2hiint(v) & ~(ROWS - 1) : 0u;
+  return open ? max(hb, ROWS) | (ROWS - 1 - (unsigned)row) : 0u;
 }
 
 // Panel [w0 + k0, + KB) of the window's rows, one work-group of NT threads per front.  The
@@ -227,6 +230,7 @@ __device__ __forceinline__ unsigned pivot_key(cd a, bool open, int row) {
 template <int KB, int Q, int R, int NT>
 __global__ void __launch_bounds__(NT) k_inv_panel(NDInv v, int w, int k0, int par) {
   constexpr int NR = NT / Q, KS = KB / Q, GW = NR / 64, CB = 8, CQ = CB / Q, LS = CB + 1;
+  constexpr int KEY = NR * R > 1024 ? 11 : 10;
   static_assert(NR % 64 == 0 && CB % Q == 0 && KS >= 2 && KS <= 16 && (KS & (KS - 1)) == 0, "panel split");
   __shared__ cd s_row[KB];                 // the pivot row, by group and slot
   __shared__ unsigned s_key[GW];
@@ -279,11 +283,11 @@ __global__ void __launch_bounds__(NT) k_inv_panel(NDInv v, int w, int k0, int pa
   bool ok = true;
   auto search = [&]() {
     cd c0 = a[0][0];
-    unsigned key = pivot_key(a[0][0], open[0], tr);
+    unsigned key = pivot_key<KEY>(a[0][0], open[0], tr);
     if (Q > 1) s_col[tr] = a[0][0];
 #pragma unroll
     for (int r = 1; r < R; ++r) {
-      const unsigned kr = pivot_key(a[r][0], open[r], r * NR + tr);
+      const unsigned kr = pivot_key<KEY>(a[r][0], open[r], r * NR + tr);
       const bool up = kr > key;
       c0.x = up ? a[r][0].x : c0.x;
       c0.y = up ? a[r][0].y : c0.y;
@@ -313,7 +317,8 @@ __global__ void __launch_bounds__(NT) k_inv_panel(NDInv v, int w, int k0, int pa
       cd ck[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) ck[r] = Q > 1 ? s_col[r * NR + tr] : mk(a[r][0].x, a[r][0].y);
-      const int p = 1023 - (__builtin_amdgcn_readfirstlane((int)bk) & 1023);   // the pivot row, from w0
+      constexpr int RM = (1 << KEY) - 1;
+      const int p = RM - (__builtin_amdgcn_readfirstlane((int)bk) & RM);   // the pivot row, from w0
 #pragma unroll
       for (int r = 0; r < R; ++r)
         if (r * NR + tr == p) {
@@ -846,13 +851,18 @@ void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, int max_nF, const
   hipLaunchKernelGGL(k_nd_extend, dim3(tiles, nids), dim3(256), 0, s, v.hf, fr, children, child_map_off, maps, v.F);
 }
 
+// the most rows of a register panel.  Windows end at 1024, where two threads' rows fit 512 threads;
+// three rows per thread take the roots of up to 1100 rows that the default schedule merges in 2D,
+// where their windows held no good pivots (about 1080 rows: set-up 3.1 ms, 6.8 with this second
+// pass, 13.1 with k_inv_panel_wide; as the only pass 3.8, so the windows come first)
+#define REG_ROWS 1152
 // columns of a panel over a window of up to rows rows, and its split (k_inv_panel): 32 columns
 // while their entries leave a thread at most 16, then 16.  A panel in us, split into 4 / 2
 // groups or whole rows per thread: 64 rows 26.6 / 28.8 / 33, 128 rows 31.3 / 35.4 / 36,
 // 256 rows 41.4 / 40.2 / 50; of 16 columns over 512 rows, 2 groups / whole rows 22.2 / 21.6,
 // over 1024 34.6 / 31.7.
 
-static int panel_cols(int rows) { return rows <= 256 ? 32 : rows <= 1024 ? 16 : WIDE_KB; }
+static int panel_cols(int rows) { return rows <= 256 ? 32 : rows <= REG_ROWS ? 16 : WIDE_KB; }
 static void inv_panel(const NDInv& v, int nids, int rows, int w, int k0, int par, hipStream_t s) {
 #define PANEL(KB, Q, R, NT) \
   hipLaunchKernelGGL((k_inv_panel<KB, Q, R, NT>), dim3(nids), dim3(NT), 0, s, v, w, k0, par)
@@ -866,6 +876,8 @@ static void inv_panel(const NDInv& v, int nids, int rows, int w, int k0, int par
     PANEL(16, 1, 1, 512);
   else if (rows <= 1024)
     PANEL(16, 1, 2, 512);
+  else if (rows <= REG_ROWS)
+    PANEL(16, 1, 3, 384);
   else
     hipLaunchKernelGGL(k_inv_panel_wide, dim3(nids), dim3(1024), 0, s, v, w, k0, par);
 }

@@ -47,9 +47,10 @@ def check(s, H, p, prec):
         assert ec < TOL[prec]
 
 
-# one front of the whole coarsest grid: 32 x 48 and 11^3 nodes in two of the default windows, 16 x
-# 16 in windows of 16 rows
-@pytest.mark.parametrize("n,win,rows", [((124, 188), 1024, 768), ((40, 40, 40), 1024, 672), ((60, 60), 16, 16)])
+# one front of the whole coarsest grid: 32 x 48, 32 x 34 and 11^3 nodes in two of the default
+# windows, 16 x 16 in windows of 16 rows
+@pytest.mark.parametrize("n,win,rows", [((124, 188), 1024, 768), ((124, 132), 1024, 544),
+                                        ((40, 40, 40), 1024, 672), ((60, 60), 16, 16)])
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 def test_window_at_a_resonance(monkeypatch, n, win, rows, prec):
     """A frequency at which the first window's block is singular, the whole separator's far from
@@ -74,10 +75,13 @@ def test_window_at_a_resonance(monkeypatch, n, win, rows, prec):
     s.close()
 
 
-# (problem, environment): separators up to 1331 rows, symmetric operators and not
+# (problem, environment): separators up to 1331 rows (register panels up to 1152), symmetric
+# operators and not
 PROBLEMS = {
     "2d": (lambda: synth.config2(128), {"HELM_ND_WIN": "16"}),
     "2d_root_700": (lambda: synth.config2(192), {"HELM_ND_WIN": "48", "HELM_ND_ROOT": "700"}),
+    "2d_dense_1088": (lambda: rect_problem((124, 132)), {"HELM_ND_LEAF": "4000"}),
+    "2d_dense_1152": (lambda: rect_problem((124, 140)), {"HELM_ND_LEAF": "4000"}),
     "3d": (lambda: synth.config3(64), {"HELM_ND_WIN": "112"}),
     "3d_dense": (lambda: synth.config3(40), {"HELM_ND_ROOT": "1331"}),
     "compact_2d": (lambda: synth.paper_stack((192, 128), "cubic"), {"HELM_ND_WIN": "112", "HELM_ND_ROOT": "300"}),
@@ -106,8 +110,8 @@ def test_pivots_from_whole_separators(monkeypatch, name, block, block_mb):
         s.close()
 
 
-# separators that fill a panel's rows (64, 128, 256, 512, 1024) and two windows (1536)
-@pytest.mark.parametrize("n", [(28, 28), (28, 60), (60, 60), (60, 124), (124, 124), (124, 188)])
+# separators that fill a panel's rows (64, 128, 256, 512, 1024; 1152 after two windows) and 1536
+@pytest.mark.parametrize("n", [(28, 28), (28, 60), (60, 60), (60, 124), (124, 124), (124, 140), (124, 188)])
 def test_last_row_without_a_pivot_is_singular(monkeypatch, n):
     """a medium that is not a number at the last node reaches only the last entry of the coarsest
     operator's last row, the one that is left for the last column: a zero pivot is reported"""
