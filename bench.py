@@ -244,7 +244,7 @@ def run_single(args, p, label, with_fp64, traffic=False):
         "vs_baseline": None, "dtype": "c64 cycle / c128 FGMRES", "data": "synthetic",
         "config": {"workload": label, "unknowns": p.N, "iterations": its[-1],
                    "true_rel_residual": info["true_rel_residual"],
-                   "nd_schedule": {"leaf": sinfo["nd_leaf"], "root": sinfo["nd_root"], "cuts": sinfo["nd_cuts"],
+                   "nd_schedule": {"leaf": sinfo["nd_leaf"], "root": sinfo["nd_root"], "merge": sinfo["nd_merge"],
                                    "tuned": bool(sinfo["nd_tuned"])}},
         "solve_only_per_sec": 1.0 / dt_solve, "setup_ms": 1e3 * (dt - dt_solve),
         "kernel_ms": kms, "kernel_launches": kl, "kernel_achieved_GBs": gbs, "roofline": roof,

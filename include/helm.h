@@ -164,7 +164,7 @@ int helm_vcycle(helm_ctx* ctx, int op, const void* r, void* z, void* stream);
 
 /* helm_vcycle for callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the same cycle and kernels,
- * with its per-call scratch (level iterates, coarsest-solve update pool, gather and
+ * with its per-call scratch (level iterates, coarsest-solve update pool and
  * partial-product buffers) taken from a static device array of HELM_NOALLOC_SCRATCH_BYTES
  * instead of the context's workspace.  It calls no hipMalloc, hipFree or other allocating
  * routine (per-kernel timing is skipped for the call).  The operator data stay in the

@@ -5,7 +5,7 @@
     xs, infos = b.solve(rhs_list, inst_of_rhs)
 
 All instances share one workspace; helm_solve_batched runs the instances
-concurrently on library streams with their captured per-iteration graphs.
+concurrently on library streams, the right-hand sides of each in lock-step.
 """
 from __future__ import annotations
 
@@ -67,7 +67,7 @@ class BatchedSolver:
         return parse_info(v)
 
     def set_timing(self, on: bool = True):
-        """per-kernel-class HIP-event timing on every instance (graphs are bypassed meanwhile)"""
+        """per-kernel-class HIP-event timing on every instance (each iteration is waited for meanwhile)"""
         L.check(L.lib.helm_set_timing(self.ctx, 1 if on else 0), "helm_set_timing")
 
     def kernel_times(self) -> dict:

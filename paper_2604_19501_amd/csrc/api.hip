@@ -183,7 +183,7 @@ struct helm_ctx {
   std::vector<hipEvent_t> evpool;
   int nd_win = 1024;            // rows of an inversion window of the factorisation (HELM_ND_WIN)
   int nd_hwin = 0;              // the first height with a separator of several windows
-  double nd_growth = 1.0;       // largest multiplier of a window (HELM_ND_GROWTH)
+  double nd_growth = 1.0;       // largest multiplier of a window (nd_factor.hip; HELM_ND_GROWTH)
   bool nd_whole = false;        // the last factorisation took the pivots from whole separators
   bool tuned = false;           // schedule parameters came from the autotuner cache
   int nd_leaf = 0, nd_root = 0;  // nested-dissection leaf size and root merge limit in use
@@ -318,8 +318,7 @@ void init_geometry(helm_ctx* c) {
 // planes of the FP32 level-2 coefficients: 3D keeps the symmetric half (centre onwards;
 // the level kernels' Op2<3, float> reads them so)
 static inline int sym2_planes(int dim) { return dim == 3 ? 14 : 9; }
-// nested-dissection parameters (tunable through the environment for the autotuner):
-// leaf box size, rows per work-group of big fronts, nodes per subtree task
+// an integer from the environment (the schedule's parameters, for the autotuner and the tests)
 int env_int(const char* name, int dflt) {
   const char* v = getenv(name);
   return v && *v ? atoi(v) : dflt;
@@ -450,9 +449,9 @@ void build_plan(helm_ctx* c) {
   //   5-point 2D: 600x640 FP64 250 / 207 / 182, 900x516 with 4 sources 539 / - / 347; leaves
   //   of 64 nodes, 32 on large grids (1024^2: 276 against 282 us).  The merged fronts near the
   //   root grow with the grid: set-up and iteration in ms with no merge / the odd levels up
-  //   to 9 / two of three at 2048^2 6.3 + 0.832 / 7.2 + 0.754 / 10.8 + 0.738, 5120x1024 6.4 +
-  //   0.994 / 7.4 + 0.907 / 17.0 + 0.904, 3072^2 10.4 + 1.766 / 11.4 + 1.684 / 49.6 + 1.725,
-  //   4096^2 17.0 + 3.216 / 18.4 + 3.202 / 46.1 + 3.311: two of three up to 2048^2, then the odd
+  //   to 9 / two of three at 2048^2 6.3 + 0.826 / 7.2 + 0.747 / 10.8 + 0.733, 5120x1024 6.4 +
+  //   0.989 / 7.4 + 0.904 / 16.9 + 0.897, 3072^2 10.4 + 1.637 / 11.3 + 1.555 / 49.3 + 1.568,
+  //   4096^2 16.9 + 2.640 / 18.4 + 2.617 / 46.0 + 2.632: two of three up to 2048^2, then the odd
   //   levels up to 9
   //   7-point 3D: 80x72x64 314 / 258 / 247 with set-ups of 1.8 / 2.0 / 3.1 ms, 96^3 391 / 338 /
   //   317 with 4.1 / 5.1 / 7.4 ms: odd levels on small grids, none on larger ones
@@ -833,8 +832,8 @@ struct Cycle {
     // the 2D cycle with one pre- and one post-sweep sweeps in the fused kernels (l2_chain,
     // cycle_tail) except where several instances share the device: there the separate sweeps
     // keep the boxes whose rounding the fused ones share, so that a batch's solutions are
-    // those of its single solves, bit by bit (in FP64 other boxes can differ in the last place); nor
-    // does such a device, already full, gain from the small restrictions (167.8 / 166.7 ms
+    // those of its single solves, bit by bit (restrictions round alike in every box, their weights
+    // being powers of two); nor does such a device, already full, gain from the small restrictions (167.8 / 166.7 ms
     // for 6 instances of 8 right-hand sides)
     A1.small_sweep = A2.small_sweep = !(c->g2.dim == 2 && c->mg.nu_pre == 1 && c->mg.nu_post == 1);
     A1.small_restrict = A2.small_restrict = A1.small_sweep || c->l2_chain;

@@ -43,8 +43,10 @@
 // (largest multiplier 1.3, 4.6, 46, 460: 1.3, 26, 75, 25000 times that with pivots from all rows).
 // k_inv_outer reports any beyond 1, which pivoting over all rows keeps every step to, and the
 // factorisation is then taken again with one window per separator, whose panels search all its
-// rows (k_inv_panel_wide).  With an absorbing layer or a complex shift the multipliers stay below
-// 1 (0.25 to 1 at 144^3 to 256^3, G = 5 to 12); without either they reach 4 to 16.
+// rows.  Multipliers of at most 1 cost nothing (ratios of 0.94 to 1.24, geometric mean 1.00, over 88
+// grids).  With an absorbing layer or a complex shift they are 0.25 to 1 at 144^3 to 256^3 (G = 5 to
+// 12), without either 4 to 16; of the 2D roots merged to 1025 to 1100 rows some exceed 1, for
+// homogeneous media above all (up to 6).
 #include <algorithm>
 #include <type_traits>
 
@@ -256,7 +258,7 @@ __global__ void __launch_bounds__(NT) k_inv_panel(NDInv v, int w, int k0, int pa
 #pragma unroll
       for (int u = 0; u < CQ; ++u) {
         const int e = t + NT * u;
-        // byte offsets of a window stay far below 4 GB (1024 rows)
+        // byte offsets of a window stay far below 4 GB (at most 1152 rows)
         const unsigned off = 16u * ((unsigned)min(r * NR + e / CB, f.wn - 1) * ls + min(c * Q + e % CB, kbb - 1));
         a[r][c + u] = *(const cd*)((const char*)src + off);
       }
@@ -409,8 +411,8 @@ __global__ void __launch_bounds__(1024) k_inv_panel_wide(NDInv v, int w, int k0,
   const bool on = c < kbb;
   const long long ls = f.ld(par), ld = f.ld(par ^ 1);
   const cd* __restrict__ src = f.q(par) + f.w0 * ls + f.w0 + k0 + (on ? c : 0);
-  cd* __restrict__ dst = f.q(par ^ 1) + f.w0 * ld + f.w0 + k0 + (on ? c : 0);
-  int* __restrict__ ip = f.ip + f.w0;
+  cd* dst = f.q(par ^ 1) + f.w0 * ld + f.w0 + k0 + (on ? c : 0);
+  int* ip = f.ip + f.w0;
   // this thread's candidate of the column in search: the largest |entry|^2 among the open rows
   // (zero and NaN: 0), the lower row among equals
   double bv = -1.0;
@@ -860,8 +862,7 @@ void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, int max_nF, const
 // while their entries leave a thread at most 16, then 16.  A panel in us, split into 4 / 2
 // groups or whole rows per thread: 64 rows 26.6 / 28.8 / 33, 128 rows 31.3 / 35.4 / 36,
 // 256 rows 41.4 / 40.2 / 50; of 16 columns over 512 rows, 2 groups / whole rows 22.2 / 21.6,
-// over 1024 34.6 / 31.7.
-
+// over 1024 34.6 / 31.7.  Panels in memory take WIDE_KB.
 static int panel_cols(int rows) { return rows <= 256 ? 32 : rows <= REG_ROWS ? 16 : WIDE_KB; }
 static void inv_panel(const NDInv& v, int nids, int rows, int w, int k0, int par, hipStream_t s) {
 #define PANEL(KB, Q, R, NT) \

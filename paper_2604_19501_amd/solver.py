@@ -22,7 +22,7 @@ from . import _lib as L
 
 INFO_KEYS = ("N1", "N2", "N3", "fronts", "L_entries", "W_entries", "upd_entries", "sep_entries",
              "fwd_launches", "bwd_launches", "workspace_bytes", "max_front", "cycle_complex_bytes",
-             "nd_leaf", "nd_root", "nd_tuned", "nd_tree_launches")
+             "nd_leaf", "nd_root", "nd_tuned")
 INFO_LEN = 31
 KERNEL_CLASSES = ("l1_sweep", "l1_restrict", "l2_sweep", "l2_restrict", "nd_fwd", "nd_bwd", "arnoldi", "l2_chain",
                   "cycle_tail")
@@ -34,7 +34,6 @@ _CLASS_INDEX = {"l1_sweep": 0, "l1_restrict": 1, "l2_sweep": 2, "l2_restrict": 3
 def parse_info(v) -> dict:
     """the INFO_LEN integers of helm_get_info as a dict"""
     out = {k: int(v[i]) for i, k in enumerate(INFO_KEYS)}
-    out["nd_cuts"] = [int(v[17 + i]) for i in range(min(4, out["nd_tree_launches"]))]
     out["nd_merge"] = [h for h in range(63) if (int(v[21]) >> h) & 1]
     out["planes2"], out["planes3"] = int(v[22]), int(v[23])
     out["coarse_complex_bytes"] = int(v[24])

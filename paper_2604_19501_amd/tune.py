@@ -17,7 +17,7 @@ tune_cache.json next to the library unless the caller set it).
 Each candidate is scored by its numerical set-up time (coefficients, Galerkin operators,
 factorisation) plus --its times its per-iteration time: a larger root front shortens the
 substitutions but lengthens the factorisation.  Both times are minima over repeats,
-after a warm-up (which also captures the per-iteration graphs).
+after a warm-up.
 """
 from __future__ import annotations
 
@@ -46,7 +46,6 @@ MERGES = {
 
 
 SPLITK_DEFAULT_KB = 98304
-SPLITK_OFF_KB = 1 << 30
 
 
 def _candidates(dim: int):
