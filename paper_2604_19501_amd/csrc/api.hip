@@ -35,8 +35,8 @@ void nd_extend(const NDInv& v, const NDFrontDev* fr, int nids, int max_nF, const
 // the block width used, which nd_products takes
 int nd_invert(const NDInv& v, int nids, int max_nS, int max_wn, int block_cols, hipStream_t s);
 template <typename C>
-void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, int sym, const long long* toff, cd* T,
-                 C* Lp, C* Wp, hipStream_t s);
+void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, const long long* toff, cd* T, C* Lp,
+                 C* Wp, hipStream_t s);
 template <typename C>
 void nd_fwd(const NDLaunchDev& L, const NDFrontDev* fr, const int* idx, const int* cidx, const C* Lp, C* upd,
             const C* r, C* x, int conj, C* P, const NDRhs& rh, hipStream_t s);
@@ -666,11 +666,11 @@ void nd_factor(helm_ctx* c, bool whole, hipStream_t s) {
     const bool blocked = hi.s_bytes >= (long long)env_int("HELM_ND_REG_BLOCK_MB", 32) * 1000000;
     const int kout = nd_invert(v, hi.count, hi.max_nS, whole ? hi.max_nS : hi.max_wn,
                                blocked ? env_int("HELM_ND_KB_OUTER", 128) : 1, s);
-    // the 5/7-point stack's operators are complex symmetric
+    // FP32 factors are those of a 5/7-point operator, which is complex symmetric
     if (!c->nd64)
-      nd_products<cf>(v, hi.count, hi.max_nS, hi.max_nB, kout, !c->compact, toff, d.T, (cf*)d.L, (cf*)d.W, s);
+      nd_products<cf>(v, hi.count, hi.max_nS, hi.max_nB, kout, toff, d.T, (cf*)d.L, (cf*)d.W, s);
     else
-      nd_products<cd>(v, hi.count, hi.max_nS, hi.max_nB, kout, !c->compact, toff, d.T, (cd*)d.L, (cd*)d.W, s);
+      nd_products<cd>(v, hi.count, hi.max_nS, hi.max_nB, kout, toff, d.T, (cd*)d.L, (cd*)d.W, s);
   }
 }
 

@@ -11,10 +11,14 @@
 //     W = -A^-1 B  (depth nS),  C A^-1  (depth nS),  D += C W  (depth nS).
 // Taking them once per front, after the inversion, keeps B, C and D (most of the front) out
 // of the pivoting: a panel covers the nS rows of A instead of all nF, the products run at
-// full depth instead of in slices of 8 to 128, and no row swap touches B.  The 5/7-point
-// stack's operators are complex symmetric, so C A^-1 = -W^T needs no product and D + C W is
-// formed for its lower tiles only: nS^3 + nS^2 nB + nS nB^2 / 2 complex multiply-adds
-// instead of nS (nS + nB)^2.  Set-up times against exchanging the S pivots over all nF rows
+// full depth instead of in slices of 8 to 128, and no row swap touches B.  FP32 factors are
+// those of a 5/7-point operator, which is complex symmetric: there C A^-1 = -W^T needs no product
+// and D + C W is formed for its lower tiles only, nS^3 + nS^2 nB + nS nB^2 / 2 complex
+// multiply-adds instead of nS (nS + nB)^2.  FP64 factors take every product: W and C A^-1 round
+// apart where A is ill-conditioned, and the transpose of one for the other costs digits that FP32
+// factors don't hold (undamped 428x484, 44x48x80 and 28x64x28 grids: 9e-8, 6e-9 and 6e-10 against
+// 7e-11, 5e-12 and 2e-12; 1.2 to 1.4 times the error on damped ones; 1 % of a 600x640 step).
+// Set-up times against exchanging the S pivots over all nF rows
 // and columns: 228 -> 121 ms (256^3), 6.8 -> 4.8 ms (1024^2), 62.7 -> 41.7 ms (192x192x72
 // compact), 17.5 -> 11.3 ms (1024^2 compact), 1.19 -> 0.74 ms (128^2).
 //
@@ -741,7 +745,7 @@ __global__ void __launch_bounds__(256) k_inv_final(NDInv v, int kout, C* __restr
 }
 
 // W = -A^-1 B: in FP64 for the Schur product (T, nS x nB row major), in the substitution's
-// precision into W and, for a complex symmetric operator, as C A^-1 = (A^-1 B)^T into the
+// precision into W and (SYM) as C A^-1 = (A^-1 B)^T into the
 // lower block of L
 template <int GT, typename C, int SYM>
 GEMM_KERNEL k_nd_w(NDInv v, const long long* __restrict__ toff, int kout, cd* __restrict__ T, C* __restrict__ Lp,
@@ -771,7 +775,7 @@ GEMM_KERNEL k_nd_w(NDInv v, const long long* __restrict__ toff, int kout, cd* __
   });
 }
 
-// C A^-1 into the lower block of L (operators that are not symmetric)
+// C A^-1 into the lower block of L (FP64 factors)
 template <int GT, typename C>
 GEMM_KERNEL k_nd_x(NDInv v, int kout, C* __restrict__ Lp) {
   const NDFrontDev fr = v.hf[blockIdx.y];
@@ -795,7 +799,7 @@ GEMM_KERNEL k_nd_x(NDInv v, int kout, C* __restrict__ Lp) {
   });
 }
 
-// D += C W, the front's Schur complement; for a complex symmetric operator the tiles on and
+// D += C W, the front's Schur complement; SYM: the tiles on and
 // below the diagonal, the others being their mirror images
 template <int GT, int SYM>
 GEMM_KERNEL k_nd_schur(NDInv v, const long long* __restrict__ toff, const cd* __restrict__ T) {
@@ -922,15 +926,18 @@ int nd_invert(const NDInv& v, int nids, int max_nS, int max_wn, int block_cols, 
   return kout;
 }
 
+// FP32 factors (those of a complex symmetric 5/7-point operator) take the products that symmetry
+// leaves; FP64 ones take all of them
 template <typename C>
-void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, int sym, const long long* toff, cd* T,
-                 C* Lp, C* Wp, hipStream_t s) {
+void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, const long long* toff, cd* T, C* Lp,
+                 C* Wp, hipStream_t s) {
+  constexpr int SYM = sizeof(C) == sizeof(cf);
   const int nt = (max_nS + 31) / 32;
   const cd* Tc = T;
   hipLaunchKernelGGL((k_inv_final<C>), dim3(nt * nt, nids), dim3(256), 0, s, v, kout, Lp);
   if (max_nB == 0) return;
-  if (sym) {
-    LAUNCH_GEMM(max_nS, max_nB, nids, s, (k_nd_w<64, C, 1>), (k_nd_w<32, C, 1>), v, toff, kout, T, Lp, Wp);
+  LAUNCH_GEMM(max_nS, max_nB, nids, s, (k_nd_w<64, C, SYM>), (k_nd_w<32, C, SYM>), v, toff, kout, T, Lp, Wp);
+  if constexpr (SYM) {
     const bool small = small_tiles(max_nB, max_nB / 2, nids);
     const int nb = (max_nB + (small ? 31 : 63)) / (small ? 32 : 64);
     if (small)
@@ -938,12 +945,11 @@ void nd_products(const NDInv& v, int nids, int max_nS, int max_nB, int kout, int
     else
       hipLaunchKernelGGL((k_nd_schur<64, 1>), dim3(nb * (nb + 1) / 2, nids), dim3(256), 0, s, v, toff, Tc);
   } else {
-    LAUNCH_GEMM(max_nS, max_nB, nids, s, (k_nd_w<64, C, 0>), (k_nd_w<32, C, 0>), v, toff, kout, T, Lp, Wp);
     LAUNCH_GEMM(max_nB, max_nS, nids, s, (k_nd_x<64, C>), (k_nd_x<32, C>), v, kout, Lp);
     LAUNCH_GEMM(max_nB, max_nB, nids, s, (k_nd_schur<64, 0>), (k_nd_schur<32, 0>), v, toff, Tc);
   }
 }
-template void nd_products<cf>(const NDInv&, int, int, int, int, int, const long long*, cd*, cf*, cf*, hipStream_t);
-template void nd_products<cd>(const NDInv&, int, int, int, int, int, const long long*, cd*, cd*, cd*, hipStream_t);
+template void nd_products<cf>(const NDInv&, int, int, int, int, const long long*, cd*, cf*, cf*, hipStream_t);
+template void nd_products<cd>(const NDInv&, int, int, int, int, const long long*, cd*, cd*, cd*, hipStream_t);
 
 }  // namespace helm

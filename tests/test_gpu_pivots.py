@@ -123,3 +123,38 @@ def test_last_row_without_a_pivot_is_singular(monkeypatch, n):
     with pytest.raises(L.HelmError) as e:
         from_problem(p, cycle_prec="f64")
     assert e.value.code == L.HELM_ESINGULAR
+
+
+# undamped grids with fronts whose interiors are close to a resonance: (n, seed, G, schedule)
+RESONANT = [((428, 484), 536, 12.0, ("32", "1100")), ((28, 64, 28), 216, 8.0, ("8", "1")),
+            ((44, 48, 80), 135, 8.0, ("8", "1"))]
+
+
+@pytest.mark.parametrize("n,seed,G,schedule", RESONANT)
+def test_fp64_factors_near_interior_resonances(monkeypatch, n, seed, G, schedule):
+    """The blocks of a front that is close to singular are far from each other's rounding: left and
+    right ones are formed separately in FP64, so that the solve stays within the operator's own
+    condition, 100 eps cond_1(A3)."""
+    import scipy.sparse.linalg as spla
+    monkeypatch.setenv("HELM_ND_LEAF", schedule[0])
+    monkeypatch.setenv("HELM_ND_ROOT", schedule[1])
+    monkeypatch.setenv("HELM_ND_MERGE", "none")
+    h = 1.0 / max(n)
+    kap = synth.layered_slowness(n, 4, 2.0, seed)
+    p = synth.Problem("resonant", len(n), n, h, kap, synth.omega_for_G(G, h, kap.max()),
+                      tuple((0, 0) for _ in n), 0.0, 1.05, 0.0, [tuple(k // 2 for k in n)], G, alpha2=1.0)
+    print("interior resonances", n, flush=True)
+    H = oracle_hierarchy(p)
+    A = H.A[2].tocsc().astype(complex)
+    inv = spla.LinearOperator(A.shape, matvec=H.lu3.solve, rmatvec=lambda v: np.conj(H.lu3.solve(np.conj(v), "T")),
+                              dtype=complex)
+    cond = spla.norm(A, 1) * spla.onenormest(inv)
+    s = from_problem(p, cycle_prec="f64")
+    rng = np.random.default_rng(seed)
+    for op in (0, HELM_OP_C):
+        r = rng.standard_normal(A.shape[0]) + 1j * rng.standard_normal(A.shape[0])
+        x = H.lu3.solve(r) if op == 0 else np.conj(H.lu3.solve(np.conj(r)))
+        e = rel(s.coarse_solve(r, op=op).cpu().numpy(), x)
+        print("  error %.2e, eps cond %.2e" % (e, 2.0 ** -53 * cond), flush=True)
+        assert e < 100 * 2.0 ** -53 * cond
+    s.close()
