@@ -192,6 +192,13 @@ template <typename C, int RB, int FWD>
 static void rows_nr(const NDLaunchDev& L, const int* idx, const int* cidx, const C* M, C* upd, const C* src, C* x,
                     int conj, const NDRhs& rh, hipStream_t s) {
   int nr = rh.n >= 5 ? 8 : rh.n >= 3 ? 4 : rh.n;
+  // Right-hand sides that share a work-group read each entry once, but make its chain longer: they
+  // share only while the launch has 128 work-groups (us per FGMRES iteration of 8 right-hand sides,
+  // shared always / with this line / with 256: 64^2 68 / 63 / 62, 96^2 77 / 69 / 76, 200^2 132 / 114 /
+  // 123, 300^2 202 / 181 / 177, 32^3 179 / 148 / 149, 48^3 295 / 259 / 256; batches of 2 media x 7
+  // on 580^2 13.1 / 12.0 / 12.0 ms, on 160^2 1.88 / 1.82 / 2.08)
+  const int ipw = std::max(1, 4 / L.waves), blocks = (L.nrows + ipw - 1) / ipw;
+  while (nr > 1 && blocks * ((rh.n + nr - 1) / nr) < 128) nr /= 2;
   while (nr > 1 && nd_rows_lds(RB, L.waves, L.max_k, nr, sizeof(C)) > 65536) nr /= 2;
   if (nr == 8) launch_rows<C, RB, 8, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);
   else if (nr == 4) launch_rows<C, RB, 4, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);

@@ -78,3 +78,24 @@ def test_substitution_shares_entries_over_right_hand_sides(monkeypatch, n, leaf,
             assert torch.equal(xs[k], ref[k]), (nr, k)
     one.close()
     many.close()
+
+
+@pytest.mark.parametrize("n", [(1024, 640), (96, 88, 80)])
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_substitution_shares_entries_on_large_grids(n, prec):
+    """launches of enough work-groups that 2, 4 and 8 right-hand sides share one: bit for bit the
+    separate solves"""
+    import torch
+    p = rect_problem(n)
+    print("shared entries, large", n, prec, flush=True)
+    rng = np.random.default_rng(9)
+    qs = [torch.from_numpy(rng.standard_normal(p.N) + 1j * rng.standard_normal(p.N)).cuda() for _ in range(11)]
+    one = from_problem(p, nu=(1, 1), cycle_prec=prec)
+    ref = [one.solve(q, tol=1e-300, max_iter=2)[0] for q in qs]
+    one.close()
+    many = from_problem(p, nu=(1, 1), cycle_prec=prec, max_rhs=11)
+    for nr in (2, 3, 8, 11):
+        xs, _ = many.solve_many(qs[:nr], tol=1e-300, max_iter=2)
+        for k in range(nr):
+            assert torch.equal(xs[k], ref[k]), (nr, k)
+    many.close()
