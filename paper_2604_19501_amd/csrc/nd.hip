@@ -191,7 +191,12 @@ static void launch_rows(const NDLaunchDev& L, const int* idx, const int* cidx, c
 template <typename C, int RB, int FWD>
 static void rows_nr(const NDLaunchDev& L, const int* idx, const int* cidx, const C* M, C* upd, const C* src, C* x,
                     int conj, const NDRhs& rh, hipStream_t s) {
-  int nr = rh.n >= 5 ? 8 : rh.n >= 3 ? 4 : rh.n;
+  // In FP64 at most 2: with 16 waves of 128 registers, 8 spill 100 of them and 4 spill 13 (us per
+  // iteration of 9 right-hand sides, at most 8 / 4 / 2 / 1: 300^2 273 / 230 / 218 / 220, 800^2 1196 /
+  // 991 / 974 / 1061, 72^3 846 / 737 / 707 / 743, 112^3 3240 / 2963 / 2926 / 3071; of 2: 800^2 - / - /
+  // 327 / 348).  FP32 has no spills: 8 and 4 differ by 4 % at most, either way.
+  constexpr int MAX_NR = sizeof(C) == sizeof(cf) ? 8 : 2;
+  int nr = std::min(MAX_NR, rh.n >= 5 ? 8 : rh.n >= 3 ? 4 : rh.n);
   // Right-hand sides that share a work-group read each entry once, but make its chain longer: they
   // share only while the launch has 128 work-groups (us per FGMRES iteration of 8 right-hand sides,
   // shared always / with this line / with 256: 64^2 68 / 63 / 62, 96^2 77 / 69 / 76, 200^2 132 / 114 /
@@ -200,9 +205,11 @@ static void rows_nr(const NDLaunchDev& L, const int* idx, const int* cidx, const
   const int ipw = std::max(1, 4 / L.waves), blocks = (L.nrows + ipw - 1) / ipw;
   while (nr > 1 && blocks * ((rh.n + nr - 1) / nr) < 128) nr /= 2;
   while (nr > 1 && nd_rows_lds(RB, L.waves, L.max_k, nr, sizeof(C)) > 65536) nr /= 2;
-  if (nr == 8) launch_rows<C, RB, 8, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);
-  else if (nr == 4) launch_rows<C, RB, 4, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);
-  else if (nr == 2) launch_rows<C, RB, 2, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);
+  if constexpr (MAX_NR == 8) {
+    if (nr == 8) return launch_rows<C, RB, 8, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);
+    if (nr == 4) return launch_rows<C, RB, 4, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);
+  }
+  if (nr == 2) launch_rows<C, RB, 2, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);
   else launch_rows<C, RB, 1, FWD>(L, idx, cidx, M, upd, src, x, conj, rh, s);
 }
 template <typename C, int FWD>
