@@ -7,7 +7,7 @@ namespace helm {
 #define KMAXM 64
 #define KMAXIT 4096
 #define KNPT 4            // nodes per thread of the node kernels
-// small grids: one node per thread (kr_npt in krylov.hip)
+// smaller grids: one or two (kr_npt in krylov.hip)
 int kr_npt(long long N);
 inline long long kr_blocks(long long N) {
   const long long per = 256LL * kr_npt(N);

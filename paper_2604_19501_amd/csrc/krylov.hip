@@ -80,7 +80,7 @@ __device__ __forceinline__ long long node_of(int q) {
   return ((long long)blockIdx.x * NPT + q) * 256 + threadIdx.x;
 }
 // basis vectors in flight per thread of the Arnoldi passes
-template <int NPT> constexpr int KPF = NPT == 1 ? 4 : 1;
+template <int NPT> constexpr int KPF = 4 / NPT;
 
 // CMP: the compact fourth-order operator (no conjugate form), a separate instantiation of
 // every kernel that applies H: inlined into the 5/7-point kernels as a run-time branch it
@@ -646,16 +646,24 @@ void kr_init(const KrylovArgs& a, int max_iter, int seq, hipStream_t s) {
 // vector at a time, where one node per thread has four vectors in flight.  Per FGMRES
 // iteration, four nodes / one: 64^2 64.0 / 58.6 us, 200^2 90.7 / 85.2, 256^2 108.9 / 104.5,
 // 300^2 FP64 113.8 / 110.1, then 400^2 114.6 / 115.3, 80^3 FP64 255 / 262, 720^2 165 / 174.
-constexpr long long KNPT_LINE = 131072;
-int kr_npt(long long N) { return N <= KNPT_LINE ? 1 : KNPT; }
+// From 65536 to 131072 nodes several right-hand sides fill the chip by themselves and only pay for
+// one node's sums, so two nodes with two vectors in flight.  One node / two, for 1 and for 16
+// right-hand sides: 256^2 96 / 96 and 225 / 209 us, in FP64 92 / 91 and 274 / 258, 340^2 100 / 102 and
+// 317 / 291, 48^3 141 / 141 and 395 / 374; below, one right-hand side would lose (200^2 76 / 80).  The
+// line may not depend on the number of right-hand sides: the sums' order, and the bits, do on it.
+constexpr long long KNPT_LINE1 = 65536, KNPT_LINE = 131072;
+int kr_npt(long long N) { return N <= KNPT_LINE1 ? 1 : N <= KNPT_LINE ? 2 : KNPT; }
 // f(NPT, CMP) with the grid's nodes per thread and the outer operator's kind as constants
 template <class F>
 static void kr_dispatch(const KrylovArgs& a, F f) {
   using std::integral_constant;
   typedef integral_constant<int, 1> C1;
+  typedef integral_constant<int, 2> C2;
   typedef integral_constant<int, KNPT> C4;
   typedef integral_constant<int, 0> P5;
-  if (kr_npt(a.op.g.tot) == 1) a.op.compact ? f(C1(), C1()) : f(C1(), P5());
+  const int npt = kr_npt(a.op.g.tot);
+  if (npt == 1) a.op.compact ? f(C1(), C1()) : f(C1(), P5());
+  else if (npt == 2) a.op.compact ? f(C2(), C1()) : f(C2(), P5());
   else a.op.compact ? f(C4(), C1()) : f(C4(), P5());
 }
 void kr_residual(const KrylovArgs& a, const cd* x, const cd* b, int with_b, hipStream_t s) {

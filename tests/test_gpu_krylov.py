@@ -1,9 +1,10 @@
-"""The FGMRES passes' two node layouts (one node per thread up to 131072 nodes, four above), at
-the edges of their blocks and on both sides of that line."""
+"""The FGMRES passes' node layouts (one node per thread up to 65536 nodes, two up to 131072, four
+above), at the edges of their blocks and on both sides of those lines."""
 import numpy as np
 import pytest
 import torch
 
+import synth
 from oracle import operators as ops
 from tests.gpu_helpers import rect_problem
 
@@ -36,3 +37,26 @@ def test_estimate_is_the_residual(n, prec):
     assert abs(res - info["history"][-1]) <= 1e-12
     assert info["status"] != 0 or res <= 1e-8 * (1 + 1e-3)
     assert info["iterations"] == info2["iterations"] and torch.equal(x, x2)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("stack", ["p5", "compact"])
+@pytest.mark.parametrize("n", [(252, 256), (256, 256), (360, 360)])
+def test_two_nodes_per_thread(n, stack, prec):
+    """65021 nodes (one per thread), 66049 and 130321 (two, the last block partly filled), both outer
+    operators: the residual estimate is the returned solution's residual, to the bound above, and
+    right-hand sides in lock-step take the separate solves' bits"""
+    p = synth.paper_stack(n, "cubic") if stack == "compact" else rect_problem(n)
+    print("krylov two nodes", n, stack, prec, p.N, flush=True)
+    op = ops.helmholtz_compact if stack == "compact" else ops.helmholtz
+    H = op(p.n, p.h, p.slowness.ravel() ** 2, p.omega, ops.layer_sigma(p.n, p.layer, p.sigma_max))
+    rng = np.random.default_rng(7)
+    qs = [rng.standard_normal(p.N) + 1j * rng.standard_normal(p.N) for _ in range(3)]
+    s = from_problem(p, nu=(1, 1), cycle_prec=prec, restart=20, max_rhs=3)
+    one = [s.solve(q, tol=1e-8, max_iter=70, history=True) for q in qs]
+    many, _ = s.solve_many([torch.from_numpy(q).cuda() for q in qs], tol=1e-8, max_iter=70)
+    s.close()
+    for q, (x, info), y in zip(qs, one, many):
+        res = np.linalg.norm(q - H @ x.cpu().numpy()) / np.linalg.norm(q)
+        assert abs(res - info["history"][-1]) <= 1e-12
+        assert torch.equal(x, y)
